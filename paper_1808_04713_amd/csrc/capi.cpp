@@ -544,37 +544,44 @@ void build_device(Handle& h) {
   d.cm_pos = upload(h, cm_pos);
   // class tables and operators
   int NC = int(h.classes.size());
-  std::vector<int> cn(NC), cm(NC), cnr(NC), cgam(NC), cR(NC), creal(NC);
-  std::vector<int64_t> o_op1(NC), o_phi(NC), o_se(NC), o_E(NC), o_D(NC), o_G(NC), o_Kc(NC), o_V(NC);
-  std::vector<double2> op1, phi, Ex, Ey, Dinv, G, Kc;
+  std::vector<int> cn(NC), cm(NC), cnr(NC);
+  std::vector<int64_t> o_op1(NC), o_phi(NC), o_se(NC);
+  std::vector<double2> op1, phi, Dinv, Kc;
   std::vector<double2> se;
-  std::vector<double> V;
+  std::vector<double> mats, V;
   std::vector<int> gam, rmod;
+  std::vector<SepClass> sc(NC);
   for (int c = 0; c < NC; ++c) {
     const ElemClass& C = h.classes[c];
     cn[c] = C.n; cm[c] = C.m; cnr[c] = C.nr;
     o_op1[c] = op1.size(); o_phi[c] = phi.size(); o_se[c] = se.size();
-    o_E[c] = Ex.size(); o_D[c] = Dinv.size(); o_G[c] = G.size(); o_Kc[c] = Kc.size(); o_V[c] = V.size();
-    cgam[c] = gam.size(); cR[c] = rmod.size();
     for (auto& v : C.Op1.a) op1.push_back(make_double2(v.real(), v.imag()));
     for (auto& v : C.Phi.a) phi.push_back(make_double2(v.real(), v.imag()));
     for (auto& v : C.Se.a) se.push_back(make_double2(v.real(), v.imag()));
-    for (auto& v : C.Ex.a) Ex.push_back(make_double2(v.real(), v.imag()));
-    for (auto& v : C.Ey.a) Ey.push_back(make_double2(v.real(), v.imag()));
-    // a real pencil (no impedance or layer terms) gives an exactly real eigenbasis
-    creal[c] = 1;
-    for (auto& v : C.Ex.a) if (v.imag() != 0.0) creal[c] = 0;
-    for (auto& v : C.Ey.a) if (v.imag() != 0.0) creal[c] = 0;
+    // a real pencil (no impedance or layer terms along its direction) gives an
+    // exactly real eigenbasis; each by column
+    int64_t at[2];
+    int real[2];
+    for (int dir = 0; dir < 2; ++dir) {
+      const MatC& Eb = dir ? C.Ey : C.Ex;
+      at[dir] = int64_t(mats.size());
+      real[dir] = 1;
+      for (auto& v : Eb.a)
+        if (v.imag() != 0.0) real[dir] = 0;
+      for (auto& v : Eb.a) {
+        mats.push_back(v.real());
+        if (!real[dir]) mats.push_back(v.imag());
+      }
+    }
+    sc[c] = SepClass{at[0], at[1], int64_t(Dinv.size()), int64_t(Kc.size()), int64_t(V.size()), C.n, C.nr,
+                     C.m, int(rmod.size()), int(gam.size()), real[0], real[1], 0};
     for (auto& v : C.Dg) { cd iv = 1.0 / v; Dinv.push_back(make_double2(iv.real(), iv.imag())); }
-    for (auto& v : C.G.a) G.push_back(make_double2(v.real(), v.imag()));
     for (auto& v : C.Kc.a) Kc.push_back(make_double2(v.real(), v.imag()));
     std::vector<double> t = gll_nodes(C.n), row(C.n);
-    std::vector<double> Vc(size_t(C.n) * C.n);
     for (int i = 0; i < C.n; ++i) {
       vertex_basis(C.n, t[i], row.data());
-      for (int a = 0; a < C.n; ++a) Vc[i + size_t(C.n) * a] = row[a];
+      V.insert(V.end(), row.begin(), row.end());
     }
-    V.insert(V.end(), Vc.begin(), Vc.end());
     gam.insert(gam.end(), C.Gam.begin(), C.Gam.end());
     rmod.insert(rmod.end(), C.R.begin(), C.R.end());
   }
@@ -613,21 +620,45 @@ void build_device(Handle& h) {
     }
     d.slot_out = upload(h, out);
   }
-  d.cls_E = upload(h, o_E); d.cls_D = upload(h, o_D); d.cls_G = upload(h, o_G);
-  d.cls_real = upload(h, creal);
   {
-    std::vector<FdmRec> fr(size_t(h.E));
-    for (int e = 0; e < h.E; ++e) {
-      const int c = h.cls[e];
-      const ElemClass& C = h.classes[c];
-      fr[e] = FdmRec{h.dof_off[e], o_E[c], o_D[c], o_Kc[c], C.n, C.nr, cR[c], h.cm_off[e],
-                     h.slot_off[e], h.slot_off[e + 1], creal[c], c};
+    // separable element solves: records, and per bucket of classes of one kernel
+    // the items for every number of elements per workgroup
+    std::vector<SepElem> el(E);
+    for (int b = 0; b < E; ++b) el[b] = SepElem{h.dof_off[h.order[b]], h.cm_off[h.order[b]], h.slot_off[h.order[b]]};
+    // kernel -> (first position in order, class), the classes with complex
+    // eigenbases (twice the products, or more) first so that none is left for the tail
+    std::map<int, std::vector<std::pair<int, int>>> runs;
+    for (int b = 0; b < E; ++b)
+      if (b == 0 || h.cls[h.order[b]] != h.cls[h.order[b - 1]]) {
+        const int c = h.cls[h.order[b]];
+        runs[sep_len(h.classes[c].n)].push_back({b, c});
+      }
+    std::vector<SepItem> items;
+    h.sep_buckets.clear();
+    for (auto& kv : runs) {
+      std::stable_sort(kv.second.begin(), kv.second.end(), [&](const std::pair<int, int>& a, const std::pair<int, int>& b) {
+        return sc[a.second].rx + sc[a.second].ry < sc[b.second].rx + sc[b.second].ry;
+      });
+      SepBucket bk;
+      bk.N = kv.first;
+      for (int eg = 1; eg <= SEP_EG_MAX; ++eg) {
+        bk.first[eg - 1] = int(items.size());
+        for (auto& rn : kv.second) {
+          const ElemClass& C = h.classes[rn.second];
+          bk.n = std::max(bk.n, C.n);
+          bk.nr = std::max(bk.nr, C.nr);
+          const int ne = int(C.elems.size());
+          for (int q = 0; q < ne; q += eg) items.push_back(SepItem{sc[rn.second], rn.first + q, std::min(eg, ne - q)});
+        }
+        bk.count[eg - 1] = int(items.size()) - bk.first[eg - 1];
+      }
+      h.sep_buckets.push_back(bk);
     }
-    d.fdm_rec = upload(h, fr);
+    d.sep_elem = upload(h, el);
+    d.sep_items = upload(h, items);
   }
-  d.cls_Kc = upload(h, o_Kc); d.cls_V = upload(h, o_V);
-  d.cls_gam = upload(h, cgam); d.gam_modes = upload(h, gam);
-  d.cls_R = upload(h, cR); d.r_modes = upload(h, rmod);
+  d.gam_modes = upload(h, gam);
+  d.r_modes = upload(h, rmod);
   // plane-wave load tables
   {
     std::vector<int> cq(NC);
@@ -684,8 +715,10 @@ void build_device(Handle& h) {
     }
     d.mass_fac = upload(h, mf);
   }
-  d.Ex = upload(h, Ex); d.Ey = upload(h, Ey); d.Dinv = upload(h, Dinv);
-  d.G = upload(h, G); d.Kc = upload(h, Kc); d.V = upload(h, V);
+  d.sep_mat = upload(h, mats);
+  d.sep_gll = upload(h, V);
+  d.Dinv = upload(h, Dinv);
+  d.Kc = upload(h, Kc);
   std::vector<int64_t> kidx;
   std::vector<double2> kval;
   coarse_coo(h, kidx, kval);
@@ -979,62 +1012,31 @@ void apply_P(Handle& h, const double2* v, double2* u, int R, int prec) {
 
 // Solve A^ [x_I; x_R] = [y_I; y_R] element-wise (eq. block_matrix_inversion):
 // y_I is read from Y (coarse modes ignored; with nu, C_1^T nu subtracted at the
-// dual slots), or from X itself when Y is null; X receives the element
-// solution; y_R is assembled from Bfull's coarse modes (or zero when Bfull is
-// null), minus C_2^T nu when nu is given.
-void element_solve(Handle& h, double2* X, const double2* Bfull, const double2* nu, int R,
-                   const double2* Y = nullptr) {
+// dual slots); X receives the element solution; y_R is assembled from Y's coarse
+// modes, minus C_2^T nu when nu is given.  A coarse pass (x_R and K_e x_R) and,
+// after the coarse solve, the full solve of y - E_R mu, which folds the Woodbury
+// correction into the separable solve.
+void element_solve(Handle& h, double2* X, const double2* Y, const double2* nu, int R) {
   auto& d = h.d;
   hipStream_t s = h.stream;
   const double c = 16.0 * R, dof = double(h.dof), ncm = h.ncm, nK = h.nK;
-  if (Y && fdm_mf_ok(h, true)) {
-    // matrix cores: a coarse pass (x_R and K_e x_R) and, after the coarse
-    // solve, the full solve of y - E_R mu, which folds the Woodbury correction
-    // into the separable solve
-    {
-      Timed t(h, KF_FDM, dof * c + 2 * ncm * c, h.flops_fdm_coarse * R);
-      launch_fdm_mf(h, 1, Y, nullptr, R, s, nu, nullptr);
-    }
-    {
-      Timed t(h, KF_ASSEMBLE, 2 * ncm * c + nK * c, 0);
-      launch_assemble<double2>(h, d.cmA, Bfull, nu, -1.0, d.gK, R, s);
-    }
-    coarse_solve_timed(h, d.gK, d.wK, R);
-    {
-      Timed t(h, KF_FDM, 2 * dof * c + ncm * c + nK * c, h.flops_fdm * R);
-      launch_fdm_mf(h, 2, Y, X, R, s, nu, d.wK);
-    }
-    return;
-  }
-  if (!Y) {
-    Timed t(h, KF_ELEMENT_MISC, ncm * c, 0);
-    launch_zero_R(h, X, R, s);
-  }
   {
-    Timed t(h, KF_FDM, 2 * dof * c, h.flops_fdm * R);
-    if (Y) launch_fdm(h, Y, X, R, s, true, nu);   // out of place, coarse modes read as zero
-    else launch_fdm(h, X, X, R, s);
-  }
-  {
-    Timed t(h, KF_ELEMENT_MISC, 2 * ncm * c, 0);
-    launch_extract_kc(h, X, d.cmA, R, s);
+    Timed t(h, KF_FDM, dof * c + 2 * ncm * c, h.flops_fdm_coarse * R);
+    launch_sep_coarse(h, Y, R, s, nu);
   }
   {
     Timed t(h, KF_ASSEMBLE, 2 * ncm * c + nK * c, 0);
-    launch_assemble<double2>(h, d.cmA, Bfull, nu, -1.0, d.gK, R, s);
+    launch_assemble<double2>(h, d.cmA, Y, nu, -1.0, d.gK, R, s);
   }
-  {
-    coarse_solve_timed(h, d.gK, d.wK, R);
-  }
-  {
-    Timed t(h, KF_ELEMENT_MISC, 2 * dof * c + ncm * c, 0);
-    launch_correct(h, X, d.wK, R, s);
-  }
+  coarse_solve_timed(h, d.gK, d.wK, R);
+  Timed t(h, KF_FDM, 2 * dof * c + ncm * c + nK * c, h.flops_fdm * R);
+  launch_coarse_minus_tw(h, d.wK, R, false, s);
+  launch_sep_full(h, Y, X, R, s, nu);
 }
 
 // Interface right-hand side g = C_1 x_1 + C_2 x_2 of x = A^-1 b^ with the element
-// loads in full0 (eq. block_matrix_inversion).  On the matrix cores only the
-// dual-slot values of x are formed: the first pass of the element solve keeps
+// loads in full0 (eq. block_matrix_inversion).  Only the dual-slot values of x are
+// formed: the first pass of the element solve keeps
 // the slot values x_S and coarse-mode values x_R of A~^-1 b (coarse rows of b
 // zeroed), and the Woodbury correction restricted to the slots is
 // x_1 = x_S - Phi (x_R - T_e w) (Phi = G_S K_e, G = A~^-1 E_R), which the slot
@@ -1043,15 +1045,9 @@ void interface_rhs(Handle& h, double2* g, int R) {
   auto& d = h.d;
   hipStream_t s = h.stream;
   const double c = 16.0 * R, nsl = h.nslots, ncm = h.ncm, nK = h.nK, dof = double(h.dof);
-  if (!fdm_mf_ok(h, true)) {
-    element_solve(h, d.full1, d.full0, nullptr, R, d.full0);
-    Timed t(h, KF_ROWGATHER, nsl * c + h.nlam * c, 0);
-    launch_rowgather<double2>(h, d.full1, true, false, d.wK, g, R, s);   // C_1 x_1 + C_2 x_2
-    return;
-  }
   {
     Timed t(h, KF_FDM, dof * c + 2 * ncm * c + nsl * c, h.flops_fdm_coarse * R);
-    launch_fdm_mf(h, 1, d.full0, nullptr, R, s, nullptr, nullptr, 0, nullptr, d.slotA);   // x_S, x_R, K_e x_R
+    launch_sep_coarse(h, d.full0, R, s, nullptr, d.slotA);   // x_S, x_R, K_e x_R
   }
   {
     // K_e x_R of the loads, for the recovery of the same loads
@@ -1066,7 +1062,7 @@ void interface_rhs(Handle& h, double2* g, int R) {
   coarse_solve_timed(h, d.gK, d.wK, R);
   {
     Timed t(h, KF_SLOT_COARSE, nsl * c * 2 + 2 * ncm * c + h.phi_bytes, h.flops_coarse * R);
-    launch_coarse_minus_tw(h, d.wK, R, s);                      // cmX = x_R - T_e w
+    launch_coarse_minus_tw(h, d.wK, R, false, s);               // cmX = x_R - T_e w
     launch_slot_coarse_cm(h, d.slotA, d.cmX, d.slotB, R, s);    // x_1 = x_S - Phi cmX
   }
   Timed t(h, KF_ROWGATHER, nsl * c + h.nlam * c, 0);
@@ -1082,8 +1078,8 @@ void interface_rhs(Handle& h, double2* g, int R) {
 void recover(Handle& h, double2* X, const double2* nu, int R) {
   auto& d = h.d;
   hipStream_t s = h.stream;
-  if (!(fdm_mf_ok(h, true) && h.cmA_b_R == R)) {
-    element_solve(h, X, d.full0, nu, R, d.full0);
+  if (h.cmA_b_R != R) {
+    element_solve(h, X, d.full0, nu, R);
     return;
   }
   const double c = 16.0 * R, nsl = h.nslots, ncm = h.ncm, nK = h.nK, dof = double(h.dof);
@@ -1102,7 +1098,8 @@ void recover(Handle& h, double2* X, const double2* nu, int R) {
   coarse_solve_timed(h, d.gK, d.wK, R);
   {
     Timed t(h, KF_FDM, 2 * dof * c + 2 * ncm * c + nK * c, h.flops_fdm * R);
-    launch_fdm_mf(h, 2, d.full0, X, R, s, nu, d.wK, 0, d.cmA);
+    launch_coarse_minus_tw(h, d.wK, R, true, s);
+    launch_sep_full(h, d.full0, X, R, s, nu, d.cmA);
   }
 }
 
@@ -1327,7 +1324,7 @@ void far_prepare(Handle& h, int n_far, const double* angles, const uint8_t* insi
   f.DU = dalloc<double2>(h, size_t(std::max(1, f.nq)) * f.capR);
 }
 
-// Set-up autotuner: each candidate tile width of the matrix-core element solve
+// Set-up autotuner: each candidate tile width of the separable element solve
 // and of the slot operators runs three times on the handle's own mesh at max_rhs
 // columns (after one untimed launch); the fastest is kept.  The element solve
 // is timed as its two passes (coarse pass and corrected solve) on a zero input
@@ -1356,18 +1353,16 @@ static void autotune(Handle& h, bool fdm, bool slot) {
   try {
     launch_fill_zero(d.full0, int64_t(h.dof) * R, s);
     launch_fill_zero(d.w, int64_t(h.nlam) * R, s);
-    if (fdm && fdm_mf_ok(h, true)) {
+    if (fdm) {
       int best = 0;
       double tbest = 1e300;
       const size_t first = h.tune.size();
       for (int rc : {1, 2, 4, 8, 16}) {
         if (rc > std::min(16, R)) break;
-        h.fdm_rc = rc;
-        if (fdm_mf_rc(h, R) != rc) continue;   // does not fit shared memory
-        launch_fill_zero(d.wK, int64_t(h.nK) * R, s);
+        launch_fill_zero(d.cmX, int64_t(h.ncm) * R, s);
         const double ms = time3([&] {
-          launch_fdm_mf(h, 1, d.full0, nullptr, R, s, nullptr, nullptr, rc);
-          launch_fdm_mf(h, 2, d.full0, d.full1, R, s, nullptr, d.wK, rc);
+          launch_sep_coarse(h, d.full0, R, s, nullptr, nullptr, rc);
+          launch_sep_full(h, d.full0, d.full1, R, s, nullptr, nullptr, rc);
         });
         h.tune.push_back({"fdm_element_solve", rc, ms, false});
         if (ms < tbest) { tbest = ms; best = rc; }
@@ -1619,9 +1614,7 @@ hdp_status hdp_local_solve(hdp_handle* H, const hdp_c64* y, hdp_c64* x, int32_t 
   Handle& h = H->h;
   if (n_rhs < 1) fail(HDP_E_ARG, "n_rhs out of range");
   after_user(h);
-  if (fdm_mf_ok(h, false)) launch_fdm_mf(h, 0, reinterpret_cast<const double2*>(y), reinterpret_cast<double2*>(x), n_rhs,
-                                   h.stream, nullptr, nullptr);
-  else launch_fdm(h, reinterpret_cast<const double2*>(y), reinterpret_cast<double2*>(x), n_rhs, h.stream);
+  launch_sep_solve(h, reinterpret_cast<const double2*>(y), reinterpret_cast<double2*>(x), n_rhs, h.stream);
   HIPCHECK(hipStreamSynchronize(h.stream));
   return HDP_OK;
   API_END

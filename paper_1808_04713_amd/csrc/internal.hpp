@@ -112,11 +112,28 @@ struct SlotBlock {
   int64_t op1, se, phi;
   int e, c, so, cmo, m, nr, pad0, pad1;
 };
-// Per-element record of the matrix-core element solves, read with one load.
-struct FdmRec {
-  int64_t base, eoff, doff, kc;   // element's first coefficient; class's E, 1/D and K_e offsets
-  int n, nr, roff, cmo;           // modes per direction, coarse modes, coarse-mode list offset, first coarse mode
-  int s0, s1, real, cls;          // dual slots [s0, s1); 1 for a real eigenbasis; the class
+// The separable element solves (separable.hip): per element, in class order, its
+// first coefficient, coarse mode and dual slot; per class its sizes and the offsets of
+// its eigenbases, 1/D, K_e, GLL sampling matrix, coarse-mode and dual-slot lists.
+// Classes are bucketed by kernel (sep_len); a bucket's items are runs of
+// at most eg elements of one class in class order, for each eg up to SEP_EG_MAX.
+constexpr int SEP_EG_MAX = 8;
+enum { SEP_SOLVE = 0, SEP_COARSE = 1, SEP_FULL = 2, SEP_GLL = 3 };
+struct SepElem {
+  int64_t base;
+  int cmo, s0;
+};
+struct SepClass {
+  int64_t ex, ey, doff, kc, voff;
+  int n, nr, ns, roff, goff, rx, ry, pad;   // rx, ry: 1 where the eigenbasis is real
+};
+struct SepItem {
+  SepClass cls;
+  int pos, count;
+};
+struct SepBucket {
+  int N = 0, n = 0, nr = 0;   // kernel (sep_len), largest n and nr
+  int first[SEP_EG_MAX] = {0}, count[SEP_EG_MAX] = {0};   // items for 1, 2, .. elements per workgroup
 };
 // Per-slot input gather of the slot kernels: value = a0 v[s0] + a1 v[s1] (an
 // index < 0 contributes nothing), the row scalings already multiplied in.
@@ -287,22 +304,18 @@ struct Handle {
     int64_t nd_ld = 0;
     // per-class tables
     int *cls_n = nullptr, *cls_m = nullptr, *cls_nr = nullptr;
-    int* cls_real = nullptr;   // 1 when the class's eigenbasis is real
-    FdmRec* fdm_rec = nullptr; // per element
+    SepElem* sep_elem = nullptr;
+    SepItem* sep_items = nullptr;
+    double *sep_mat = nullptr, *sep_gll = nullptr;   // eigenbases, GLL sampling matrices
     int64_t *cls_op1 = nullptr, *cls_phi = nullptr, *cls_se = nullptr;   // offsets
-    int64_t *cls_E = nullptr, *cls_D = nullptr, *cls_G = nullptr, *cls_Kc = nullptr, *cls_V = nullptr;
-    int* cls_gam = nullptr;   // per class offset into gam_modes
-    int* gam_modes = nullptr;
-    int* cls_R = nullptr;     // per class offset into r_modes
-    int* r_modes = nullptr;
+    int *gam_modes = nullptr, *r_modes = nullptr;   // dual-slot and coarse modes of every class
     // operators
     double2 *op1 = nullptr, *phi = nullptr;   // FP64
     double2* se = nullptr;
     float2 *op1_f = nullptr, *phi_f = nullptr; // FP32 copies
     float2* se_f = nullptr;
     double2* mass_fac = nullptr;   // per element s_x s_y (layers only; null without layers)
-    double2 *Ex = nullptr, *Ey = nullptr, *Dinv = nullptr, *G = nullptr, *Kc = nullptr;
-    double* V = nullptr;      // GLL sampling matrices per class
+    double2 *Dinv = nullptr, *Kc = nullptr;
     double2* Kinv = nullptr;  // nK x nK (symmetric)
     // the same inverse as its upper 64 x 64 tiles (one-RHS coarse apply)
     double2 *Ksym = nullptr, *sym_part = nullptr;
@@ -356,7 +369,8 @@ struct Handle {
   } far;
   void* rocblas = nullptr;   // rocblas_handle for the batched coarse solve
   bool use_graphs = false;
-  int fdm_rc = 0;    // right-hand sides per block of the matrix-core element solve (0: heuristic)
+  int fdm_rc = 0;    // right-hand sides per workgroup of the separable element solve (0: by size)
+  std::vector<SepBucket> sep_buckets;
   int slot_rb = 32;  // right-hand sides per block of the matrix-core slot operators (16, 32, 64)
   struct Tune {
     std::string kernel;

@@ -30,8 +30,8 @@ template <class T2>
 void launch_slot_coarse(const Handle& h, const T2* X, const double2* w, T2* Z, int R, hipStream_t s);
 // Z = X - Phi_c cm with cm per-element coarse-mode values ([ncm][R], FP64)
 void launch_slot_coarse_cm(const Handle& h, const double2* X, const double2* cm, double2* Z, int R, hipStream_t s);
-// cmX -= T_e w at every coarse mode
-void launch_coarse_minus_tw(const Handle& h, const double2* w, int R, hipStream_t s);
+// cmX -= T_e w at every coarse mode (cmX = -T_e w with from_zero)
+void launch_coarse_minus_tw(const Handle& h, const double2* w, int R, bool from_zero, hipStream_t s);
 // u[row] = scale_row * (sum coef * src[pos(slot)] + (C_2 w)[row])  (pos = slot if full == false;
 // the C_2 term only on meshes with hanging edges and w != nullptr)
 template <class T2>
@@ -48,28 +48,19 @@ void launch_hblock(const Handle& h, bool y2, const double2* x, bool in_gather, c
 // w = K^-1 g (dense, FP64)
 void launch_coarse_solve(const Handle& h, const double2* g, double2* w, int R, hipStream_t s);
 
-// Full-element operations (arrays [dof][R])
-// With zero_coarse the element's coarse-mode entries of `in` are read as zero
-// (the solve of the interior problem from a full load vector, out of place);
-// with nu ([nlam][R]) the dual slots read in - C^T nu as well.
-void launch_fdm(const Handle& h, const double2* in, double2* out, int R, hipStream_t s, bool zero_coarse = false,
-                const double2* nu = nullptr);
-void launch_zero_R(const Handle& h, double2* X, int R, hipStream_t s);
-// Element solves on the matrix cores (every class n <= 32; fdm_mf_ok with
-// coarse: the two passes also fit shared memory): mode 0 out = A~^-1 in;
-// mode 1 the coarse pass (x_R into cmX, K_e x_R into cmA; in read with the
-// coarse rows zeroed and C_1^T nu subtracted when nu is given); mode 2 the full
-// solve with the Woodbury correction from cmX and the coarse solution w (with
-// kx: from K_e x_R given in kx, [ncm][R], instead of the first pass's x_R).  rc:
-// right-hand sides per block (0: the handle's choice).  xslot (mode 1): the
-// dual-slot values of the first pass's A~^-1 y as well ([nslots][R]).
-bool fdm_mf_ok(const Handle& h, bool coarse);
-int fdm_mf_rc(const Handle& h, int R);
-void launch_fdm_mf(const Handle& h, int mode, const double2* in, double2* out, int R, hipStream_t s,
-                   const double2* nu, const double2* w, int rc = 0, const double2* kx = nullptr,
-                   double2* xslot = nullptr);
-void launch_extract_kc(const Handle& h, const double2* X, double2* GL, int R, hipStream_t s);
-void launch_correct(const Handle& h, double2* X, const double2* w, int R, hipStream_t s);
+// Full-element operations (arrays [dof][R]; separable.hip).  Element solves by
+// the separable eigenbases, degrees up to 40: out = A~^-1 in; the coarse pass
+// (x_R into cmX, K_e x_R into cmA, with xslot [nslots][R] the dual-slot values of
+// A~^-1 y as well; in read with the coarse rows zeroed and C_1^T nu subtracted
+// when nu is given); the full solve with the Woodbury correction, cmX holding
+// x_R - T_e w, or -T_e w where kx gives K_e x_R ([ncm][R]).  rc: right-hand sides
+// per workgroup (0: the handle's choice).
+int sep_len(int n);
+void launch_sep_solve(const Handle& h, const double2* in, double2* out, int R, hipStream_t s);
+void launch_sep_coarse(const Handle& h, const double2* in, int R, hipStream_t s, const double2* nu,
+                       double2* xslot = nullptr, int rc = 0);
+void launch_sep_full(const Handle& h, const double2* in, double2* out, int R, hipStream_t s, const double2* nu,
+                     const double2* kx = nullptr, int rc = 0);
 void launch_gll(const Handle& h, const double2* X, double2* field, int R, int64_t rhs_stride,
                 int nrhs_out, hipStream_t s);
 

@@ -121,3 +121,19 @@ def test_interface_rhs_and_field_of_mixed_degrees(make):
     ref = np.concatenate(pb.gll_field(disc.mesh, disc.degrees, phis))
     assert rel(field.cpu().numpy()[0], ref) < 1e-10
     s.close()
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 7, 8, 11, 12, 15, 16, 17, 18, 19, 20, 21, 22, 23, 24, 28, 32])
+def test_local_solve_at_the_edges_of_every_kernel(p):
+    """Every number of modes at which the steps, row tiles or extra rows of the
+    separable kernels change, on a mesh with interior, edge and corner elements
+    (real, mixed and complex eigenbases), one column (several elements per
+    workgroup) and five; the tolerance is cond(E_x) cond(E_y) eps."""
+    w = W.small_uniform(4, p, 2.0 * p ** 0.5, l=1)
+    s = hdp().Solver(w)
+    for R in (1, 5):
+        rng = np.random.default_rng(p)
+        y = rng.standard_normal((s.dof, R)) + 1j * rng.standard_normal((s.dof, R))
+        x = s.local_solve(torch.from_numpy(y).cuda()).cpu().numpy()
+        assert rel(x, _dense_ref(w, y)) < 1e-10, R
+    s.close()
