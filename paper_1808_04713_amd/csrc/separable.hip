@@ -9,7 +9,8 @@
 // 16 lines at a time: it reads them, forms their products on the FP64 matrix
 // cores (16x16x4: rows of the eigenbasis by lines) and writes them back into the
 // same places, so that one stage serves every product and only a barrier parts
-// them.  The eigenbasis stays in the wave's registers for a whole product.  Where
+// them.  (Near an element resonance 1 / D amplifies rounding by many digits, so the
+// order of the products, x y x y, and of their sums is kept as it is.)  The eigenbasis stays in the wave's registers for a whole product.  Where
 // n passes a multiple of 16 by at most 6 (17 modes are the usual case) the rows
 // beyond it are summed on the vector ALUs instead of filling a second tile.
 //
@@ -35,6 +36,10 @@ namespace {
 
 constexpr int SEP_EG = SEP_EG_MAX;   // elements per workgroup, at most
 constexpr int SEP_FB = 16;           // entries per thread and batch of the staging loops
+
+__device__ __forceinline__ double2 cfma2(double2 a, double2 b, double2 c) {
+  return make_double2(c.x + a.x * b.x - a.y * b.y, c.y + a.x * b.y + a.y * b.x);
+}
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
@@ -147,8 +152,8 @@ __device__ __forceinline__ void tile_products(const SepMat<KS, MT, XR, CPLX>& M,
 }
 
 // One product on the stage A (entry (ix + n iy) ld + column): along x (the lines of
-// (iy, column)) or y; M(m, k) at mat[m ms + k ks].  With dinv the entries are read
-// times 1 / D (y lines: entry (i, k) of D at i + n k).
+// (iy, column)) or y; M(m, k) at mat[m ms + k ks].  With dinv (along x) the entries
+// are read times 1 / D (entry (k, j) of D at k + n j).
 template <int KS, int MT, int XR, bool CPLX>
 __device__ __forceinline__ void sep_product(const double* __restrict__ mat, int ms, int ks, bool along_x, int n,
                                             int ncol, int ld, double2* A, const double2* __restrict__ dinv = nullptr) {
@@ -159,7 +164,7 @@ __device__ __forceinline__ void sep_product(const double* __restrict__ mat, int 
   auto over = [&](int i) { return int((float(i) + 0.5f) * inv); };   // i / ncol (i below 2^15)
   tile_products(M, n, n * ncol, A, along_x ? ld : n * ld,
                 [&](int i) { const int q = over(i); return q * step + (i - q * ncol); },
-                [&](int i, int k) { return dinv[over(i) + n * k]; }, dinv != nullptr);
+                [&](int i, int k) { return dinv[k + n * over(i)]; }, dinv != nullptr);
 }
 
 template <int KS, int MT, int XR>
@@ -296,11 +301,9 @@ __global__ void __launch_bounds__(256) k_sep(SepArgs g, const double* __restrict
       const int a = i / ncol, c = i - a * ncol;
       double2 y = make_double2(0, 0);
       if (MODE == SEP_FULL) {
-        for (int b = 0; b < nr; ++b) {
-          const double2 k = K[a + nr * b], x = xs[b * ncol + c];
-          y.x -= k.x * x.x - k.y * x.y;
-          y.y -= k.x * x.y + k.y * x.x;
-        }
+        for (int b = 0; b < nr; ++b) y = cfma2(K[a + nr * b], xs[b * ncol + c], y);
+        y.x = -y.x;
+        y.y = -y.y;
         if (g.kx) {
           const int el = c / rc, r = c - el * rc;
           const double2 k = g.kx[(int64_t)(se[el].cmo + a) * R + r0 + r];
@@ -335,8 +338,8 @@ __global__ void __launch_bounds__(256) k_sep(SepArgs g, const double* __restrict
   // eigenbases by column: E(i, j) at i + n j
   sep_product_any<KS, MT, XR>(C.rx, mats + C.ex, n, 1, true, n, ncol, ld, A);
   sep_product_any<KS, MT, XR>(C.ry, mats + C.ey, n, 1, false, n, ncol, ld, A);
-  sep_product_any<KS, MT, XR>(C.ry, mats + C.ey, 1, n, false, n, ncol, ld, A, Dinv + C.doff);
-  sep_product_any<KS, MT, XR>(C.rx, mats + C.ex, 1, n, true, n, ncol, ld, A);
+  sep_product_any<KS, MT, XR>(C.rx, mats + C.ex, 1, n, true, n, ncol, ld, A, Dinv + C.doff);
+  sep_product_any<KS, MT, XR>(C.ry, mats + C.ey, 1, n, false, n, ncol, ld, A);
   if (MODE == SEP_COARSE) {
     const double2* __restrict__ K = Kc + C.kc;
     for (int i = threadIdx.x; i < nr * ncol; i += NTH) {
@@ -349,11 +352,7 @@ __global__ void __launch_bounds__(256) k_sep(SepArgs g, const double* __restrict
     for (int i = threadIdx.x; i < nr * ncol; i += NTH) {
       const int a = i / ncol, c = i - a * ncol, el = c / rc, r = c - el * rc;
       double2 y = make_double2(0, 0);
-      for (int b = 0; b < nr; ++b) {
-        const double2 k = K[a + nr * b], x = xs[b * ncol + c];
-        y.x += k.x * x.x - k.y * x.y;
-        y.y += k.x * x.y + k.y * x.x;
-      }
+      for (int b = 0; b < nr; ++b) y = cfma2(K[a + nr * b], xs[b * ncol + c], y);
       g.GL[(int64_t)(se[el].cmo + a) * R + r0 + r] = y;
     }
     if (g.xslot)
