@@ -5,7 +5,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhdp.so")
-SOURCES = ["setup.cpp", "coarse_nd.cpp", "capi.cpp", "kernels.hip", "separable.hip", "noalloc.hip"]
+SOURCES = ["setup.cpp", "coarse_nd.cpp", "capi.cpp", "kernels.hip", "separable.hip", "nested.hip", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -195,7 +195,7 @@ static void build_coarse_dense(Handle& h, const std::vector<int64_t>& kidx, cons
 static void coarse_solve_dense_tiles(Handle& h, const double2* g, double2* w, int R) {
   auto& d = h.d;
   NDView v;
-  v.off = d.dn_off; v.boff = d.dn_boff; v.bnd = d.dn_int + 2; v.uoff = d.dn_zero64; v.push = d.dn_int + 2;
+  v.off = d.dn_off; v.boff = d.dn_boff; v.bnd = d.dn_int + 2; v.uoff = d.dn_zero64;
   v.mD = d.dn_zero64; v.mL = d.dn_zero64; v.mLt = d.dn_zero64; v.fac = d.Kinv;
   v.push2 = d.dn_int + 2; v.child = d.dn_int; v.slot = nullptr; v.ld = pow2ceil(h.max_rhs); v.srows = 0; v.nK = h.nK;
   launch_nd_tiles(true, d.dn_tasks, h.dn_ntiles, h.dn_S, v, g, w, R, d.dn_P, h.stream);
@@ -207,35 +207,22 @@ static void build_coarse_nd(Handle& h, const std::vector<int64_t>& kidx, const s
   auto& d = h.d;
   NDHost f;
   nd_factor(h, kidx, kval, f);
-  d.nd_fac = upload(h, f.fac);
   d.nd_off = upload(h, h.nd_off);
   d.nd_boff = upload(h, h.nd_boff);
   d.nd_bnd = upload(h, h.nd_bnd);
   d.nd_uoff = upload(h, f.uoff);
-  d.nd_push = upload(h, f.push);
   d.nd_mD = upload(h, f.mD);
   d.nd_mL = upload(h, f.mL);
   d.nd_mLt = upload(h, f.mLt);
-  {
-    // the one-column sweeps read flattened task records (same order as t1f / t1b)
-    std::vector<ND1Fwd> f1(f.t1f.size());
-    for (size_t q = 0; q < f.t1f.size(); ++q) {
-      const int t = f.t1f[q].x, b = f.t1f[q].y;
-      const int o = h.nd_off[t], nI = h.nd_off[t + 1] - o;
-      const int64_t u = f.uoff[t] + b;
-      f1[q] = ND1Fwd{f.mL[t] + int64_t(nI) * b, u, o, nI, f.push[u], 0};
-    }
-    std::vector<ND1Bwd> b1(f.t1b.size());
-    for (size_t q = 0; q < f.t1b.size(); ++q) {
-      const int t = f.t1b[q].x, i = f.t1b[q].y;
-      const int o = h.nd_off[t], nI = h.nd_off[t + 1] - o;
-      const int64_t bo = h.nd_boff[t];
-      const int nB = int(h.nd_boff[t + 1] - bo);
-      b1[q] = ND1Bwd{f.mD[t] + int64_t(nI) * i, f.mLt[t] + int64_t(nB) * i, bo, o, nI, nB, i};
-    }
-    d.nd_f1 = upload(h, f1);
-    d.nd_b1 = upload(h, b1);
+  for (int bwd = 0; bwd < 2; ++bwd) {
+    ND1Plan p;
+    nd_units(h, f, bwd != 0, p);   // (may transpose blocks of the factor)
+    d.nd_u1[bwd] = upload(h, p.units);
+    d.nd_r1[bwd] = upload(h, p.rows);
+    d.nd_g1[bwd] = upload(h, p.gptr);
+    h.nd_l1[bwd] = p.launches;
   }
+  d.nd_fac = upload(h, f.fac);
   const size_t Rp = size_t(pow2ceil(h.max_rhs));
   {
     // task lists and partial tiles sized for every split the autotuner may try
@@ -259,15 +246,16 @@ static void build_coarse_nd(Handle& h, const std::vector<int64_t>& kidx, const s
     if (Rp > 1 && most > 0) d.nd_P = dalloc<double2>(h, size_t(most) * 32 * 64);
   }
   d.nd_urows = f.urows;
-  // one column: accumulators cleared per solve; several: the child slots,
-  // cleared once here (a slot row is either rewritten by every solve or never)
-  d.nd_FA = dalloc<double2>(h, size_t(h.nK + f.urows));
+  // the child slots, cleared once here (a slot row is either rewritten by every
+  // solve or never): one column's, and those of several at their own stride
+  d.nd_push2 = upload(h, f.push2);
+  d.nd_slot1 = dalloc<double2>(h, 2 * size_t(h.nK + f.urows));
+  HIPCHECK(hipMemsetAsync(d.nd_slot1, 0, 2 * size_t(h.nK + f.urows) * sizeof(double2), h.stream));
   if (Rp > 1) {
     d.nd_ld = int64_t(Rp);
     const size_t ns = 2 * size_t(h.nK + f.urows) * Rp;
     d.nd_slot = dalloc<double2>(h, ns);
     HIPCHECK(hipMemsetAsync(d.nd_slot, 0, ns * sizeof(double2), h.stream));
-    d.nd_push2 = upload(h, f.push2);
     d.nd_childv = upload(h, h.nd_child);
   }
   h.nd_levels = f.levels;
@@ -338,21 +326,12 @@ static void set_nd_split(Handle& h, int target) {
 static void coarse_solve_nd(Handle& h, const double2* g, double2* w, int R) {
   auto& d = h.d;
   NDView v;
-  v.off = d.nd_off; v.boff = d.nd_boff; v.bnd = d.nd_bnd; v.uoff = d.nd_uoff; v.push = d.nd_push;
+  v.off = d.nd_off; v.boff = d.nd_boff; v.bnd = d.nd_bnd; v.uoff = d.nd_uoff;
   v.mD = d.nd_mD; v.mL = d.nd_mL; v.mLt = d.nd_mLt; v.fac = d.nd_fac;
   const int nd = int(h.nd_levels.size());
   if (R == 1) {
-    double2* F = d.nd_FA;
-    double2* A = d.nd_FA + h.nK;
-    launch_fill_zero(F, int64_t(h.nK) + d.nd_urows, h.stream);   // a fill kernel (capturable)
-    for (int L = nd - 1; L >= 0; --L) {   // leaves first
-      const NDLevel& lv = h.nd_levels[L];
-      launch_nd_fwd1(d.nd_f1 + lv.f1, lv.nf1, v, g, F, A, h.stream);
-    }
-    for (int L = 0; L < nd; ++L) {   // root first
-      const NDLevel& lv = h.nd_levels[L];
-      launch_nd_bwd1(d.nd_b1 + lv.b1, lv.nb1, v, g, F, w, h.stream);
-    }
+    for (int bwd = 0; bwd < 2; ++bwd)
+      for (const ND1Launch& l : h.nd_l1[bwd]) launch_nd1(bwd != 0, l, h, g, w, h.stream);
     return;
   }
   v.push2 = d.nd_push2; v.child = d.nd_childv; v.slot = d.nd_slot; v.ld = d.nd_ld;
@@ -368,7 +347,7 @@ static void coarse_solve_nd(Handle& h, const double2* g, double2* w, int R) {
                          v.srows * d.nd_ld, d.nd_top_r, R, h.stream);
     NDView tv;
     tv.off = d.nd_top_off; tv.boff = d.nd_top_boff; tv.bnd = d.nd_top_int + 2; tv.uoff = d.nd_top_zero64;
-    tv.push = d.nd_top_int + 2; tv.mD = d.nd_top_zero64; tv.mL = d.nd_top_zero64; tv.mLt = d.nd_top_zero64;
+    tv.mD = d.nd_top_zero64; tv.mL = d.nd_top_zero64; tv.mLt = d.nd_top_zero64;
     tv.fac = d.nd_top_inv; tv.push2 = d.nd_top_int + 2; tv.child = d.nd_top_int; tv.slot = nullptr;
     tv.ld = d.nd_ld; tv.srows = 0; tv.nK = h.nd_top_n;
     launch_nd_tiles(true, d.nd_top_tasks, h.nd_top_ntiles, h.nd_top_S, tv, d.nd_top_r, d.nd_top_x, R, d.nd_top_P,

@@ -227,14 +227,12 @@ void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vec
     for (auto& th : pool) th.join();
     if (!err.empty()) fail(HDP_E_COARSE, err);
   }
-  // where each update row goes in the parent's front
+  // where each update row goes in the parent's front: slot k of the parent's rows
+  // for child k (interior rows first, then update rows from nK on)
   std::vector<int> parent(nn, -1);
   for (int t = 0; t < nn; ++t)
     for (int k = 0; k < 2; ++k)
       if (h.nd_child[2 * size_t(t) + k] >= 0) parent[h.nd_child[2 * size_t(t) + k]] = t;
-  // several columns: slot k of the parent's rows for child k (interior rows
-  // first, then update rows from nK on)
-  f.push.assign(size_t(std::max<int64_t>(1, urows)), 0);
   f.push2.assign(size_t(std::max<int64_t>(1, urows)), 0);
   const int64_t srows = nK + urows;
   if (2 * srows >= (int64_t(1) << 31)) fail(HDP_E_COARSE, "nested-dissection slot index overflows");
@@ -246,13 +244,11 @@ void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vec
     for (int a = 0; a < nB_of(t); ++a) {
       const int g = Bt[a];
       if (g >= h.nd_off[p] && g < h.nd_off[p + 1]) {
-        f.push[f.uoff[t] + a] = -1 - g;
         f.push2[f.uoff[t] + a] = int(k * srows + g);
       } else {
         const int* Bp = h.nd_bnd.data() + h.nd_boff[p];
         const int* it = std::lower_bound(Bp, Bp + nB_of(p), g);
         if (it == Bp + nB_of(p) || *it != g) fail(HDP_E_COARSE, "child boundary outside its parent's front");
-        f.push[f.uoff[t] + a] = int(f.uoff[p] + (it - Bp));
         f.push2[f.uoff[t] + a] = int(k * srows + nK + f.uoff[p] + (it - Bp));
       }
     }
@@ -272,16 +268,11 @@ void nd_tasks(const Handle& h, NDHost& f, int target) {
   auto nI_of = [&](int t) { return h.nd_off[t + 1] - h.nd_off[t]; };
   auto nB_of = [&](int t) { return int(h.nd_boff[t + 1] - h.nd_boff[t]); };
   f.levels.assign(maxd + 1, NDLevel{});
-  f.t1f.clear(); f.t1b.clear(); f.tRf.clear(); f.tRb.clear();
+  f.tRf.clear();
+  f.tRb.clear();
   f.part_tasks = 0;
   for (int dpt = 0; dpt <= maxd; ++dpt) {
     NDLevel& L = f.levels[dpt];
-    L.f1 = int(f.t1f.size()); L.b1 = int(f.t1b.size());
-    for (int t : by_depth[dpt]) {
-      for (int b = 0; b < nB_of(t); ++b) f.t1f.push_back(make_int2(t, b));
-      for (int i = 0; i < nI_of(t); ++i) f.t1b.push_back(make_int2(t, i));
-    }
-    L.nf1 = int(f.t1f.size()) - L.f1; L.nb1 = int(f.t1b.size()) - L.b1;
     for (int bwd = 0; bwd < 2; ++bwd) {
       int ntiles = 0, kmax = 0;
       for (int t : by_depth[dpt]) {
@@ -315,6 +306,123 @@ void nd_tasks(const Handle& h, NDHost& f, int target) {
       if (bwd) { L.bR = first; L.nbR = ntiles; L.Sb = S; }
       else { L.fR = first; L.nfR = ntiles; L.Sf = S; }
     }
+  }
+}
+
+// One-column sweeps.  A depth whose sums are at least ND1_ROW long on average (a
+// wave's lanes) runs a wave per output: 32 / 64 / 128 gave 6.63 / 5.60 / 5.67 ms per
+// solve of the 80x80 layered scatterer and 17.8 / 16.9 / 17.9 ms of the refined disk.
+// The other depths, near the leaves, run in units of ND1_P outputs,
+// and consecutive ones become the stages of one launch, a workgroup per subtree rooted
+// at the shallowest of them, while there are ND1_MIN_ROOTS subtrees (half the compute
+// units) and none holds more than ND1_MAX_WORK factor entries (0.6 MB, some 5 us for
+// a compute unit at 0.13 MB per us, about what the merged launches save).
+//
+// Backward units read D by columns; so that they use the same inverse as the rows
+// (the computed D is symmetric only up to its own error, which a nearly singular
+// front makes large), their D is transposed in the factor.  The sweeps at several
+// columns read D by rows, so a handle for more than one column runs rows here.
+void nd_units(const Handle& h, NDHost& f, bool bwd, ND1Plan& p) {
+  constexpr int ND1_ROW = 64, ND1_MIN_ROOTS = 128;
+  constexpr double ND1_MAX_WORK = 40000;
+  const int nn = int(h.nd_off.size()) - 1;
+  int maxd = 0;
+  for (int t = 0; t < nn; ++t) maxd = std::max(maxd, h.nd_depth[t]);
+  std::vector<std::vector<int>> by_depth(maxd + 1);
+  for (int t = 0; t < nn; ++t) by_depth[h.nd_depth[t]].push_back(t);
+  auto nI = [&](int t) { return h.nd_off[t + 1] - h.nd_off[t]; };
+  auto nB = [&](int t) { return int(h.nd_boff[t + 1] - h.nd_boff[t]); };
+  auto outs = [&](int t) { return bwd ? nI(t) : nB(t); };
+  auto sums = [&](int t) { return bwd ? nI(t) + nB(t) : nI(t); };
+  auto work = [&](int t) { return double(outs(t)) * sums(t); };
+  auto long_sums = [&](int d) {
+    if (bwd && h.max_rhs > 1) return true;   // the blocks D are not transposed (below)
+    double o = 0, k = 0;
+    for (int t : by_depth[d]) {
+      o += outs(t);
+      k += work(t);
+    }
+    return k >= ND1_ROW * o;
+  };
+  auto node_units = [&](int t) {
+    if (bwd) {
+      double2* D = f.fac.data() + f.mD[t];
+      for (int i = 0; i < nI(t); ++i)
+        for (int j = 0; j < i; ++j) std::swap(D[size_t(i) * nI(t) + j], D[size_t(j) * nI(t) + i]);
+    }
+    for (int o0 = 0; o0 < outs(t); o0 += ND1_P)
+      p.units.push_back(ND1Unit{bwd ? f.mD[t] : f.mLt[t], h.nd_boff[t], outs(t), o0, sums(t), nI(t), h.nd_off[t],
+                                int(f.uoff[t])});
+  };
+  p = ND1Plan{};
+  // the batches of depths [top, bottom], deepest first; sub[t]: work of t's subtree
+  // within its batch
+  std::vector<std::pair<int, int>> batches;
+  std::vector<double> sub(nn, 0.0);
+  for (int bottom = maxd; bottom >= 0;) {
+    for (int t : by_depth[bottom]) sub[t] = work(t);
+    int top = bottom;
+    while (!long_sums(bottom) && top > 0 && !long_sums(top - 1) && int(by_depth[top - 1].size()) >= ND1_MIN_ROOTS) {
+      double most = 0;
+      for (int t : by_depth[top - 1]) {
+        sub[t] = work(t);
+        for (int k = 0; k < 2; ++k) {
+          const int c = h.nd_child[2 * size_t(t) + k];
+          if (c >= 0) sub[t] += sub[c];
+        }
+        most = std::max(most, sub[t]);
+      }
+      if (most > ND1_MAX_WORK) break;
+      --top;
+    }
+    batches.push_back({top, bottom});
+    bottom = top - 1;
+  }
+  if (bwd) std::reverse(batches.begin(), batches.end());
+  for (auto& b : batches) {
+    ND1Launch L;
+    L.stages = b.second - b.first + 1;
+    if (L.stages == 1 && long_sums(b.first)) {
+      L.rows = true;
+      L.first = int64_t(p.rows.size());
+      for (int t : by_depth[b.first])
+        for (int j = 0; j < outs(t); ++j) {
+          if (bwd)
+            p.rows.push_back(ND1Row{f.mD[t] + int64_t(nI(t)) * j, f.mLt[t] + int64_t(nB(t)) * j, h.nd_boff[t], nI(t),
+                                    nB(t), h.nd_off[t], h.nd_off[t] + j});
+          else
+            p.rows.push_back(ND1Row{f.mL[t] + int64_t(nI(t)) * j, 0, 0, nI(t), 0, h.nd_off[t], int(f.uoff[t]) + j});
+        }
+      L.groups = int(int64_t(p.rows.size()) - L.first);
+    } else if (L.stages == 1) {
+      L.first = int64_t(p.gptr.size());
+      const int u0 = int(p.units.size());
+      for (int t : by_depth[b.first]) node_units(t);
+      const int n = int(p.units.size()) - u0;
+      for (int u = 0; u < n; u += L.waves) {
+        p.gptr.push_back(u0 + u);
+        p.gptr.push_back(u0 + std::min(n, u + L.waves));
+        ++L.groups;
+      }
+    } else {
+      L.first = int64_t(p.gptr.size());
+      L.waves = 8;
+      for (int root : by_depth[b.first]) {
+        std::vector<std::vector<int>> at(L.stages);
+        at[0].push_back(root);
+        for (int s = 0; s + 1 < L.stages; ++s)
+          for (int t : at[s])
+            for (int k = 0; k < 2; ++k)
+              if (h.nd_child[2 * size_t(t) + k] >= 0) at[s + 1].push_back(h.nd_child[2 * size_t(t) + k]);
+        for (int s = 0; s < L.stages; ++s) {
+          p.gptr.push_back(int(p.units.size()));
+          for (int t : at[bwd ? s : L.stages - 1 - s]) node_units(t);
+        }
+        p.gptr.push_back(int(p.units.size()));
+        ++L.groups;
+      }
+    }
+    p.launches.push_back(L);
   }
 }
 

@@ -71,26 +71,32 @@ struct Prof {
   int64_t n[KF_COUNT] = {0};
 };
 
-// One depth of the nested-dissection tree: ranges in the assembly-entry and
-// task arrays (R = 1 tasks are rows, other tasks 32-row tiles).
+// One depth of the nested-dissection tree at several columns: ranges in the task
+// arrays (32-row tiles).
 struct NDLevel {
-  int f1 = 0, nf1 = 0, b1 = 0, nb1 = 0;
   int fR = 0, nfR = 0, Sf = 1, bR = 0, nbR = 0, Sb = 1;   // first task, tiles, splits per tile
 };
 
-// One-column sweep tasks with the node tables already looked up, so that a
-// wave starts from one record: forward (row b of node t's L and where its
-// update goes) and backward (row i of node t's D^-1 and L^T).
-struct ND1Fwd {
-  int64_t lrow;   // offset of L_t row b in the factor
-  int64_t u;      // update row of (t, b)
-  int o, nI;      // node's first unknown and count
-  int push, pad;  // destination of the update (as NDHost::push)
+// One-column sweeps.  ND1Unit: ND1_P outputs o0 .. of a node's product out(j) =
+// sum_k M[k][j] z_k (M at mat, n_out columns, K rows), the node's first unknown o and
+// count nI, its first update row u (forward) and its boundary list (backward).
+// ND1Row: one output, the row of L (forward) or of D and L^T (backward).  ND1Launch:
+// either `groups` rows, or `groups` workgroups of `waves` waves with the units of
+// `stages` consecutive depths each (first: in the rows, or in the group pointers,
+// groups x (stages + 1)).
+constexpr int ND1_P = 8;
+struct ND1Unit {
+  int64_t mat, bo;
+  int n_out, o0, K, nI, o, u;
 };
-struct ND1Bwd {
-  int64_t drow, lrow;   // offsets of D^-1_t row i and L^T_t row i in the factor
-  int64_t bo;           // node's boundary list offset
-  int o, nI, nB, i;     // first unknown, count, boundary count, the row
+struct ND1Row {
+  int64_t m0, m1, bo;
+  int n0, n1, o, out;
+};
+struct ND1Launch {
+  int64_t first = 0;
+  int groups = 0, stages = 1, waves = 4;
+  bool rows = false;
 };
 
 // GMRES on the device: iterations queued beyond the one whose status the host
@@ -208,6 +214,7 @@ struct Handle {
   std::vector<int64_t> nd_boff;
   std::vector<int> nd_bnd;
   std::vector<NDLevel> nd_levels;   // per tree depth
+  std::vector<ND1Launch> nd_l1[2];  // one column: the launches of a forward and a backward sweep
   int nd_split = 1024;              // workgroups a depth's split tiles aim at (several columns)
   int dn_ntiles = 0, dn_S = 1;      // dense inverse at several columns: output tiles, splits
   int64_t nd_P_tasks = 0;           // partial tiles nd_P holds
@@ -275,12 +282,13 @@ struct Handle {
     double* cls_M = nullptr;   // per class the 1-D vertex mass matrix (n x n)
     int64_t* cls_Moff = nullptr;
     // nested-dissection coarse factor
-    double2 *nd_fac = nullptr, *nd_FA = nullptr;   // FA: front accumulators, n_K then update rows
-    int *nd_off = nullptr, *nd_bnd = nullptr, *nd_push = nullptr;
+    double2 *nd_fac = nullptr, *nd_slot1 = nullptr;   // slot1: one column's child slots, [2][nK + urows]
+    int *nd_off = nullptr, *nd_bnd = nullptr;
     int64_t *nd_boff = nullptr, *nd_uoff = nullptr, *nd_mD = nullptr, *nd_mL = nullptr, *nd_mLt = nullptr;
     int64_t nd_urows = 0;
-    ND1Fwd* nd_f1 = nullptr;
-    ND1Bwd* nd_b1 = nullptr;
+    ND1Unit* nd_u1[2] = {nullptr, nullptr};   // one column, forward and backward
+    ND1Row* nd_r1[2] = {nullptr, nullptr};
+    int* nd_g1[2] = {nullptr, nullptr};
     // one step of iterative refinement of the coarse solve (when the factor alone
     // misses 1e-10): K in CSR by row, residual and correction buffers
     int64_t* k_ptr = nullptr;
@@ -426,16 +434,13 @@ double coarse_band_bytes(int nK, const std::vector<int64_t>& kidx);
 // coarse_nd.cpp: the nested-dissection factor assembled on the host.  Per node
 // the blocks Dinv (nI x nI), L (nB x nI) and Lt = L^T, row-major, back to back in
 // fac; update rows (uoff) hold the boundary entries of the nodes' fronts, and
-// push names each row's place in the parent's front (-1 - unknown for a row the
-// parent owns, else the parent's update row).  Per tree depth: the row tasks of
+// push2 names each row's slot in the parent's front.  Per tree depth: the tasks of
 // the device sweeps.
 struct NDHost {
   std::vector<double2> fac;
   std::vector<int64_t> uoff, mD, mL, mLt;
   int64_t urows = 0;
-  std::vector<int> push;
-  std::vector<int> push2;     // slot row of each update row (several columns)
-  std::vector<int2> t1f, t1b;
+  std::vector<int> push2;     // slot row of each update row
   std::vector<int4> tRf, tRb;
   std::vector<NDLevel> levels;
   int64_t part_tasks = 0;     // largest split level (tiles x splits)
@@ -444,9 +449,18 @@ struct NDHost {
 void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vector<double2>& kval, NDHost& f);
 // every device block of the handle back through its allocator (or hipFree)
 void release_allocations(Handle& h);
-// the row tasks alone (levels, t1f/t1b, tRf/tRb, part_tasks) for a split target;
+// the tile tasks alone (levels, tRf/tRb, part_tasks) for a split target;
 // ND_SPLITS are the targets the set-up autotuner tries
 void nd_tasks(const Handle& h, NDHost& f, int target);
+// the units, rows and launches of the one-column sweeps, forward or backward (called
+// once each, before the factor is uploaded)
+struct ND1Plan {
+  std::vector<ND1Unit> units;
+  std::vector<ND1Row> rows;
+  std::vector<int> gptr;
+  std::vector<ND1Launch> launches;
+};
+void nd_units(const Handle& h, NDHost& f, bool bwd, ND1Plan& p);
 constexpr int ND_SPLITS[] = {256, 512, 1024, 2048};
 // most unknowns of the dense top block of the nested-dissection sweeps
 constexpr int64_t ND_TOP_MAX = 3072;

@@ -744,23 +744,14 @@ constexpr int SMJ = 32;   // outputs per workgroup
 constexpr int SMK = 32;   // rows of M staged per pass
 
 // ---------------------------------------------------------------------------
-// Nested-dissection coarse solve.  Node t owns the coarse unknowns
-// [off_t, off_t + nI_t) and has the boundary list bnd_t (nB_t ancestor unknowns);
+// Nested-dissection coarse solve at several columns (one column: nested.hip).  Node
+// t owns the coarse unknowns [off_t, off_t + nI_t) and has the boundary list bnd_t
+// (nB_t ancestor unknowns);
 // its factor blocks are Dinv_t (nI x nI), L_t (nB x nI) and Lt_t = L_t^T (nI x nB),
 // all row-major.  Forward, deepest level first, with Y_I = g_I + F_I:
-//   U_t = A_t - L_t Y_I, added into the parent's front
-// where F (own rows) and A (boundary rows) collect the children's updates;
+//   U_t = A_t - L_t Y_I, stored into t's slot of its parent's rows,
+// where F (own rows) and A (boundary rows) are the sums of the children's slots;
 // backward, root first:  X_I = Dinv_t Y_I - Lt_t X_B.
-// A front entry receives at most two additions onto zero (one per child), so
-// the atomic additions give the same sums in any order.  push[u] names where
-// update row u goes: the parent's own row -1 - push[u] of F, or row push[u] of A.
-
-__device__ __forceinline__ void nd_push(double2* __restrict__ F, double2* __restrict__ A, int dst, int64_t col,
-                                        int R, double2 v) {
-  double2* p = dst < 0 ? F + (int64_t)(-1 - dst) * R + col : A + (int64_t)dst * R + col;
-  unsafeAtomicAdd(&p->x, v.x);
-  unsafeAtomicAdd(&p->y, v.y);
-}
 
 // Node tables on the device.
 struct NDNodes {
@@ -768,7 +759,6 @@ struct NDNodes {
   const int64_t* boff;     // [n + 1] into bnd
   const int* bnd;
   const int64_t* uoff;     // first update row of node t
-  const int* push;         // per update row
   const int64_t* mD;       // factor offsets
   const int64_t* mL;
   const int64_t* mLt;
@@ -783,72 +773,6 @@ struct NDNodes {
   int64_t ld, srows;     // column stride, rows per slot (nK + urows)
   int nK;
 };
-
-// One column: one wave per output row, lanes over the row.
-__global__ void __launch_bounds__(NT) k_nd_fwd1(const ND1Fwd* __restrict__ task, int ntask,
-                                                const double2* __restrict__ fac, const double2* __restrict__ g,
-                                                double2* __restrict__ F, double2* __restrict__ A) {
-  const int lane = threadIdx.x & 63;
-  // the row is uniform over the wave: its record comes in through scalar loads
-  const int q = __builtin_amdgcn_readfirstlane(blockIdx.x * (NT / 64) + (threadIdx.x >> 6));
-  if (q >= ntask) return;
-  const ND1Fwd tk = task[q];
-  const int o = tk.o, nI = tk.nI;
-  const double2* Lr = fac + tk.lrow;
-  // the accumulated update row is read alongside the operands, not after the sum
-  double2 a = make_double2(0.0, 0.0);
-  if (lane == 0) a = A[tk.u];
-  double ax = 0, ay = 0;
-  for (int i = lane; i < nI; i += 64) {
-    const double2 m = Lr[i], y0 = g[o + i], y1 = F[o + i];
-    const double yx = y0.x + y1.x, yy = y0.y + y1.y;
-    ax += m.x * yx - m.y * yy;
-    ay += m.x * yy + m.y * yx;
-  }
-  for (int sh = 32; sh > 0; sh >>= 1) {
-    ax += __shfl_xor(ax, sh, 64);
-    ay += __shfl_xor(ay, sh, 64);
-  }
-  if (lane == 0) nd_push(F, A, tk.push, 0, 1, make_double2(a.x - ax, a.y - ay));
-}
-
-__global__ void __launch_bounds__(NT) k_nd_bwd1(const ND1Bwd* __restrict__ task, int ntask,
-                                                const double2* __restrict__ fac, const int* __restrict__ bnd,
-                                                const double2* __restrict__ g, const double2* __restrict__ F,
-                                                double2* __restrict__ X) {
-  const int lane = threadIdx.x & 63;
-  const int q = __builtin_amdgcn_readfirstlane(blockIdx.x * (NT / 64) + (threadIdx.x >> 6));
-  if (q >= ntask) return;
-  const ND1Bwd tk = task[q];
-  const int o = tk.o, nI = tk.nI, nB = tk.nB;
-  const double2* Dr = fac + tk.drow;
-  const double2* Lr = fac + tk.lrow;
-  double ax = 0, ay = 0;
-  // the first boundary gather (index, then value) is the longest chain: start it first
-  double2 m0 = make_double2(0.0, 0.0), x0 = make_double2(0.0, 0.0);
-  if (lane < nB) {
-    m0 = Lr[lane];
-    x0 = X[bnd[tk.bo + lane]];
-  }
-  for (int k = lane; k < nI; k += 64) {
-    const double2 m = Dr[k], y0 = g[o + k], y1 = F[o + k];
-    const double yx = y0.x + y1.x, yy = y0.y + y1.y;
-    ax += m.x * yx - m.y * yy;
-    ay += m.x * yy + m.y * yx;
-  }
-  ax -= m0.x * x0.x - m0.y * x0.y;
-  ay -= m0.x * x0.y + m0.y * x0.x;
-  for (int b = lane + 64; b < nB; b += 64) {
-    const double2 m = Lr[b], x = X[bnd[tk.bo + b]];
-    ax -= m.x * x.x - m.y * x.y;
-    ay -= m.x * x.y + m.y * x.x;
-  }
-  for (int sh = 32; sh > 0; sh >>= 1) {
-    ax += __shfl_xor(ax, sh, 64);
-    ay += __shfl_xor(ay, sh, 64);
-  }
-  if (lane == 0) X[o + tk.i] = make_double2(ax, ay);
-}
 
 // Several columns (R <= 64, lane = column): a workgroup owns 32 outputs of a
 // node and a range [i0, i1) of the summation (the top levels of the tree hold few
@@ -2799,25 +2723,11 @@ void launch_fill_zero(double2* x, int64_t count, hipStream_t s) {
   HIPCHECK(hipGetLastError());
 }
 
-void launch_nd_fwd1(const ND1Fwd* task, int ntask, const NDView& v, const double2* g, double2* F, double2* A,
-                    hipStream_t s) {
-  if (ntask == 0) return;
-  hipLaunchKernelGGL(k_nd_fwd1, dim3(nblocks(ntask, NT / 64)), dim3(NT), 0, s, task, ntask, v.fac, g, F, A);
-  HIPCHECK(hipGetLastError());
-}
-
-void launch_nd_bwd1(const ND1Bwd* task, int ntask, const NDView& v, const double2* g, const double2* F, double2* X,
-                    hipStream_t s) {
-  if (ntask == 0) return;
-  hipLaunchKernelGGL(k_nd_bwd1, dim3(nblocks(ntask, NT / 64)), dim3(NT), 0, s, task, ntask, v.fac, v.bnd, g, F, X);
-  HIPCHECK(hipGetLastError());
-}
-
 void launch_nd_tiles(bool bwd, const int4* task, int ntiles, int S, const NDView& v, const double2* g, double2* X,
                      int R, double2* P, hipStream_t s) {
   if (ntiles == 0) return;
   if (R > v.ld) fail(HDP_E_ARG, "nested-dissection sweep: more columns than the slot stride");
-  const NDNodes nd{v.off, v.boff, v.bnd, v.uoff, v.push, v.mD, v.mL, v.mLt, v.fac,
+  const NDNodes nd{v.off, v.boff, v.bnd, v.uoff, v.mD, v.mL, v.mLt, v.fac,
                    v.push2, v.child, v.slot, v.ld, v.srows, v.nK};
   double2* part = S > 1 ? P : nullptr;
   const unsigned nt = unsigned(ntiles) * unsigned(S);

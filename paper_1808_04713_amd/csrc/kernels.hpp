@@ -78,14 +78,11 @@ void launch_axpby(const double2* x, const double2* y, double2* z, int64_t count,
 void launch_cast_f(const double2* x, float2* y, int64_t count, hipStream_t s);
 void launch_cast_d(const float2* x, double2* y, int64_t count, hipStream_t s);
 // Nested-dissection coarse solve (device views of the node tables and the factor).
-// F (n_K rows) and A (update rows) start at zero and collect the children's
-// updates; push[u] < 0 sends update row u to F row -1 - push[u], else to A row push[u].
 struct NDView {
   const int* off = nullptr;
   const int64_t* boff = nullptr;
   const int* bnd = nullptr;
   const int64_t* uoff = nullptr;
-  const int* push = nullptr;
   const int64_t *mD = nullptr, *mL = nullptr, *mLt = nullptr;
   const double2* fac = nullptr;
   // several columns: two child slots per front row at column stride ld (rows
@@ -97,12 +94,9 @@ struct NDView {
   int64_t ld = 0, srows = 0;
   int nK = 0;
 };
-// one column: tasks {node, row}; forward U = A - L (g + F)_I pushed to the parent,
-// backward X_I = Dinv (g + F)_I - Lt X_B
-void launch_nd_fwd1(const ND1Fwd* task, int ntask, const NDView& v, const double2* g, double2* F, double2* A,
-                    hipStream_t s);
-void launch_nd_bwd1(const ND1Bwd* task, int ntask, const NDView& v, const double2* g, const double2* F, double2* X,
-                    hipStream_t s);
+// one column (nested.hip): one launch of the forward (the children's updates into
+// their parents' slots) or the backward sweep (X)
+void launch_nd1(bool bwd, const ND1Launch& l, const Handle& h, const double2* g, double2* X, hipStream_t s);
 // several columns (R <= ld): ntiles output tiles of 32 rows, each split into S
 // tasks {node, first row, i0, i1} over the summation; with S > 1 the partial
 // tiles go to P (ntiles * S * 32 * 64 values) and a second kernel adds them

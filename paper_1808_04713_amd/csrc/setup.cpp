@@ -1139,7 +1139,8 @@ void build_host(Handle& h, const hdp_mesh* mesh, const hdp_problem* prob) {
   // (a requested factor gets small blocks, so that small meshes exercise it too;
   // solves of 9 or more columns take leaves of up to 192 unknowns, whose fewer,
   // fuller launches are faster there: 0.476 against 0.483 ms per 64-column solve
-  // on the 64x64 scatterer, where one column keeps 96)
+  // on the 64x64 scatterer; one column keeps 96, where 32 / 48 / 96 gave 178 / 178 /
+  // 162 us per coarse solve of the 80x80 layered scatterer)
   const bool requested = h.coarse_mode >= 0;
   if (h.coarse_mode < 0) h.coarse_mode = h.nK > 6000 ? 2 : 0;
   if (h.coarse_mode == 2) order_coarse_nd(h, requested ? 32 : (h.max_rhs >= 9 ? 192 : 96));

@@ -285,6 +285,26 @@ def test_coarse_solvers_against_the_oracle(name, coarse, oracles):
     s.close()
 
 
+def test_one_column_sweeps_of_a_deep_tree():
+    """A tree of 128 and more subtrees, whose depths near the leaves run as stages
+    of one launch: the interface operator at one column with the nested-dissection
+    factor against the dense inverse of the same coarse matrix (both set-up checks
+    bound the difference)."""
+    w = W.small_uniform(44, 4, 60.0, l=2)
+    sn = hdp().Solver(w, coarse="nd", max_iter=10)
+    sd = hdp().Solver(w, coarse="dense", max_iter=10)
+    assert sn.info["coarse_blocks"] >= 255
+    rng = np.random.default_rng(3)
+    bound = 1e3 * max(sn.info["coarse_residual"], sd.info["coarse_residual"], 1e-15)
+    for _ in range(2):   # a second solve finds the slots of the first
+        v = rng.standard_normal((sn.n_lambda, 1)) + 1j * rng.standard_normal((sn.n_lambda, 1))
+        a = sn.apply_interface(torch.from_numpy(v).cuda()).cpu().numpy()
+        b = sd.apply_interface(torch.from_numpy(v).cuda()).cpu().numpy()
+        assert rel(a, b) < bound < 1e-7
+    sn.close()
+    sd.close()
+
+
 def test_handle_memory_from_the_callers_allocator(oracles):
     """hdp_options.allocator: with torch's caching allocator the handle's device
     memory comes from torch's pool (torch.cuda.memory_allocated grows by at least
