@@ -171,13 +171,13 @@ static void build_coarse_dense(Handle& h, const std::vector<int64_t>& kidx, cons
   h.coarse_bytes1 = 16.0 * double(nK) * double(nK + 1) / 2;
   // several columns: w = K^-T g by the nested-dissection tile kernels, the inverse
   // taken as the diagonal block of a one-node tree (no boundary, no children);
-  // 32-row output tiles, each tile's sum split so that about 1024 workgroups run
+  // each output tile's sum split so that about 1024 workgroups run
   if (pow2ceil(h.max_rhs) >= 4) {
-    const int ntiles = int((nK + 31) / 32);
-    const int S = std::max(1, std::min((1024 + ntiles - 1) / ntiles, ntiles));
+    const int ntiles = int((nK + ND_TILE - 1) / ND_TILE);
+    const int S = std::max(1, std::min((1024 + ntiles - 1) / ntiles, int(nK + 63) / 64));
     const int chunk = int((nK + S - 1) / S);
     std::vector<int4> tasks;
-    for (int j = 0; j < int(nK); j += 32)
+    for (int j = 0; j < int(nK); j += ND_TILE)
       for (int c = 0; c < S; ++c)
         tasks.push_back(make_int4(0, j, std::min(int(nK), c * chunk), std::min(int(nK), (c + 1) * chunk)));
     d.dn_tasks = upload(h, tasks);
@@ -187,7 +187,7 @@ static void build_coarse_dense(Handle& h, const std::vector<int64_t>& kidx, cons
     d.dn_int = upload(h, std::vector<int>{-1, -1, 0});
     h.dn_ntiles = ntiles;
     h.dn_S = S;
-    if (S > 1) d.dn_P = dalloc<double2>(h, size_t(ntiles) * S * 32 * 64);
+    if (S > 1) d.dn_P = dalloc<double2>(h, size_t(ntiles) * S * ND_TILE * 64);
   }
 }
 
@@ -243,7 +243,7 @@ static void build_coarse_nd(Handle& h, const std::vector<int64_t>& kidx, const s
     if (!f.tRf.empty()) HIPCHECK(hipMemcpy(d.nd_tRf, f.tRf.data(), f.tRf.size() * sizeof(int4), hipMemcpyHostToDevice));
     if (!f.tRb.empty()) HIPCHECK(hipMemcpy(d.nd_tRb, f.tRb.data(), f.tRb.size() * sizeof(int4), hipMemcpyHostToDevice));
     h.nd_P_tasks = Rp > 1 ? most : 0;
-    if (Rp > 1 && most > 0) d.nd_P = dalloc<double2>(h, size_t(most) * 32 * 64);
+    if (Rp > 1 && most > 0) d.nd_P = dalloc<double2>(h, size_t(most) * ND_TILE * 64);
   }
   d.nd_urows = f.urows;
   // the child slots, cleared once here (a slot row is either rewritten by every
@@ -391,19 +391,19 @@ static void build_nd_top(Handle& h, const std::vector<int64_t>& kidx, const std:
     launch_nd_top_collect(n, d.nd_top_idx, d.wK, Rp, k0, cols, d.nd_top_inv, h.stream);
     HIPCHECK(hipStreamSynchronize(h.stream));   // hidx is rewritten by the next batch
   }
-  // 32-row output tiles, each tile's sum split so that about 1024 workgroups run
-  const int ntiles = (n + 31) / 32;
-  const int S = std::max(1, std::min((1024 + ntiles - 1) / ntiles, ntiles));
+  // each output tile's sum split so that about 1024 workgroups run
+  const int ntiles = (n + ND_TILE - 1) / ND_TILE;
+  const int S = std::max(1, std::min((1024 + ntiles - 1) / ntiles, (n + 63) / 64));
   const int chunk = (n + S - 1) / S;
   std::vector<int4> tasks;
-  for (int j = 0; j < n; j += 32)
+  for (int j = 0; j < n; j += ND_TILE)
     for (int c = 0; c < S; ++c) tasks.push_back(make_int4(0, j, std::min(n, c * chunk), std::min(n, (c + 1) * chunk)));
   d.nd_top_tasks = upload(h, tasks);
   d.nd_top_off = upload(h, std::vector<int>{0, n});
   d.nd_top_boff = upload(h, std::vector<int64_t>{0, 0});
   d.nd_top_zero64 = upload(h, std::vector<int64_t>{0});
   d.nd_top_int = upload(h, std::vector<int>{-1, -1, 0});
-  if (S > 1) d.nd_top_P = dalloc<double2>(h, size_t(ntiles) * S * 32 * 64);
+  if (S > 1) d.nd_top_P = dalloc<double2>(h, size_t(ntiles) * S * ND_TILE * 64);
   h.nd_top_ntiles = ntiles;
   h.nd_top_S = S;
   h.nd_top_n = n;

@@ -256,8 +256,8 @@ void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vec
   nd_tasks(h, f, 1024);
 }
 
-// Row tasks of the device sweeps, depth by depth.  Several columns: tiles of 32
-// outputs; a depth with few tiles splits each tile's sum so that about `target`
+// Row tasks of the device sweeps, depth by depth.  Several columns: tiles of
+// ND_TILE outputs; a depth with few tiles splits each tile's sum so that about `target`
 // workgroups run (the set-up autotuner tries several targets).
 void nd_tasks(const Handle& h, NDHost& f, int target) {
   const int nn = int(h.nd_off.size()) - 1;
@@ -277,11 +277,11 @@ void nd_tasks(const Handle& h, NDHost& f, int target) {
       int ntiles = 0, kmax = 0;
       for (int t : by_depth[dpt]) {
         const int nout = bwd ? nI_of(t) : nB_of(t);
-        ntiles += (nout + 31) / 32;
+        ntiles += (nout + ND_TILE - 1) / ND_TILE;
         if (nout > 0) kmax = std::max(kmax, bwd ? nI_of(t) + nB_of(t) : nI_of(t));
       }
       int S = 1;
-      if (ntiles > 0) S = std::max(1, std::min((target + ntiles - 1) / ntiles, (kmax + 31) / 32));
+      if (ntiles > 0) S = std::max(1, std::min((target + ntiles - 1) / ntiles, (kmax + 63) / 64));   // at least 16 rows for each of a tile's four waves
       std::vector<int4>& T = bwd ? f.tRb : f.tRf;
       const int first = int(T.size());
       // nodes with the longest sums first: a depth whose tiles overflow one round
@@ -296,7 +296,7 @@ void nd_tasks(const Handle& h, NDHost& f, int target) {
         const int nout = bwd ? nI_of(t) : nB_of(t);
         const int K = bwd ? nI_of(t) + nB_of(t) : nI_of(t);
         const int chunk = (K + S - 1) / S;
-        for (int j = 0; j < nout; j += 32)
+        for (int j = 0; j < nout; j += ND_TILE)
           for (int c = 0; c < S; ++c) {
             const int i0 = std::min(K, c * chunk), i1 = std::min(K, (c + 1) * chunk);
             T.push_back(make_int4(t, j, i0, i1));

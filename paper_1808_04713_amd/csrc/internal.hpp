@@ -72,7 +72,8 @@ struct Prof {
 };
 
 // One depth of the nested-dissection tree at several columns: ranges in the task
-// arrays (32-row tiles).
+// arrays (tiles of ND_TILE output rows).
+constexpr int ND_TILE = 16;
 struct NDLevel {
   int fR = 0, nfR = 0, Sf = 1, bR = 0, nbR = 0, Sb = 1;   // first task, tiles, splits per tile
 };

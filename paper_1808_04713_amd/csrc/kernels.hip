@@ -739,296 +739,6 @@ __global__ void __launch_bounds__(NT) k_hblock(int nh, const int* __restrict__ b
   }
 }
 
-// Tiles of the nested-dissection products (several columns).
-constexpr int SMJ = 32;   // outputs per workgroup
-constexpr int SMK = 32;   // rows of M staged per pass
-
-// ---------------------------------------------------------------------------
-// Nested-dissection coarse solve at several columns (one column: nested.hip).  Node
-// t owns the coarse unknowns [off_t, off_t + nI_t) and has the boundary list bnd_t
-// (nB_t ancestor unknowns);
-// its factor blocks are Dinv_t (nI x nI), L_t (nB x nI) and Lt_t = L_t^T (nI x nB),
-// all row-major.  Forward, deepest level first, with Y_I = g_I + F_I:
-//   U_t = A_t - L_t Y_I, stored into t's slot of its parent's rows,
-// where F (own rows) and A (boundary rows) are the sums of the children's slots;
-// backward, root first:  X_I = Dinv_t Y_I - Lt_t X_B.
-
-// Node tables on the device.
-struct NDNodes {
-  const int* off;          // [n + 1]
-  const int64_t* boff;     // [n + 1] into bnd
-  const int* bnd;
-  const int64_t* uoff;     // first update row of node t
-  const int64_t* mD;       // factor offsets
-  const int64_t* mL;
-  const int64_t* mLt;
-  const double2* fac;
-  // several columns: each front row has two slots (one per child) at a fixed
-  // column stride ld; update row u of a node goes by a plain store to slot row
-  // push2[u] (slot k of the parent's interior row, or of its update row nK + a);
-  // slot rows no child writes stay zero from set-up
-  const int* push2;
-  const int* child;      // [2 n], -1 where absent
-  double2* slot;         // [2][nK + urows][ld]
-  int64_t ld, srows;     // column stride, rows per slot (nK + urows)
-  int nK;
-};
-
-// Several columns (R <= 64, lane = column): a workgroup owns 32 outputs of a
-// node and a range [i0, i1) of the summation (the top levels of the tree hold few
-// large nodes, so their sums are split over several workgroups and the partial
-// tiles added by k_nd_reduce).  32-row tiles of the factor block go through LDS
-// and are read back as wave-wide broadcasts; the operand rows are read coalesced
-// (gathered through xidx when given; X2, when given, is added to X).
-// acc += sum_i M[i + K j] X_row(i) for this thread's 8 outputs.
-__device__ __forceinline__ void nd_mm_core(const double2* __restrict__ M, int K, int i0, int i1, int n_out, int j0,
-                                           const double2* __restrict__ X, const double2* __restrict__ X2,
-                                           int64_t xbase, const int* __restrict__ xidx, int R, double2 (&acc)[8],
-                                           int64_t ld2 = 0, int64_t sst = 0) {
-  __shared__ double2 Ms[SMK][SMJ + 1];
-  const int r = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const bool live = r < R;
-  for (int ib = i0; ib < i1; ib += SMK) {
-    const int nk = min(SMK, i1 - ib);
-    for (int e = threadIdx.x; e < SMK * SMJ; e += NT) {
-      const int jj = e / SMK, kk = e % SMK;
-      Ms[kk][jj] = (kk < nk && j0 + jj < n_out) ? M[(ib + kk) + (int64_t)K * (j0 + jj)] : make_double2(0, 0);
-    }
-    __syncthreads();
-    if (live)
-      for (int kk = 0; kk < nk; ++kk) {
-        const int64_t row = xidx ? (int64_t)xidx[ib + kk] : xbase + ib + kk;
-        double2 x = X[row * R + r];
-        if (X2) {
-          const double2 x2 = X2[row * ld2 + r], x3 = X2[sst + row * ld2 + r];
-          x.x += x2.x + x3.x;
-          x.y += x2.y + x3.y;
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) acc[t] = cfma(Ms[kk][wv * 8 + t], x, acc[t]);
-      }
-    __syncthreads();
-  }
-}
-
-// The same product on the matrix cores for R = 16, 32, 64 columns: each wave
-// owns 16 outputs (j tile jt = wave & 1) and two 16-column tiles of R, and
-// accumulates complex products as four real FP64 16x16x4 matrix operations per
-// step of 4 summation rows (A operand: the 16 operand columns x 4 rows, B
-// operand: 4 rows x the 16 outputs of M).  In the result, lane l holds entry
-// (row (l >> 4) + 4 v, column l & 15) in its v-th value; the tiles go through
-// Dt to the thread-per-column layout of acc used by the callers.
-
-__device__ __forceinline__ void nd_mm_core_mfma(const double2* __restrict__ M, int K, int i0, int i1, int n_out,
-                                                int j0, const double2* __restrict__ X,
-                                                const double2* __restrict__ X2, int64_t xbase,
-                                                const int* __restrict__ xidx, int R, double2 (&acc)[8],
-                                                double2* Dt, int64_t ld2 = 0, int64_t sst = 0) {
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int jl = l & 15, kq = l >> 4;
-  const int jt = wv & 1, rt0 = (wv >> 1) * 2;
-  const int nrt = R >> 4;
-  const bool act0 = rt0 < nrt, act1 = rt0 + 1 < nrt;
-  const int j = j0 + 16 * jt + jl;
-  const bool jv = j < n_out;
-  const double2* mcol = M + (int64_t)K * (jv ? j : 0);
-  d4 cr0 = {0, 0, 0, 0}, ci0 = {0, 0, 0, 0}, cr1 = {0, 0, 0, 0}, ci1 = {0, 0, 0, 0};
-  if (act0) {
-    // NU steps of 4 summation rows per pass: every operand load of the pass is
-    // issued before its matrix operations (rows past i1 read row i1 - 1, an
-    // entry in range, and are zeroed); the operations keep the one-step order
-    constexpr int NU = 2;
-    for (int k = i0; k < i1; k += 4 * NU) {
-      double2 b[NU], a0[NU], a1[NU];
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        const int kk = k + 4 * u + kq;
-        const bool kv = kk < i1;
-        const int kc = kv ? kk : i1 - 1;
-        b[u] = mcol[kc];
-        const int64_t row = xidx ? (int64_t)xidx[kc] : xbase + kc;
-        const double2* xr = X + row * R + jl;
-        a0[u] = xr[16 * rt0];
-        a1[u] = act1 ? xr[16 * (rt0 + 1)] : make_double2(0, 0);
-        if (X2) {
-          // the two child slots of the row
-          const double2* x2 = X2 + row * ld2 + jl;
-          const double2 c0 = x2[16 * rt0], c1 = x2[sst + 16 * rt0];
-          a0[u].x += c0.x + c1.x;
-          a0[u].y += c0.y + c1.y;
-          if (act1) {
-            const double2 d0 = x2[16 * (rt0 + 1)], d1 = x2[sst + 16 * (rt0 + 1)];
-            a1[u].x += d0.x + d1.x;
-            a1[u].y += d0.y + d1.y;
-          }
-        }
-        if (!(kv && jv)) b[u] = make_double2(0, 0);
-        if (!kv) {
-          a0[u] = make_double2(0, 0);
-          a1[u] = make_double2(0, 0);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        if (k + 4 * u >= i1) break;   // a step wholly past the range (uniform)
-        cr0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[u].x, b[u].x, cr0, 0, 0, 0);
-        ci0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[u].x, b[u].y, ci0, 0, 0, 0);
-        cr0 = __builtin_amdgcn_mfma_f64_16x16x4f64(-a0[u].y, b[u].y, cr0, 0, 0, 0);
-        ci0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[u].y, b[u].x, ci0, 0, 0, 0);
-        if (act1) {
-          cr1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[u].x, b[u].x, cr1, 0, 0, 0);
-          ci1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[u].x, b[u].y, ci1, 0, 0, 0);
-          cr1 = __builtin_amdgcn_mfma_f64_16x16x4f64(-a1[u].y, b[u].y, cr1, 0, 0, 0);
-          ci1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[u].y, b[u].x, ci1, 0, 0, 0);
-        }
-      }
-    }
-    double2* dj = Dt + (16 * jt + jl) * 64;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) dj[16 * rt0 + kq + 4 * v] = make_double2(cr0[v], ci0[v]);
-    if (act1) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) dj[16 * (rt0 + 1) + kq + 4 * v] = make_double2(cr1[v], ci1[v]);
-    }
-  }
-  __syncthreads();
-  if (l < R) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const double2 d = Dt[(wv * 8 + q) * 64 + l];
-      acc[q].x += d.x;
-      acc[q].y += d.y;
-    }
-  }
-  __syncthreads();
-}
-
-// Partial tiles: P[task][32][64].  A task is {node, first output, i0, i1}.
-__device__ __forceinline__ void nd_store_part(double2* __restrict__ P, const double2 (&acc)[8], int R) {
-  const int r = threadIdx.x & 63, jw = (threadIdx.x >> 6) * 8;
-  if (r >= R) return;
-  double2* dst = P + (int64_t)blockIdx.x * SMJ * 64;
-  for (int q = 0; q < 8; ++q) dst[(jw + q) * 64 + r] = acc[q];
-}
-
-// The child slots of front row `row` (interior rows [0, nK), update rows after):
-// their sum, or zero at a leaf (no child writes there).
-__device__ __forceinline__ double2 nd_slots(const NDNodes& nd, bool leaf, int64_t row, int r) {
-  if (leaf) return make_double2(0, 0);
-  const double2* p = nd.slot + row * nd.ld + r;
-  const double2 a = p[0], b = p[nd.srows * nd.ld];
-  return make_double2(a.x + b.x, a.y + b.y);
-}
-
-__device__ __forceinline__ bool nd_leaf(const NDNodes& nd, int t) {
-  return nd.child[2 * t] < 0 && nd.child[2 * t + 1] < 0;
-}
-
-// U_t = A_t - L_t Y_I over the task's range of I (into P when the sum is split);
-// Y_I = g_I plus the children's slots, A_t the children's slots of t's update
-// rows; U_t goes by plain stores into t's slot of its parent's rows.
-template <bool MF>
-__global__ void __launch_bounds__(NT) k_nd_fwdR(const int4* __restrict__ task, NDNodes nd,
-                                                const double2* __restrict__ g, int R, double2* __restrict__ P) {
-  __shared__ double2 Dt[MF ? SMJ * 64 : 1];
-  const int4 tk = task[blockIdx.x];
-  const int t = tk.x, j0 = tk.y;
-  const int o = nd.off[t], nI = nd.off[t + 1] - o;
-  const int nB = int(nd.boff[t + 1] - nd.boff[t]);
-  const bool leaf = nd_leaf(nd, t);
-  const double2* Ys = leaf ? nullptr : nd.slot;
-  const int64_t sst = nd.srows * nd.ld;
-  double2 acc[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = make_double2(0, 0);
-  if (MF) nd_mm_core_mfma(nd.fac + nd.mL[t], nI, tk.z, tk.w, nB, j0, g, Ys, o, nullptr, R, acc, Dt, nd.ld, sst);
-  else nd_mm_core(nd.fac + nd.mL[t], nI, tk.z, tk.w, nB, j0, g, Ys, o, nullptr, R, acc, nd.ld, sst);
-  if (P) {
-    nd_store_part(P, acc, R);
-    return;
-  }
-  const int r = threadIdx.x & 63, jw = j0 + (threadIdx.x >> 6) * 8;
-  if (r >= R) return;
-  for (int q = 0; q < 8; ++q) {
-    const int j = jw + q;
-    if (j >= nB) break;
-    const int64_t u = nd.uoff[t] + j;
-    const double2 a = nd_slots(nd, leaf, nd.nK + u, r);
-    nd.slot[(int64_t)nd.push2[u] * nd.ld + r] = make_double2(a.x - acc[q].x, a.y - acc[q].y);
-  }
-}
-
-// X_I = Dinv_t Y_I - Lt_t X_B; the summation runs over [0, nI) for the first
-// product and [nI, nI + nB) for the second, of which the task takes [i0, i1).
-template <bool MF>
-__global__ void __launch_bounds__(NT) k_nd_bwdR(const int4* __restrict__ task, NDNodes nd,
-                                                const double2* __restrict__ g, double2* __restrict__ X, int R,
-                                                double2* __restrict__ P) {
-  __shared__ double2 Dt[MF ? SMJ * 64 : 1];
-  const int4 tk = task[blockIdx.x];
-  const int t = tk.x, j0 = tk.y;
-  const int o = nd.off[t], nI = nd.off[t + 1] - o;
-  const int64_t bo = nd.boff[t];
-  const int nB = int(nd.boff[t + 1] - bo);
-  const double2* Ys = nd_leaf(nd, t) ? nullptr : nd.slot;
-  const int64_t sst = nd.srows * nd.ld;
-  double2 a1[8], a2[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) a1[q] = a2[q] = make_double2(0, 0);
-  const int e1 = min(tk.w, nI);
-  const int s2 = max(tk.z, nI) - nI, e2 = tk.w - nI;
-  if (MF) {
-    if (tk.z < e1) nd_mm_core_mfma(nd.fac + nd.mD[t], nI, tk.z, e1, nI, j0, g, Ys, o, nullptr, R, a1, Dt, nd.ld, sst);
-    if (s2 < e2) nd_mm_core_mfma(nd.fac + nd.mLt[t], nB, s2, e2, nI, j0, X, nullptr, 0, nd.bnd + bo, R, a2, Dt);
-  } else {
-    if (tk.z < e1) nd_mm_core(nd.fac + nd.mD[t], nI, tk.z, e1, nI, j0, g, Ys, o, nullptr, R, a1, nd.ld, sst);
-    if (s2 < e2) nd_mm_core(nd.fac + nd.mLt[t], nB, s2, e2, nI, j0, X, nullptr, 0, nd.bnd + bo, R, a2);
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q) a1[q] = make_double2(a1[q].x - a2[q].x, a1[q].y - a2[q].y);
-  if (P) {
-    nd_store_part(P, a1, R);
-    return;
-  }
-  const int r = threadIdx.x & 63, jw = j0 + (threadIdx.x >> 6) * 8;
-  if (r >= R) return;
-  for (int q = 0; q < 8; ++q) {
-    const int j = jw + q;
-    if (j >= nI) break;
-    X[((int64_t)o + j) * R + r] = a1[q];
-  }
-}
-
-// Sums the S partial tiles of each output tile (tasks q S .. q S + S - 1 share
-// node and first output) and finishes the step: U = A - sum stored into the
-// parent's slot (forward) or X = sum (backward).
-__global__ void k_nd_reduce(const int4* __restrict__ task, int ntiles, int S, const double2* __restrict__ P,
-                            NDNodes nd, double2* __restrict__ X, int R, int bwd) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (int64_t)ntiles * SMJ * R) return;
-  const int r = int(e % R);
-  const int jj = int((e / R) % SMJ);
-  const int q = int(e / ((int64_t)R * SMJ));
-  const int4 tk = task[(int64_t)q * S];
-  const int t = tk.x, j = tk.y + jj;
-  const int o = nd.off[t], nI = nd.off[t + 1] - o;
-  const int n_out = bwd ? nI : int(nd.boff[t + 1] - nd.boff[t]);
-  if (j >= n_out) return;
-  double sx = 0, sy = 0;
-  for (int c = 0; c < S; ++c) {
-    const double2 v = P[((int64_t)q * S + c) * SMJ * 64 + jj * 64 + r];
-    sx += v.x;
-    sy += v.y;
-  }
-  if (bwd) {
-    X[((int64_t)o + j) * R + r] = make_double2(sx, sy);
-  } else {
-    const int64_t u = nd.uoff[t] + j;
-    const double2 a = nd_slots(nd, nd_leaf(nd, t), nd.nK + u, r);
-    nd.slot[(int64_t)nd.push2[u] * nd.ld + r] = make_double2(a.x - sx, a.y - sy);
-  }
-}
-
 // The top depths of the tree as one dense block (several columns): the
 // right-hand side of the top unknowns once every deeper node is eliminated,
 // r[i] = g[x_i] plus both child slots of each front row listed for x_i
@@ -2720,29 +2430,6 @@ void launch_eps_gradient(const Handle& h, const double2* U, const double2* Lam, 
 void launch_fill_zero(double2* x, int64_t count, hipStream_t s) {
   if (count == 0) return;
   hipLaunchKernelGGL(k_fill_zero, dim3(nblocks(count)), dim3(NT), 0, s, x, count);
-  HIPCHECK(hipGetLastError());
-}
-
-void launch_nd_tiles(bool bwd, const int4* task, int ntiles, int S, const NDView& v, const double2* g, double2* X,
-                     int R, double2* P, hipStream_t s) {
-  if (ntiles == 0) return;
-  if (R > v.ld) fail(HDP_E_ARG, "nested-dissection sweep: more columns than the slot stride");
-  const NDNodes nd{v.off, v.boff, v.bnd, v.uoff, v.mD, v.mL, v.mLt, v.fac,
-                   v.push2, v.child, v.slot, v.ld, v.srows, v.nK};
-  double2* part = S > 1 ? P : nullptr;
-  const unsigned nt = unsigned(ntiles) * unsigned(S);
-  // 16, 32 or 64 columns go to the matrix cores
-  const bool mf = R >= 16 && R % 16 == 0;
-  if (bwd) {
-    if (mf) hipLaunchKernelGGL(k_nd_bwdR<true>, dim3(nt), dim3(NT), 0, s, task, nd, g, X, R, part);
-    else hipLaunchKernelGGL(k_nd_bwdR<false>, dim3(nt), dim3(NT), 0, s, task, nd, g, X, R, part);
-  } else {
-    if (mf) hipLaunchKernelGGL(k_nd_fwdR<true>, dim3(nt), dim3(NT), 0, s, task, nd, g, R, part);
-    else hipLaunchKernelGGL(k_nd_fwdR<false>, dim3(nt), dim3(NT), 0, s, task, nd, g, R, part);
-  }
-  if (S > 1)
-    hipLaunchKernelGGL(k_nd_reduce, dim3(nblocks(int64_t(ntiles) * SMJ * R)), dim3(NT), 0, s, task, ntiles, S, P, nd,
-                       X, R, bwd ? 1 : 0);
   HIPCHECK(hipGetLastError());
 }
 

@@ -97,9 +97,9 @@ struct NDView {
 // one column (nested.hip): one launch of the forward (the children's updates into
 // their parents' slots) or the backward sweep (X)
 void launch_nd1(bool bwd, const ND1Launch& l, const Handle& h, const double2* g, double2* X, hipStream_t s);
-// several columns (R <= ld): ntiles output tiles of 32 rows, each split into S
+// several columns (R <= ld): ntiles output tiles of ND_TILE rows, each split into S
 // tasks {node, first row, i0, i1} over the summation; with S > 1 the partial
-// tiles go to P (ntiles * S * 32 * 64 values) and a second kernel adds them
+// tiles go to P (ntiles * S * ND_TILE * 64 values) and a second kernel adds them
 void launch_nd_tiles(bool bwd, const int4* task, int ntiles, int S, const NDView& v, const double2* g, double2* X,
                      int R, double2* P, hipStream_t s);
 // the top depths as one dense block (several columns): gather the top unknowns'
