@@ -11,8 +11,9 @@
 // same places, so that one stage serves every product and only a barrier parts
 // them.  (Near an element resonance 1 / D amplifies rounding by many digits, so the
 // order of the products, x y x y, and of their sums is kept as it is.)  The eigenbasis stays in the wave's registers for a whole product.  Where
-// n passes a multiple of 16 by at most 6 (17 modes are the usual case) the rows
-// beyond it are summed on the vector ALUs instead of filling a second tile.
+// n passes 16 or 32 by at most 4 (17 modes are the usual case) the rows
+// beyond it are summed on the vector ALUs instead of filling another tile (at 21 and
+// 22 modes a padded tile is the faster: the six rows took 285 registers).
 //
 // What bounds it: 16 n^3 flops per column with a real eigenbasis against 32 n^2
 // bytes of HBM traffic; at n = 17 the two take about the same time, and a
@@ -387,8 +388,13 @@ size_t sep_lds(int n, int nr, int ncol, bool padded) {
 
 // The widest classes of a bucket decide (n, nr its largest).  Of the widths whose
 // stage stays within 40 KiB (four workgroups per compute unit, so that the loads
-// of some cover the products of others), the one that needs the fewest tiles of 16
-// lines is taken, the smaller on a tie.  want > 0 fixes the width (options,
+// of some cover the products of others), the one with the least chunks x (tiles of
+// 16 lines + 3) is taken: a workgroup's load, store and barriers cost about three
+// tiles, and narrow chunks read pieces of cache lines (at 16 modes, where one column
+// fills a tile exactly, single columns took twice the time of eight).  Where so few
+// elements leave less than two workgroups per compute unit, a workgroup's own chain
+// counts and single columns are the faster (100 elements of 22 modes, 3 columns: 51
+// us a call in one chunk, 42 in three).  want > 0 fixes the width (options,
 // autotuner).
 SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
   const int n = b.n, nr = b.nr;
@@ -400,8 +406,9 @@ SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
   } else {
     int64_t best = INT64_MAX;
     for (int rc = 1; rc <= std::min(R, 64); ++rc) {
-      if (rc > 1 && sep_lds(n, nr, rc, padded) > 40 * 1024) break;
-      const int64_t cost = int64_t((R + rc - 1) / rc) * tiles(rc);
+      const int nchunk = (R + rc - 1) / rc;
+      if (rc > 1 && (sep_lds(n, nr, rc, padded) > 40 * 1024 || int64_t(b.count[0]) * nchunk < 512)) break;
+      const int64_t cost = int64_t(nchunk) * (tiles(rc) + 3);
       if (cost < best) { best = cost; c.rc = rc; }
     }
     if (c.rc == R) {
@@ -453,9 +460,9 @@ void launch_sep(const Handle& h, int mode, SepArgs a, int want, hipStream_t s) {
 #define HDP_SEP_CASE(V, KS, MT, XR) \
   case V: launch_n<KS, MT, XR>(mode, a, grid, c.threads, c.lds, h, s); break;
       HDP_SEP_CASE(4, 1, 1, 0) HDP_SEP_CASE(8, 2, 1, 0) HDP_SEP_CASE(12, 3, 1, 0) HDP_SEP_CASE(16, 4, 1, 0)
-      HDP_SEP_CASE(18, 5, 1, 2) HDP_SEP_CASE(20, 5, 1, 4) HDP_SEP_CASE(22, 6, 1, 6) HDP_SEP_CASE(24, 6, 2, 0)
+      HDP_SEP_CASE(18, 5, 1, 2) HDP_SEP_CASE(20, 5, 1, 4) HDP_SEP_CASE(24, 6, 2, 0)
       HDP_SEP_CASE(28, 7, 2, 0) HDP_SEP_CASE(32, 8, 2, 0) HDP_SEP_CASE(34, 9, 2, 2) HDP_SEP_CASE(36, 9, 2, 4)
-      HDP_SEP_CASE(38, 10, 2, 6) HDP_SEP_CASE(40, 10, 3, 0) HDP_SEP_CASE(44, 11, 3, 0)
+      HDP_SEP_CASE(40, 10, 3, 0) HDP_SEP_CASE(44, 11, 3, 0)
 #undef HDP_SEP_CASE
       default: fail(HDP_E_UNSUPPORTED, "element solve: degree out of range");
     }
@@ -467,7 +474,7 @@ void launch_sep(const Handle& h, int mode, SepArgs a, int want, hipStream_t s) {
 
 // the kernel of a class of n modes per direction, by the largest n it takes
 int sep_len(int n) {
-  for (int N : {4, 8, 12, 16, 18, 20, 22, 24, 28, 32, 34, 36, 38, 40, 44})
+  for (int N : {4, 8, 12, 16, 18, 20, 24, 28, 32, 34, 36, 40, 44})
     if (n <= N) return N;
   fail(HDP_E_UNSUPPORTED, "element solve: degree out of range");
 }
