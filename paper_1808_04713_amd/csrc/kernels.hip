@@ -2034,8 +2034,12 @@ inline int pow2_at_least(int x) {
 // fit: at most 64 KB and 16 output tiles per element)
 
 // columns per block of the matrix-core slot operators: the handle's choice
-// (16, 32 or 64; 32 unless tuned), at most R
-static int slot_rb(const Handle& h, int R) { return std::min(R, h.slot_rb); }
+// (16, 32 or 64; 32 unless tuned), at most R and a divisor of it (R is a multiple of 16)
+static int slot_rb(const Handle& h, int R) {
+  int rb = std::min(R, h.slot_rb);
+  while (R % rb) rb -= 16;
+  return rb;
+}
 
 static size_t slot_mfma_lds(const Handle& h, int R, int mode) {
   if (R < 16 || R % 16 != 0) return 0;

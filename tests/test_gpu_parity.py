@@ -305,6 +305,29 @@ def test_one_column_sweeps_of_a_deep_tree():
     sd.close()
 
 
+@pytest.mark.parametrize("coarse", ["dense", "nd"])
+def test_operators_at_ragged_column_counts(coarse):
+    """F v at column counts beside and between the tile widths of the several-column
+    coarse solves, and at 48 (the matrix-core slot operators' width has to divide it:
+    it was 32 and left the last 16 columns out), against one column at a time; P^-1 v
+    and the mixed path at 48."""
+    w = W.small_uniform(20, 4, 27.0, l=2)
+    s = hdp().Solver(w, coarse=coarse, max_iter=10, max_rhs=64)
+    rng = np.random.default_rng(8)
+    v = torch.from_numpy(rng.standard_normal((s.n_lambda, 64)) + 1j * rng.standard_normal((s.n_lambda, 64))).cuda()
+    ref = torch.cat([s.apply_interface(v[:, r:r + 1].contiguous()) for r in range(64)], dim=1).cpu().numpy()
+    pref = torch.cat([s.apply_precond(v[:, r:r + 1].contiguous()) for r in range(64)], dim=1).cpu().numpy()
+    bound = max(1e-12, 1e3 * s.info["coarse_residual"])
+    for R in (2, 3, 7, 15, 17, 24, 31, 33, 48, 63):
+        x = v[:, :R].contiguous()
+        assert rel(s.apply_interface(x).cpu().numpy(), ref[:, :R]) < bound < 1e-9, R
+        if R % 16 == 0:
+            assert rel(s.apply_precond(x).cpu().numpy(), pref[:, :R]) < 1e-12, R
+            assert rel(s.apply_interface(x, "mixed").cpu().numpy(), ref[:, :R]) < 1e-4, R
+            assert rel(s.apply_precond(x, "mixed").cpu().numpy(), pref[:, :R]) < 1e-5, R
+    s.close()
+
+
 def test_handle_memory_from_the_callers_allocator(oracles):
     """hdp_options.allocator: with torch's caching allocator the handle's device
     memory comes from torch's pool (torch.cuda.memory_allocated grows by at least
