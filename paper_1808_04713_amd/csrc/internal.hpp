@@ -111,6 +111,9 @@ struct ND1Launch {
 constexpr int GMRES_AHEAD = 1;
 constexpr int64_t GMRES_LONG = int64_t(1) << 20;
 constexpr int STATUS_SLOTS = 4;
+// row chunks of the multi-dot up to which the scalar step adds the partials itself
+// (2,048 unknowns at one column)
+constexpr int DOTS_FOLD = 8;
 
 // Per-block record of the slot kernels (blocks follow the class-grouped element
 // order): the element, its class, slot and coarse-mode offsets and counts, and
@@ -346,10 +349,13 @@ struct Handle {
     double *nrm = nullptr, *npart = nullptr;
     float2* vf = nullptr;
     double2 *vcur = nullptr, *Hdev = nullptr, *cs = nullptr, *sn = nullptr, *gvec = nullptr;
-    double *beta = nullptr, *resid = nullptr, *hist = nullptr;   // hist: (max_iter+1) x R
+    // resid, iteration counts (Rp each) and hist ((max_iter+1) x R) in one run
+    double *beta = nullptr, *resid = nullptr, *hist = nullptr;
     int *jdev = nullptr, *counter = nullptr, *status = nullptr, *done = nullptr, *iters = nullptr;
     int* status_host = nullptr;   // pinned, mapped, coherent: STATUS_SLOTS pairs of ints
     int* status_hdev = nullptr;   // the same memory as the device addresses it
+    // the rest of that memory: what one copy of resid brings, then norms (2 Rp), angles (Rp)
+    double *res_host = nullptr, *nrm_host = nullptr, *ang_host = nullptr;
     int* load_elems = nullptr;
     int64_t* load_off = nullptr;
     double2* load_vals = nullptr;

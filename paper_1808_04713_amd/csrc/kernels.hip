@@ -1400,10 +1400,10 @@ __global__ void k_dense_scatter(const int64_t* __restrict__ idx, const double2* 
 // w[row][r] += sign * sum_{i < nvec} V_i[row][r] h[i][r]; when npart is given the
 // block also writes the partial squared norms of the updated w (per RHS column).
 __global__ void __launch_bounds__(NT) k_mupdate(const double2* __restrict__ V, int64_t vs, const int* __restrict__ jptr,
-                                                int jfix, const double2* __restrict__ hc, double2* __restrict__ w,
+                                                const double2* __restrict__ hc, double2* __restrict__ w,
                                                 int n, int R, double sign, double* __restrict__ npart) {
   __shared__ double2 red[NT];
-  const int nvec = (jptr ? *jptr : jfix) + 1;
+  const int nvec = *jptr;
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int r = threadIdx.x % R;   // NT is a multiple of R, so idx % R == threadIdx.x % R
   double nx = 0;
@@ -1432,11 +1432,11 @@ __global__ void __launch_bounds__(NT) k_mupdate(const double2* __restrict__ V, i
 constexpr int UPD_SPLIT_MAX = 1 << 20;   // entries (rows x RHS) up to which the split form is used
 
 __global__ void __launch_bounds__(NT) k_mupdate_split(const double2* __restrict__ V, int64_t vs,
-                                                      const int* __restrict__ jptr, int jfix,
+                                                      const int* __restrict__ jptr,
                                                       const double2* __restrict__ hc, double2* __restrict__ w, int n,
                                                       int R, double sign, double* __restrict__ npart) {
   __shared__ double2 red[NT / 64][64];
-  const int nvec = (jptr ? *jptr : jfix) + 1;
+  const int nvec = *jptr;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t idx = (int64_t)blockIdx.x * 64 + lane;
   const bool live = idx < (int64_t)n * R;
@@ -1473,8 +1473,11 @@ __global__ void __launch_bounds__(NT) k_mupdate_split(const double2* __restrict_
 }
 
 // Partial squared norms of w per block and RHS column.
-__global__ void __launch_bounds__(NT) k_norm2_part(const double2* __restrict__ w, int n, int R, double* __restrict__ part) {
+// With blockIdx.y = 1 those of w2, behind them.
+__global__ void __launch_bounds__(NT) k_norm2_part(const double2* __restrict__ w1, const double2* __restrict__ w2,
+                                                   int n, int R, double* __restrict__ part) {
   __shared__ double2 red[NT];
+  const double2* __restrict__ w = blockIdx.y ? w2 : w1;
   const int r = threadIdx.x % R, rl = threadIdx.x / R, step = NT / R;
   double acc = 0;
   for (int64_t row = (int64_t)blockIdx.x * step + rl; row < n; row += (int64_t)gridDim.x * step) {
@@ -1482,22 +1485,20 @@ __global__ void __launch_bounds__(NT) k_norm2_part(const double2* __restrict__ w
     acc += a.x * a.x + a.y * a.y;
   }
   double2 s = block_sum_by_rhs(make_double2(acc, 0), R, red);
-  if (threadIdx.x < R) part[blockIdx.x * R + threadIdx.x] = s.x;
+  if (threadIdx.x < R) part[(blockIdx.y * gridDim.x + blockIdx.x) * R + threadIdx.x] = s.x;
 }
 
-// nrm[r] = sqrt(sum of partials); out = w / nrm (zero where nrm = 0).  Every
-// block reduces the partials itself; block 0 publishes nrm.  out2 (optional)
-// receives the same vector.  The destination is V_kry + (j + 1 + dst_shift) * vs
-// when jptr is given, else out directly.
-// nrm[r] = sqrt(sum_b part[b][r]): one block per RHS column.
+// nrm[r] = sqrt(sum_b part[b][r]): one block per RHS column (and vector: the second
+// one's partials and norms follow the first's).
 __global__ void __launch_bounds__(NT) k_norm_reduce(const double* __restrict__ part, int nblk, int R,
                                                     double* __restrict__ nrm) {
   __shared__ double2 red[NT];
   const int r = blockIdx.x;
+  part += (int64_t)blockIdx.y * nblk * R;
   double acc = 0;
   for (int b = threadIdx.x; b < nblk; b += NT) acc += part[(int64_t)b * R + r];
   double2 t = block_sum_by_rhs(make_double2(acc, 0), 1, red);
-  if (threadIdx.x == 0) nrm[r] = sqrt(t.x);
+  if (threadIdx.x == 0) nrm[blockIdx.y * R + r] = sqrt(t.x);
 }
 
 // out = w / nrm (zero where nrm = 0); out2 (optional) receives the same vector.
@@ -1799,22 +1800,21 @@ __global__ void __launch_bounds__(NT) k_dmdot_reduce(const double2* __restrict__
   if (lane == 0) D[idx] = make_double2(ax, ay);
 }
 
-// block-wide sum of (x, y) over all threads; valid in every thread
-__device__ __forceinline__ double2 block_sum_all(double x, double y, double2* red) {
-  for (int off = 32; off > 0; off >>= 1) {
-    x += __shfl_xor(x, off, 64);
-    y += __shfl_xor(y, off, 64);
-  }
+// block-wide sums of four values over all threads; valid in every thread
+__device__ __forceinline__ void block_sum4(double (&v)[4], double (*red)[4]) {
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] += __shfl_xor(v[q], off, 64);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) red[wv][q] = v[q];
   __syncthreads();
-  if (lane == 0) red[wv] = make_double2(x, y);
-  __syncthreads();
-  double2 t = make_double2(0, 0);
-  for (int q = 0; q < NT / 64; ++q) {
-    t.x += red[q].x;
-    t.y += red[q].y;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    v[q] = 0;
+    for (int u = 0; u < NT / 64; ++u) v[q] += red[u][q];
   }
-  return t;
 }
 
 // The scalar step of an iteration, one block per system r: finishes column j-1
@@ -1824,7 +1824,13 @@ __device__ __forceinline__ double2 block_sum_all(double x, double y, double2* re
 // update kernel that follows (they are first used in the next scalar step).
 // Every global value the step needs is loaded up front; the column and the
 // earlier rotations are kept in shared memory ((3 maxvec + 1) entries).
-__global__ void __launch_bounds__(NT) k_dcgs_scalar(int* __restrict__ jptr, const double2* __restrict__ D,
+// D: the reduced dots, or with nch > 1 the partials of that many row chunks, cstride
+// apart, which each thread adds for its entries.  A step is a chain of some 5 us
+// (j, dots, two reductions, the rotation's square roots and quotients) at any j, so a
+// reduction launch ahead of it is worth its 2 to 4 us only where one block's loads
+// would take longer (DOTS_FOLD).
+__global__ void __launch_bounds__(NT) k_dcgs_scalar(int* __restrict__ jptr, const double2* __restrict__ D, int nch,
+                                                    int64_t cstride,
                                                     double2* __restrict__ Hraw, const double2* __restrict__ hprev,
                                                     double* __restrict__ rho, double2* __restrict__ uc,
                                                     double2* __restrict__ H, double2* __restrict__ cs,
@@ -1837,18 +1843,28 @@ __global__ void __launch_bounds__(NT) k_dcgs_scalar(int* __restrict__ jptr, cons
   double2* col = shm;                  // column j-1: maxvec + 1 entries
   double2* csl = col + maxvec + 1;     // rotations 0..j-2
   double2* snl = csl + maxvec;
-  __shared__ double2 red[NT / 64];
+  __shared__ double red[NT / 64][4];
   __shared__ double2 xj_sh;
   const int r = blockIdx.x;
   const int j = *jptr;
+  auto dot = [&](int k) {
+    double2 a = D[(int64_t)k * R + r];
+#pragma unroll 4
+    for (int c = 1; c < nch; ++c) {
+      const double2 b = D[c * cstride + (int64_t)k * R + r];
+      a.x += b.x;
+      a.y += b.y;
+    }
+    return a;
+  };
   const double rho_prev = rho[r];
   const int is_done = done[r];
   const double2 gj = j >= 1 ? g[(j - 1) * R + r] : make_double2(0, 0);
-  const double2 uz = D[(int64_t)(2 * j) * R + r];
-  const double uu = D[(int64_t)(2 * j + 1) * R + r].x, zz = D[(int64_t)(2 * j + 2) * R + r].x;
+  const double2 uz = dot(2 * j);
+  const double uu = dot(2 * j + 1).x, zz = dot(2 * j + 2).x;
   double ss = 0, tt = 0, stx = 0, sty = 0;
   for (int i = threadIdx.x; i < j; i += NT) {
-    const double2 a = D[(int64_t)i * R + r], b = D[(int64_t)(j + i) * R + r];
+    const double2 a = dot(i), b = dot(j + i);
     const double2 hp = hprev[(int64_t)i * R + r];
     if (i < j - 1) {
       csl[i] = cs[(int64_t)i * R + r];
@@ -1861,9 +1877,10 @@ __global__ void __launch_bounds__(NT) k_dcgs_scalar(int* __restrict__ jptr, cons
     tt += b.x * b.x + b.y * b.y;
     cdot_acc(a, b, stx, sty);   // s^H t
   }
-  const double2 sum_ss_tt = block_sum_all(ss, tt, red);
-  const double2 st = block_sum_all(stx, sty, red);
-  const double nu2 = uu - sum_ss_tt.x;
+  double sums[4] = {ss, tt, stx, sty};
+  block_sum4(sums, red);
+  const double2 st = make_double2(sums[2], sums[3]);
+  const double nu2 = uu - sums[0];
   const double nu = nu2 > 0 ? sqrt(nu2) : 0.0;
   const double inu = nu > 0 ? 1.0 / nu : 0.0;
   if (j >= 1) {
@@ -1877,7 +1894,7 @@ __global__ void __launch_bounds__(NT) k_dcgs_scalar(int* __restrict__ jptr, cons
   if (threadIdx.x == 0) {
     // tau = (u^H z - s^H t) / nu; sigma^2 = |z|^2 - |t|^2 - |tau|^2
     const double2 tau = make_double2((uz.x - st.x) * inu, (uz.y - st.y) * inu);
-    const double sg2 = zz - sum_ss_tt.y - (tau.x * tau.x + tau.y * tau.y);
+    const double sg2 = zz - sums[1] - (tau.x * tau.x + tau.y * tau.y);
     const double sg = sg2 > 0 ? sqrt(sg2) : 0.0;
     const double isg = sg > 0 ? 1.0 / sg : 0.0;
     uc[(int64_t)(2 * j) * R + r] = tau;
@@ -1889,24 +1906,29 @@ __global__ void __launch_bounds__(NT) k_dcgs_scalar(int* __restrict__ jptr, cons
 }
 
 // First-pass coefficients of column j, hprev = ([t; tau] - H s) / nu with H the
-// unrotated (j+1) x j Hessenberg matrix: one (row, system) item per block in
-// turn, a block-wide dot over the row.  Every block of the update kernels
-// takes part, so that the rows cost no launch of their own.
+// unrotated (j+1) x j Hessenberg matrix: one (row, system) item per wave in turn.
+// Every wave of the update kernels takes part, the last blocks first, so that the
+// rows cost no launch of their own (with a block-wide dot per item the 33 rows of
+// three blocks, 168 unknowns, took 8 of the 13 us of that update).
 __device__ void first_pass_rows(int j, int R, int maxvec, const double2* __restrict__ Hraw,
-                                const double2* __restrict__ uc, double2* __restrict__ hprev, double2* red) {
-  for (int item = blockIdx.x; item < (j + 1) * R; item += gridDim.x) {
+                                const double2* __restrict__ uc, double2* __restrict__ hprev) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  for (int item = (gridDim.x - 1 - blockIdx.x) * (NT / 64) + wv; item < (j + 1) * R; item += gridDim.x * (NT / 64)) {
     const int i = item / R, r = item - i * R;
     double x = 0, y = 0;
-    for (int k = max(0, i - 1) + (int)threadIdx.x; k < j; k += NT) {
+    for (int k = max(0, i - 1) + lane; k < j; k += 64) {
       const double2 a = Hraw[((int64_t)k * maxvec + i) * R + r], b = uc[(int64_t)k * R + r];
       x += a.x * b.x - a.y * b.y;
       y += a.x * b.y + a.y * b.x;
     }
-    const double2 hs = block_sum_all(x, y, red);
-    if (threadIdx.x == 0) {
+    for (int off = 32; off > 0; off >>= 1) {
+      x += __shfl_xor(x, off, 64);
+      y += __shfl_xor(y, off, 64);
+    }
+    if (lane == 0) {
       const double2 c = uc[(int64_t)(i < j ? j + i : 2 * j) * R + r];
       const double inu = uc[(int64_t)(2 * j + 1) * R + r].x;
-      hprev[(int64_t)i * R + r] = make_double2((c.x - hs.x) * inu, (c.y - hs.y) * inu);
+      hprev[(int64_t)i * R + r] = make_double2((c.x - x) * inu, (c.y - y) * inu);
     }
   }
 }
@@ -1921,7 +1943,6 @@ __global__ void __launch_bounds__(NT) k_dupdate_split(double2* __restrict__ V, i
                                                       double2* __restrict__ out2, const double2* __restrict__ Hraw,
                                                       double2* __restrict__ hprev, int maxvec) {
   __shared__ double2 red[2][NT / 64][64];
-  __shared__ double2 red1[NT / 64];
   const int j = *jptr - 1;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t idx = (int64_t)blockIdx.x * 64 + lane;
@@ -1960,7 +1981,7 @@ __global__ void __launch_bounds__(NT) k_dupdate_split(double2* __restrict__ V, i
     if (out2) out2[idx] = un;
     z[idx] = make_double2(0, 0);   // cleared for the next operator output (added into)
   }
-  first_pass_rows(j, R, maxvec, Hraw, uc, hprev, red1);
+  first_pass_rows(j, R, maxvec, Hraw, uc, hprev);
 }
 
 // the same for long vectors: one thread per entry over all basis vectors
@@ -1968,7 +1989,6 @@ __global__ void __launch_bounds__(NT) k_dupdate(double2* __restrict__ V, int64_t
                                                 const double2* __restrict__ uc, double2* __restrict__ z, int n,
                                                 int R, double2* __restrict__ out2, const double2* __restrict__ Hraw,
                                                 double2* __restrict__ hprev, int maxvec) {
-  __shared__ double2 red1[NT / 64];
   const int j = *jptr - 1;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < (int64_t)n * R) {
@@ -1993,7 +2013,80 @@ __global__ void __launch_bounds__(NT) k_dupdate(double2* __restrict__ V, int64_t
     if (out2) out2[idx] = un;
     z[idx] = make_double2(0, 0);
   }
-  first_pass_rows(j, R, maxvec, Hraw, uc, hprev, red1);
+  first_pass_rows(j, R, maxvec, Hraw, uc, hprev);
+}
+
+// End of a GMRES run: H y = g (upper triangular, one block per system) for the
+// columns the system took, zero beyond; block 0 leaves the largest column count of
+// all systems in jptr, and each its iteration count behind its residual in res
+// ([2][rstride], ahead of the residual history), so that one copy carries all the
+// host reads.  Blocks of EB columns, from the last: one wave solves the block's
+// triangle out of shared memory, all threads take its columns off the rows above.
+// With H copied to the host instead (the whole rectangle of maxvec rows a column, in
+// pageable memory) and four more synchronous copies this end took 0.25 ms at one
+// column and 0.45 ms at 64.
+constexpr int EB = 32;
+
+__global__ void __launch_bounds__(NT) k_gmres_end(const double2* __restrict__ H, const double2* __restrict__ g,
+                                                  const int* __restrict__ iters, int maxvec, int R,
+                                                  double2* __restrict__ y, int* __restrict__ jptr,
+                                                  double* __restrict__ res, int rstride) {
+  extern __shared__ double2 b[];           // right-hand side, then solution: the system's columns
+  __shared__ double2 T[EB][EB + 1];        // T[c][l] = H(b0 + l, b0 + c)
+  const int r = blockIdx.x, k = iters[r];
+  int kmax = 0;
+  for (int q = 0; q < R; ++q) kmax = max(kmax, iters[q]);
+  auto at = [&](int i, int c) { return H[((int64_t)c * maxvec + i) * R + r]; };
+  for (int i = threadIdx.x; i < k; i += NT) b[i] = g[(int64_t)i * R + r];
+  for (int b0 = k > 0 ? (k - 1) / EB * EB : -1; b0 >= 0; b0 -= EB) {
+    const int nb = min(EB, k - b0);
+    for (int q = threadIdx.x; q < nb * EB; q += NT) {
+      const int c = q / EB, l = q - c * EB;
+      if (l <= c) T[c][l] = at(b0 + l, b0 + c);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      const int l = min((int)threadIdx.x, nb - 1);
+      // 1 / T_ll, scaled by the larger part
+      const double2 d = T[l][l];
+      double2 inv;
+      if (fabs(d.x) >= fabs(d.y)) {
+        const double q = d.y / d.x, den = d.x + d.y * q;
+        inv = make_double2(1.0 / den, -q / den);
+      } else {
+        const double q = d.x / d.y, den = d.x * q + d.y;
+        inv = make_double2(q / den, -1.0 / den);
+      }
+      double2 v = b[b0 + l];
+      for (int c = nb - 1; c >= 0; --c) {
+        const double2 yl = cmul(v, inv);
+        const double2 yc = make_double2(__shfl(yl.x, c, 64), __shfl(yl.y, c, 64));
+        if (l < c) {
+          const double2 t = T[c][l];
+          v.x -= t.x * yc.x - t.y * yc.y;
+          v.y -= t.x * yc.y + t.y * yc.x;
+        }
+      }
+      if (threadIdx.x < nb) b[b0 + l] = cmul(v, inv);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < b0; i += NT) {
+      double2 v = b[i];
+#pragma unroll 8
+      for (int c = 0; c < nb; ++c) {
+        const double2 t = at(i, b0 + c), yc = b[b0 + c];
+        v.x -= t.x * yc.x - t.y * yc.y;
+        v.y -= t.x * yc.y + t.y * yc.x;
+      }
+      b[i] = v;
+    }
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < kmax; i += NT) y[(int64_t)i * R + r] = i < k ? b[i] : make_double2(0, 0);
+  if (threadIdx.x == 0) {
+    res[rstride + r] = k;
+    if (r == 0) *jptr = kmax;
+  }
 }
 
 // Start of a GMRES run: g_0 = beta = ||P^-1 rhs||, flags cleared, j = 0.
@@ -2275,21 +2368,29 @@ GmresDims gmres_dims(int n, int R, int maxvec) {
   return g;
 }
 
-void launch_mupdate(const double2* V, int64_t vs, const int* jptr, int jfix, const double2* hc, double2* w, int n,
+void launch_mupdate(const double2* V, int64_t vs, const int* jptr, const double2* hc, double2* w, int n,
                     int R, double sign, double* npart, hipStream_t s) {
   if (int64_t(n) * R <= UPD_SPLIT_MAX)
-    hipLaunchKernelGGL(k_mupdate_split, dim3(nblocks(int64_t(n) * R, 64)), dim3(NT), 0, s, V, vs, jptr, jfix, hc, w, n,
+    hipLaunchKernelGGL(k_mupdate_split, dim3(nblocks(int64_t(n) * R, 64)), dim3(NT), 0, s, V, vs, jptr, hc, w, n,
                        R, sign, npart);
   else
-    hipLaunchKernelGGL(k_mupdate, dim3(nblocks(int64_t(n) * R)), dim3(NT), 0, s, V, vs, jptr, jfix, hc, w, n, R, sign,
+    hipLaunchKernelGGL(k_mupdate, dim3(nblocks(int64_t(n) * R)), dim3(NT), 0, s, V, vs, jptr, hc, w, n, R, sign,
                        npart);
+  HIPCHECK(hipGetLastError());
+}
+
+// nrm[r] = |w_r|, and with w2 nrm[R + r] = |w2_r|
+void launch_norms(const double2* w, const double2* w2, int n, int R, const GmresDims& g, double* part, double* nrm,
+                  hipStream_t s) {
+  const int two = w2 ? 2 : 1;
+  hipLaunchKernelGGL(k_norm2_part, dim3(g.nnorm, two), dim3(NT), 0, s, w, w2, n, R, part);
+  hipLaunchKernelGGL(k_norm_reduce, dim3(R, two), dim3(NT), 0, s, part, g.nnorm, R, nrm);
   HIPCHECK(hipGetLastError());
 }
 
 void launch_normalize(const double2* w, int n, int R, const GmresDims& g, double* part, double* nrm, double2* out,
                       const int* jptr, int64_t vs, double2* out2, hipStream_t s) {
-  hipLaunchKernelGGL(k_norm2_part, dim3(g.nnorm), dim3(NT), 0, s, w, n, R, part);
-  hipLaunchKernelGGL(k_norm_reduce, dim3(R), dim3(NT), 0, s, part, g.nnorm, R, nrm);
+  launch_norms(w, nullptr, n, R, g, part, nrm, s);
   hipLaunchKernelGGL(k_normalize, dim3(g.nnorm), dim3(NT), 0, s, w, nrm, n, R, out, jptr, vs, out2);
   HIPCHECK(hipGetLastError());
 }
@@ -2312,12 +2413,12 @@ void launch_dmdot_reduce(const double2* part, const GmresDims& g, const int* jpt
   HIPCHECK(hipGetLastError());
 }
 
-void launch_dcgs_scalar(int* jptr, const double2* D, double2* Hraw, const double2* hprev, double* rho, double2* uc,
+void launch_dcgs_scalar(int* jptr, const double2* D, int nch, int64_t cstride, double2* Hraw, const double2* hprev, double* rho, double2* uc,
                         double2* H, double2* cs, double2* sn, double2* g, const double* beta, int* done, int* iters,
                         double* resid, double tol, int maxvec, int R, int* counter, int* status, double* hist,
                         hipStream_t s) {
   const size_t shm = (3 * size_t(maxvec) + 1) * sizeof(double2);
-  hipLaunchKernelGGL(k_dcgs_scalar, dim3(R), dim3(NT), shm, s, jptr, D, Hraw, hprev, rho, uc, H, cs, sn, g, beta,
+  hipLaunchKernelGGL(k_dcgs_scalar, dim3(R), dim3(NT), shm, s, jptr, D, nch, cstride, Hraw, hprev, rho, uc, H, cs, sn, g, beta,
                      done, iters, resid, tol, maxvec, R, counter, status, hist);
   HIPCHECK(hipGetLastError());
 }
@@ -2325,11 +2426,19 @@ void launch_dcgs_scalar(int* jptr, const double2* D, double2* Hraw, const double
 void launch_dupdate(double2* V, int64_t vs, const int* jptr, const double2* uc, double2* z, int n, int R,
                     double2* out2, const double2* Hraw, double2* hprev, int maxvec, hipStream_t s) {
   if (int64_t(n) * R <= UPD_SPLIT_MAX)
-    hipLaunchKernelGGL(k_dupdate_split, dim3(nblocks(int64_t(n) * R, 64)), dim3(NT), 0, s, V, vs, jptr, uc, z, n, R,
+    // (blocks past the entries take first-pass rows alone)
+    hipLaunchKernelGGL(k_dupdate_split, dim3(std::max(nblocks(int64_t(n) * R, 64), 32u)), dim3(NT), 0, s, V, vs, jptr, uc, z, n, R,
                        out2, Hraw, hprev, maxvec);
   else
     hipLaunchKernelGGL(k_dupdate, dim3(nblocks(int64_t(n) * R)), dim3(NT), 0, s, V, vs, jptr, uc, z, n, R, out2, Hraw,
                        hprev, maxvec);
+  HIPCHECK(hipGetLastError());
+}
+
+void launch_gmres_end(const double2* H, const double2* g, const int* iters, int maxvec, int R, double2* y, int* jptr,
+                      double* res, int rstride, hipStream_t s) {
+  hipLaunchKernelGGL(k_gmres_end, dim3(R), dim3(NT), size_t(maxvec) * sizeof(double2), s, H, g, iters, maxvec, R, y,
+                     jptr, res, rstride);
   HIPCHECK(hipGetLastError());
 }
 
