@@ -1228,6 +1228,10 @@ void far_prepare(Handle& h, int n_far, const double* angles, const uint8_t* insi
   std::vector<int> el, sd, noff{0};
   std::vector<int64_t> toff{0};
   std::vector<double> tab, dsc, px, py, pw, pnx, pny;
+  struct Rule {
+    std::vector<double> x, w, N, d0, d1;   // nodes, weights, [q][n] basis, derivatives at -1 and 1
+  };
+  std::map<int, Rule> rules;   // by n
   for (int e = 0; e < h.E; ++e) {
     if (in[e]) continue;
     for (int s = 1; s <= 4; ++s) {
@@ -1243,15 +1247,22 @@ void far_prepare(Handle& h, int n_far, const double* angles, const uint8_t* insi
         facing_inside = n_in != 0;
       }
       if (!facing_inside) continue;
-      int n = h.deg[e] + 1, q = n + 12;
-      std::vector<double> xq, wq;
-      gauss_legendre(q, xq, wq);
+      const int n = h.deg[e] + 1, q = n + 12;
+      Rule& u = rules[n];
+      if (u.x.empty()) {
+        gauss_legendre(q, u.x, u.w);
+        u.N.resize(size_t(q) * n);
+        for (int t = 0; t < q; ++t) vertex_basis(n, u.x[t], u.N.data() + size_t(t) * n);
+        u.d0.resize(n);
+        u.d1.resize(n);
+        vertex_basis_dx(n, -1.0, u.d0.data());
+        vertex_basis_dx(n, 1.0, u.d1.data());
+      }
+      const std::vector<double>&xq = u.x, &wq = u.w;
       double ox = h.ox[e], oy = h.oy[e], hx = h.hx[e], hy = h.hy[e];
       double nx = s == 1 ? 1 : s == 2 ? -1 : 0, ny = s == 3 ? 1 : s == 4 ? -1 : 0;   // into e
-      std::vector<double> row(n);
+      tab.insert(tab.end(), u.N.begin(), u.N.end());
       for (int t = 0; t < q; ++t) {
-        vertex_basis(n, xq[t], row.data());
-        tab.insert(tab.end(), row.begin(), row.end());
         double x, y;
         if (s <= 2) { x = s == 1 ? ox : ox + hx; y = oy + (xq[t] + 1) * hy / 2; }
         else { y = s == 3 ? oy : oy + hy; x = ox + (xq[t] + 1) * hx / 2; }
@@ -1261,8 +1272,8 @@ void far_prepare(Handle& h, int n_far, const double* angles, const uint8_t* insi
         pnx.push_back(nx);
         pny.push_back(ny);
       }
-      vertex_basis_dx(n, (s == 2 || s == 4) ? 1.0 : -1.0, row.data());
-      tab.insert(tab.end(), row.begin(), row.end());
+      const auto& dend = (s == 2 || s == 4) ? u.d1 : u.d0;
+      tab.insert(tab.end(), dend.begin(), dend.end());
       dsc.push_back(s <= 2 ? nx * 2.0 / hx : ny * 2.0 / hy);
       el.push_back(e);
       sd.push_back(s);
@@ -1845,58 +1856,6 @@ hdp_status hdp_solve(hdp_handle* H, const hdp_rhs* rhs, hdp_c64* field, int32_t 
   API_END
 }
 
-// dE_far(angle)/dphi as element vectors (vertex basis, x index fastest): the far
-// field is linear in the coefficients of the outside elements along Gamma,
-// E = sum_q c_q [(xhat.n') u(x_q) + (ik)^-1 d_n' u(x_q)], c_q = w_q e^{-ik xhat.x_q}.
-static std::vector<cd> far_functional(const Handle& h, double angle, const uint8_t* inside) {
-  std::vector<cd> g(size_t(h.dof), 0.0);
-  const double xh = std::cos(angle), yh = std::sin(angle);
-  const cd I(0.0, 1.0);
-  for (int e = 0; e < h.E; ++e) {
-    if (inside[e]) continue;
-    for (int s = 1; s <= 4; ++s) {
-      const int si = 4 * e + s - 1;
-      bool facing_inside = false;
-      if (h.side_type[si] == 1 || h.side_type[si] == 2) {
-        facing_inside = inside[h.nb_e[si]] != 0;
-      } else if (h.side_type[si] == 3) {
-        int n_in = 0;
-        for (int f : h.side_nbrs[si]) n_in += inside[f] != 0;
-        if (n_in != 0 && n_in != int(h.side_nbrs[si].size()))
-          fail(HDP_E_ARG, "far-field boundary must follow whole element sides of the outside elements");
-        facing_inside = n_in != 0;
-      }
-      if (!facing_inside) continue;
-      const int n = h.deg[e] + 1, q = n + 12;
-      std::vector<double> xq, wq, row(n), dend(n);
-      gauss_legendre(q, xq, wq);
-      const double ox = h.ox[e], oy = h.oy[e], hx = h.hx[e], hy = h.hy[e];
-      const double nx = s == 1 ? 1 : s == 2 ? -1 : 0, ny = s == 3 ? 1 : s == 4 ? -1 : 0;   // into e
-      const double xn = xh * nx + yh * ny;
-      const double dsc = s <= 2 ? nx * 2.0 / hx : ny * 2.0 / hy;
-      vertex_basis_dx(n, (s == 2 || s == 4) ? 1.0 : -1.0, dend.data());
-      std::vector<cd> T(n, 0.0);   // T_b = sum_q c_q N~_b(t_q)
-      for (int t = 0; t < q; ++t) {
-        double x, y;
-        if (s <= 2) { x = s == 1 ? ox : ox + hx; y = oy + (xq[t] + 1) * hy / 2; }
-        else { y = s == 3 ? oy : oy + hy; x = ox + (xq[t] + 1) * hx / 2; }
-        const cd c = wq[t] * ((s <= 2 ? hy : hx) / 2) * std::exp(-I * h.k * (xh * x + yh * y));
-        vertex_basis(n, xq[t], row.data());
-        for (int b = 0; b < n; ++b) T[b] += c * row[b];
-      }
-      const int a0 = (s == 2 || s == 4) ? 0 : 1;
-      const int64_t base = h.dof_off[e];
-      for (int b = 0; b < n; ++b)
-        for (int a = 0; a < n; ++a) {
-          const cd v = T[b] * ((a == a0 ? xn : 0.0) + dsc * dend[a] / (I * h.k));
-          const int64_t idx = s <= 2 ? a + int64_t(n) * b : b + int64_t(n) * a;
-          g[base + idx] += v;
-        }
-    }
-  }
-  return g;
-}
-
 hdp_status hdp_far_intensity_gradient(hdp_handle* H, double incidence, double far_angle, const uint8_t* far_inside,
                                       double* J, double* grad, hdp_stats* stats) {
   API_BEGIN
@@ -1920,19 +1879,17 @@ hdp_status hdp_far_intensity_gradient(hdp_handle* H, double incidence, double fa
   fw.kind = HDP_RHS_PLANE_WAVE_SCATTERED;
   fw.n_rhs = 1;
   fw.angles = &incidence;
+  double2 E;
   SolveOut so = solve_core(h, &fw, 1, 1, [&] {
     HIPCHECK(hipMemcpyAsync(d.adj_u, d.full1, size_t(h.dof) * sizeof(double2), hipMemcpyDeviceToDevice, s));
     far_prepare(h, 1, &far_angle, far_inside, 1);
     launch_far_field(h, d.full1, 1, 1, d.adj_E, s);
+    HIPCHECK(hipMemcpyAsync(&E, d.adj_E, sizeof(double2), hipMemcpyDeviceToHost, s));
   });
-  double2 E;
-  HIPCHECK(hipMemcpyAsync(&E, d.adj_E, sizeof(double2), hipMemcpyDeviceToHost, s));
-  // adjoint: A lambda = dE/dphi with the same solver (A is complex symmetric)
-  std::vector<cd> g = far_functional(h, far_angle, far_inside);
-  std::vector<double2> gp(g.size());
-  for (size_t i = 0; i < g.size(); ++i) gp[i] = make_double2(g[i].real(), g[i].imag());
-  HIPCHECK(hipMemcpyAsync(d.adj_g, gp.data(), gp.size() * sizeof(double2), hipMemcpyHostToDevice, s));
-  HIPCHECK(hipStreamSynchronize(s));
+  // adjoint: A lambda = dE/dphi with the same solver (A is complex symmetric).  The far
+  // field is linear in the coefficients of the outside elements along Gamma,
+  // E = sum_q c_q [(xhat.n') u(x_q) + (ik)^-1 d_n' u(x_q)], c_q = w_q e^{-ik xhat.x_q}.
+  launch_far_adjoint(h, d.adj_g, s);
   hdp_rhs ad{};
   ad.kind = HDP_RHS_ELEMENT_LOADS;
   ad.n_rhs = 1;

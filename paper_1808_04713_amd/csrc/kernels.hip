@@ -1181,107 +1181,198 @@ __global__ void __launch_bounds__(NT) k_far_trace(const int* __restrict__ elem, 
 }
 
 // Far field, step 2: E[r][phi] = sum_q w_q e^{-i k xhat.x_q} [(xhat.n'_q) U_q + (i k)^-1 DU_q].
+// A workgroup takes FAR_A angles and FAR_R columns: w_q e^{-i k xhat.x_q} and xhat.n'_q
+// of FAR_Q nodes are formed once (a sine and a cosine each) and shared by its columns,
+// and a node's U and DU are read once for its angles.  360 angles and 64 columns on
+// the boundary of a 64x64-element box: 316 us with a workgroup per angle and the
+// phases formed by every column's thread.
+constexpr int FAR_A = 4, FAR_R = 16, FAR_Q = 64;
+
 __global__ void __launch_bounds__(NT) k_far_sum(int nq, const double* __restrict__ px, const double* __restrict__ py,
                                                 const double* __restrict__ pw, const double* __restrict__ pnx,
                                                 const double* __restrict__ pny, const double* __restrict__ ang,
                                                 double k, const double2* __restrict__ U, const double2* __restrict__ DU,
                                                 int R, int nrhs_out, int nfar, double2* __restrict__ E) {
   __shared__ double2 red[NT];
-  const int f = blockIdx.x;
-  const double cx = cos(ang[f]), cy = sin(ang[f]);
-  const int r = threadIdx.x % R, rl = threadIdx.x / R, step = NT / R;
-  double ax = 0, ay = 0;
-  for (int q = rl; q < nq; q += step) {
-    double ph = -k * (cx * px[q] + cy * py[q]);
-    double c = cos(ph), s = sin(ph);
-    double xn = cx * pnx[q] + cy * pny[q];
-    double2 u = U[(int64_t)q * R + r], du = DU[(int64_t)q * R + r];
-    // (i k)^-1 du = -i du / k
-    double tx = xn * u.x + du.y / k, ty = xn * u.y - du.x / k;
-    ax += pw[q] * (c * tx - s * ty);
-    ay += pw[q] * (c * ty + s * tx);
+  __shared__ double2 ph[FAR_A][FAR_Q];
+  __shared__ double xn[FAR_A][FAR_Q];
+  const int f0 = blockIdx.x * FAR_A, nf = min(FAR_A, nfar - f0);
+  const int RB = min(R, FAR_R), r0 = blockIdx.y * RB;   // R is a power of two
+  const int rl = threadIdx.x % RB, ql = threadIdx.x / RB, step = NT / RB;
+  // the angle whose phases this thread forms
+  const int tf = threadIdx.x / FAR_Q, tq = threadIdx.x % FAR_Q;
+  static_assert(FAR_A * FAR_Q == NT, "one phase per thread");
+  const double cx = cos(ang[f0 + min(tf, nf - 1)]), cy = sin(ang[f0 + min(tf, nf - 1)]);
+  double2 acc[FAR_A];
+#pragma unroll
+  for (int f = 0; f < FAR_A; ++f) acc[f] = make_double2(0, 0);
+  const double ik = 1.0 / k;
+  for (int q0 = 0; q0 < nq; q0 += FAR_Q) {
+    const int q = min(q0 + tq, nq - 1);
+    const double a = -k * (cx * px[q] + cy * py[q]), w = q0 + tq < nq ? pw[q] : 0.0;
+    __syncthreads();
+    ph[tf][tq] = make_double2(w * cos(a), w * sin(a));
+    xn[tf][tq] = cx * pnx[q] + cy * pny[q];
+    __syncthreads();
+    for (int t = ql; t < min(FAR_Q, nq - q0); t += step) {
+      const double2 u = U[(int64_t)(q0 + t) * R + r0 + rl], du = DU[(int64_t)(q0 + t) * R + r0 + rl];
+      const double2 v = make_double2(du.y * ik, -du.x * ik);   // (i k)^-1 du
+#pragma unroll
+      for (int f = 0; f < FAR_A; ++f) {
+        const double2 c = ph[f][t];
+        const double x = xn[f][t], tx = x * u.x + v.x, ty = x * u.y + v.y;
+        acc[f].x += c.x * tx - c.y * ty;
+        acc[f].y += c.x * ty + c.y * tx;
+      }
+    }
   }
-  double2 t = block_sum_by_rhs(make_double2(ax, ay), R, red);
-  if (threadIdx.x < R && threadIdx.x < nrhs_out) E[(int64_t)threadIdx.x * nfar + f] = t;
+#pragma unroll
+  for (int f = 0; f < FAR_A; ++f) {
+    if (f >= nf) break;   // uniform
+    const double2 t = block_sum_by_rhs(acc[f], RB, red);
+    if (threadIdx.x < RB && r0 + threadIdx.x < nrhs_out) E[(int64_t)(r0 + threadIdx.x) * nfar + f0 + f] = t;
+  }
 }
 
-// Plane-wave loads in the vertex basis, one block per (listed element, RHS):
+// The adjoint of the two far-field steps at one angle: the element vectors
+// dE/dphi of the outside elements along the boundary (G is zero elsewhere, cleared
+// before).  One workgroup per element: the sides of an element follow each other in
+// the list, the first one's workgroup adds them all, in their order.  With
+// T_b = sum_q w_q e^{-i k xhat.x_q} N~_b(t_q) a side's entry (a across it, b along it)
+// is T_b ((xhat.n') [a = a0] + (i k)^-1 dscale dN~_a).  Formed on the host, with a
+// whole zero vector to allocate and to send, it took 1.8 ms on 64x64 elements.
+__global__ void __launch_bounds__(NT) k_far_adjoint(int nsides, const int* __restrict__ elem,
+                                                    const int* __restrict__ side, const int* __restrict__ node_off,
+                                                    const int64_t* __restrict__ tab_off,
+                                                    const double* __restrict__ tab, const double* __restrict__ dscale,
+                                                    const int* __restrict__ elem_cls, const int* __restrict__ cls_n,
+                                                    const int64_t* __restrict__ dof_off,
+                                                    const double* __restrict__ px, const double* __restrict__ py,
+                                                    const double* __restrict__ pw, const double* __restrict__ pnx,
+                                                    const double* __restrict__ pny, const double* __restrict__ ang,
+                                                    double k, double2* __restrict__ G) {
+  __shared__ double2 c[128], T[64];
+  const int e = elem[blockIdx.x];
+  if (blockIdx.x > 0 && elem[blockIdx.x - 1] == e) return;
+  const int n = cls_n[elem_cls[e]];
+  double2* __restrict__ g = G + dof_off[e];
+  const double cx = cos(ang[0]), cy = sin(ang[0]);
+  for (int s = blockIdx.x; s < nsides && elem[s] == e; ++s) {
+    const int q0 = node_off[s], nq = node_off[s + 1] - q0, sd = side[s];
+    const double* Nq = tab + tab_off[s];
+    const double* dend = Nq + (int64_t)nq * n;
+    for (int q = threadIdx.x; q < nq; q += NT) {
+      const double a = -k * (cx * px[q0 + q] + cy * py[q0 + q]), w = pw[q0 + q];
+      c[q] = make_double2(w * cos(a), w * sin(a));
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < n; b += NT) {
+      double2 t = make_double2(0, 0);
+      for (int q = 0; q < nq; ++q) {
+        const double N = Nq[(int64_t)q * n + b];
+        t.x += c[q].x * N;
+        t.y += c[q].y * N;
+      }
+      T[b] = t;
+    }
+    __syncthreads();
+    const bool xside = sd <= 2;
+    const int a0 = (sd == 2 || sd == 4) ? 0 : 1;
+    const double xn = cx * pnx[q0] + cy * pny[q0], ds = dscale[s] / k;
+    for (int t = threadIdx.x; t < n * n; t += NT) {
+      const int ix = t % n, iy = t / n, a = xside ? ix : iy, b = xside ? iy : ix;
+      const double2 v = cmul(T[b], make_double2(a == a0 ? xn : 0.0, -ds * dend[a]));
+      double2 o = s == (int)blockIdx.x ? make_double2(0, 0) : g[t];
+      o.x += v.x;
+      o.y += v.y;
+      g[t] = o;
+    }
+    __syncthreads();
+  }
+}
+
+// Plane-wave loads in the vertex basis:
 // scattered field, f = k^2 (eps - 1) e^{ik d.x} (separable: b = f0 a (x) b);
 // total field, impedance data g = ik(d.n - 1) e^{ik d.x} on the boundary sides.
-// Nq holds the vertex basis at the element degree's Gauss nodes ([q][n]).
+// N holds the vertex basis at the element degree's Gauss nodes ([q][64]).
+// One workgroup per (listed element, RB columns): the phases of its nodes are formed
+// once per column (2 q or 4 q of them, in shared memory), then every basis function's
+// integral, then the element's block in runs of RB columns.  With a workgroup per
+// column and the phases formed again for every basis function, 256 elements of degree
+// 15 and 64 angles took 330 us, nearly all of it sines and cosines.
+constexpr int PW_R = 8;
+
 __global__ void __launch_bounds__(NT) k_plane_wave_loads(
     int kind, const int* __restrict__ elems, const int* __restrict__ elem_cls, const int* __restrict__ cls_n,
     const int64_t* __restrict__ dof_off, const int* __restrict__ cls_q, const int64_t* __restrict__ cls_qoff,
     const double* __restrict__ qx, const double* __restrict__ qw, const double* __restrict__ qN,
     const double* __restrict__ ox, const double* __restrict__ oy, const double* __restrict__ hx,
     const double* __restrict__ hy, const double* __restrict__ eps, const int* __restrict__ bmask,
-    const double* __restrict__ angles, double k, double2* __restrict__ B, int R) {
-  __shared__ double2 a[64], b[64], sv[4][64];
-  const int e = elems[blockIdx.x], r = blockIdx.y;
+    const double* __restrict__ angles, double k, double2* __restrict__ B, int nrhs, int R, int RB) {
+  extern __shared__ double2 sm[];
+  const int e = elems[blockIdx.x], r0 = blockIdx.y * RB, nr = min(RB, nrhs - r0);
   const int c = elem_cls[e], n = cls_n[c], q = cls_q[c];
   const double* xq = qx + cls_qoff[c];
   const double* wq = qw + cls_qoff[c];
   const double* N = qN + cls_qoff[c] * 64;   // [q][64], basis padded to 64 columns
-  const double dx = cos(angles[r]), dy = sin(angles[r]);
   const double X0 = ox[e], Y0 = oy[e], HX = hx[e], HY = hy[e];
   const int64_t base = dof_off[e];
-  if (kind == 2) {
-    for (int m = threadIdx.x; m < 2 * n; m += NT) {
-      const bool yd = m >= n;
-      const int mm = yd ? m - n : m;
-      double sx = 0, sy = 0;
-      for (int t = 0; t < q; ++t) {
-        double pos = yd ? Y0 + (xq[t] + 1) * HY / 2 : X0 + (xq[t] + 1) * HX / 2;
-        double ph = k * (yd ? dy : dx) * pos;
-        double wn = wq[t] * N[(int64_t)t * 64 + mm];
-        sx += wn * cos(ph);
-        sy += wn * sin(ph);
-      }
-      if (yd) b[mm] = make_double2(sx, sy); else a[mm] = make_double2(sx, sy);
+  const int ns = kind == 2 ? 2 : 4;   // directions, or sides
+  double2* ph = sm;                   // [ns][q][nr]: weighted phases
+  double2* sv = sm + ns * q * nr;     // [ns][n][nr]: integrals against the basis
+  for (int i = threadIdx.x; i < ns * q * nr; i += NT) {
+    const int r = i % nr, st = i / nr, sd = st / q, t = st - sd * q;
+    const double dx = cos(angles[r0 + r]), dy = sin(angles[r0 + r]);
+    double2 v = make_double2(0, 0);
+    if (kind == 2) {
+      const double pos = sd ? Y0 + (xq[t] + 1) * HY / 2 : X0 + (xq[t] + 1) * HX / 2;
+      const double p = k * (sd ? dy : dx) * pos;
+      v = make_double2(cos(p), sin(p));
+    } else if (bmask[e] & (1 << sd)) {
+      const double nx = sd == 0 ? -1 : sd == 1 ? 1 : 0, ny = sd == 2 ? -1 : sd == 3 ? 1 : 0;
+      const double gy = k * (dx * nx + dy * ny - 1.0);   // ik(d.n - 1)
+      double x, y;
+      if (sd <= 1) { x = sd == 0 ? X0 : X0 + HX; y = Y0 + (xq[t] + 1) * HY / 2; }
+      else { y = sd == 2 ? Y0 : Y0 + HY; x = X0 + (xq[t] + 1) * HX / 2; }
+      const double p = k * (dx * x + dy * y);
+      v = make_double2(-gy * sin(p), gy * cos(p));
     }
-    __syncthreads();
-    const double f0 = k * k * (eps[e] - 1.0) * (HX / 2) * (HY / 2);
-    for (int t = threadIdx.x; t < n * n; t += NT) {
-      int ix = t % n, iy = t / n;
-      double2 p = cmul(a[ix], b[iy]);
-      B[(base + t) * R + r] = make_double2(f0 * p.x, f0 * p.y);
+    ph[i] = v;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < ns * n * nr; i += NT) {
+    const int r = i % nr, st = i / nr, sd = st / n, m = st - sd * n;
+    const double hl = kind == 2 ? 1.0 : (sd <= 1 ? HY : HX) / 2;
+    double sx = 0, sy = 0;
+    for (int t = 0; t < q; ++t) {
+      const double wn = wq[t] * hl * N[(int64_t)t * 64 + m];
+      const double2 v = ph[(sd * q + t) * nr + r];
+      sx += wn * v.x;
+      sy += wn * v.y;
     }
-  } else {
-    for (int t = threadIdx.x; t < n * n; t += NT) B[(base + t) * R + r] = make_double2(0, 0);
-    for (int m = threadIdx.x; m < 4 * n; m += NT) {
-      const int sd = m / n + 1, mm = m % n;
-      double sx = 0, sy = 0;
-      if (bmask[e] & (1 << (sd - 1))) {
-        const double nx = sd == 1 ? -1 : sd == 2 ? 1 : 0, ny = sd == 3 ? -1 : sd == 4 ? 1 : 0;
-        const double hl = sd <= 2 ? HY : HX;
-        const double gx = 0, gy = k * (dx * nx + dy * ny - 1.0);   // ik(d.n - 1)
-        for (int t = 0; t < q; ++t) {
-          double x, y;
-          if (sd <= 2) { x = sd == 1 ? X0 : X0 + HX; y = Y0 + (xq[t] + 1) * HY / 2; }
-          else { y = sd == 3 ? Y0 : Y0 + HY; x = X0 + (xq[t] + 1) * HX / 2; }
-          double ph = k * (dx * x + dy * y);
-          double cr = cos(ph), ci = sin(ph);
-          double wn = wq[t] * (hl / 2) * N[(int64_t)t * 64 + mm];
-          sx += wn * (gx * cr - gy * ci);
-          sy += wn * (gx * ci + gy * cr);
-        }
-      }
-      sv[sd - 1][mm] = make_double2(sx, sy);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      // scatter the four side vectors onto the trace modes (left: ix=1, right: ix=0,
-      // bottom: iy=1, top: iy=0); corners receive two contributions
-      for (int sd = 1; sd <= 4; ++sd) {
-        if (!(bmask[e] & (1 << (sd - 1)))) continue;
-        for (int mm = 0; mm < n; ++mm) {
-          int64_t pos = sd == 1 ? 1 + (int64_t)n * mm : sd == 2 ? (int64_t)n * mm : sd == 3 ? mm + n : mm;
-          double2& dst = B[(base + pos) * R + r];
-          dst.x += sv[sd - 1][mm].x;
-          dst.y += sv[sd - 1][mm].y;
-        }
+    sv[i] = make_double2(sx, sy);
+  }
+  __syncthreads();
+  const double f0 = k * k * (eps[e] - 1.0) * (HX / 2) * (HY / 2);
+  const int mask = kind == 2 ? 0 : bmask[e];
+  for (int i = threadIdx.x; i < n * n * nr; i += NT) {
+    const int r = i % nr, t = i / nr, ix = t % n, iy = t / n;
+    double2 v = make_double2(0, 0);
+    if (kind == 2) {
+      const double2 p = cmul(sv[ix * nr + r], sv[(n + iy) * nr + r]);
+      v = make_double2(f0 * p.x, f0 * p.y);
+    } else {
+      // the side vectors on the trace modes (left: ix=1, right: ix=0, bottom: iy=1,
+      // top: iy=0); corners receive two contributions
+      for (int sd = 0; sd < 4; ++sd) {
+        const int across = sd <= 1 ? ix : iy, along = sd <= 1 ? iy : ix;
+        if (!(mask & (1 << sd)) || across != (sd & 1 ? 0 : 1)) continue;
+        const double2 a = sv[(sd * n + along) * nr + r];
+        v.x += a.x;
+        v.y += a.y;
       }
     }
+    B[(base + t) * R + r0 + r] = v;
   }
 }
 
@@ -2513,8 +2604,19 @@ void launch_far_field(const Handle& h, const double2* X, int R, int nrhs_out, do
   }
   hipLaunchKernelGGL(k_far_trace, dim3(f.nsides, R), dim3(NT), 0, s, f.elem, f.side, f.node_off, f.tab_off, f.tab,
                      f.dscale, d.elem_cls, d.cls_n, d.dof_off, X, R, f.U, f.DU);
-  hipLaunchKernelGGL(k_far_sum, dim3(f.nfar), dim3(NT), 0, s, f.nq, f.px, f.py, f.pw, f.pnx, f.pny, f.ang, h.k, f.U,
+  hipLaunchKernelGGL(k_far_sum, dim3((f.nfar + FAR_A - 1) / FAR_A, (R + FAR_R - 1) / FAR_R), dim3(NT), 0, s, f.nq, f.px, f.py, f.pw, f.pnx, f.pny, f.ang, h.k, f.U,
                      f.DU, R, nrhs_out, f.nfar, E);
+  HIPCHECK(hipGetLastError());
+}
+
+// G (dof, cleared here) = dE/dphi at the first angle of the prepared boundary
+void launch_far_adjoint(const Handle& h, double2* G, hipStream_t s) {
+  const auto& d = h.d;
+  const auto& f = h.far;
+  launch_fill_zero(G, h.dof, s);
+  if (f.nsides == 0) return;
+  hipLaunchKernelGGL(k_far_adjoint, dim3(f.nsides), dim3(NT), 0, s, f.nsides, f.elem, f.side, f.node_off, f.tab_off,
+                     f.tab, f.dscale, d.elem_cls, d.cls_n, d.dof_off, f.px, f.py, f.pw, f.pnx, f.pny, f.ang, h.k, G);
   HIPCHECK(hipGetLastError());
 }
 
@@ -2523,8 +2625,12 @@ void launch_plane_wave_loads(const Handle& h, int kind, const int* elems, int ne
   if (nel == 0 || nrhs == 0) return;
   if (nrhs > R) fail(HDP_E_ARG, "plane-wave loads: more right-hand sides than the stride");
   const auto& d = h.d;
-  hipLaunchKernelGGL(k_plane_wave_loads, dim3(nel, nrhs), dim3(NT), 0, s, kind, elems, d.elem_cls, d.cls_n, d.dof_off,
-                     d.cls_q, d.cls_qoff, d.qx, d.qw, d.qN, d.ox, d.oy, d.hx, d.hy, d.eps, d.bmask, angles, h.k, B, R);
+  size_t rows = 0;   // nodes and basis functions of the largest class
+  for (auto& C : h.classes) rows = std::max(rows, h.quad_x.at(C.n).size() + size_t(C.n));
+  const int RB = std::min(nrhs, PW_R);
+  const size_t lds = rows * (kind == 2 ? 2 : 4) * RB * sizeof(double2);
+  hipLaunchKernelGGL(k_plane_wave_loads, dim3(nel, (nrhs + RB - 1) / RB), dim3(NT), lds, s, kind, elems, d.elem_cls, d.cls_n, d.dof_off,
+                     d.cls_q, d.cls_qoff, d.qx, d.qw, d.qN, d.ox, d.oy, d.hx, d.hy, d.eps, d.bmask, angles, h.k, B, nrhs, R, RB);
   HIPCHECK(hipGetLastError());
 }
 

@@ -127,6 +127,7 @@ void launch_eps_gradient(const Handle& h, const double2* U, const double2* Lam, 
 void launch_plane_wave_loads(const Handle& h, int kind, const int* elems, int nel, const double* angles, double2* B,
                              int nrhs, int R, hipStream_t s);
 // far field of the recovered fields X ([dof][R]) into E ([nrhs_out][nfar]) using h.far
+void launch_far_adjoint(const Handle& h, double2* G, hipStream_t s);
 void launch_far_field(const Handle& h, const double2* X, int R, int nrhs_out, double2* E, hipStream_t s);
 int dots_blocks(int n, int R);
 

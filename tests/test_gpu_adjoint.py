@@ -39,6 +39,20 @@ def test_gradient_matches_oracle_adjoint(precision):
     assert np.linalg.norm(g - g0) < tol * np.linalg.norm(g0)
 
 
+def test_gradient_with_two_boundary_sides_on_one_element():
+    """A boundary around an L: the outside element in its notch carries two sides,
+    which one workgroup adds."""
+    w, _ = design_case()
+    c = W.leaf_centres(w)
+    inside = (np.abs(c[:, 0]) < 0.7) & (np.abs(c[:, 1]) < 0.7) & ~((c[:, 0] > 0.4) & (c[:, 1] > 0.4))
+    J0, g0, E0 = adj.eps_gradient(w, 0.4, 2.1, inside)
+    s = hdp().Solver(w, tol=1e-13, max_iter=400)
+    J, g, st = s.far_intensity_gradient(0.4, 2.1, inside)
+    s.close()
+    assert abs(J - J0) < 1e-9 * J0
+    assert np.linalg.norm(g - g0) < 1e-9 * np.linalg.norm(g0)
+
+
 def test_autograd_function_returns_the_adjoint_gradient():
     w, inside = design_case()
     _, g0, _ = adj.eps_gradient(w, 0.0, 0.0, inside)

@@ -166,6 +166,47 @@ def test_interface_rhs_several_angles(name, kind):
     s.close()
 
 
+@pytest.mark.parametrize("kind", ["plane_wave_scattered", "plane_wave_total"])
+@pytest.mark.parametrize("R", [1, 7, 8, 9, 33])
+def test_loads_and_far_field_at_every_block_width(R, kind):
+    """The workgroup of the plane-wave loads takes 8 columns, that of the far-field
+    sum 16 columns and 4 angles: counts at and beside these against one column and
+    all angles at a time."""
+    w = CASES["scatterer_6x6_p6"]
+    c = W.leaf_centres(w)
+    inside = (np.abs(c[:, 0]) < 0.4) & (np.abs(c[:, 1]) < 0.4)
+    inside |= np.asarray(w["eps_r"]) != 1.0
+    angles = np.linspace(0.1, 6.0, R)
+    s = hdp().Solver(w, tol=1e-12, max_iter=300, max_rhs=64)
+    g = s.interface_rhs(kind, angles).cpu().numpy()
+    fars = [s.solve(kind, angles, False, np.linspace(0, 5, nf), inside)[1].cpu().numpy() for nf in (1, 3, 4, 5)]
+    for i, a in enumerate(angles):
+        one = s.interface_rhs(kind, [a]).cpu().numpy()
+        assert rel(g[:, i], one[:, 0]) < 1e-12
+    for i in range(0, R, 4):
+        for far, nf in zip(fars, (1, 3, 4, 5)):
+            one = s.solve(kind, [angles[i]], False, np.linspace(0, 5, nf), inside)[1].cpu().numpy()
+            assert rel(far[i], one[0]) < 1e-9
+    s.close()
+
+
+@pytest.mark.parametrize("m", [1, 2, 31, 32, 33, 64, 65])
+def test_unfinished_solves_match_the_oracle(m, oracles):
+    """The iterate after m steps at the edges of the back substitution's blocks of 32
+    columns, three equal columns, against the oracle's iterate."""
+    name = "uniform_5x5_p7_l3"
+    disc, l, E = oracles[name]
+    w = CASES[name]
+    kind, vals = hdp().rhs_values(w)
+    s = hdp().Solver(w, tol=1e-14, max_iter=m, max_rhs=4)
+    field, st = s.solve(kind, [vals[0]] * 3)
+    got = field.cpu().numpy()
+    ref = np.concatenate(pb.gll_field(disc.mesh, disc.degrees, E.solve(tol=1e-14, max_iter=m)))
+    for r in range(3):
+        assert rel(got[r], ref) < 1e-10
+    s.close()
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_solve_fp64_matches_oracle(name, oracles):
     disc, l, E = oracles[name]
