@@ -12,6 +12,7 @@
 #include "basis.hpp"
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "team.hpp"
 
 struct hdp_handle {
   hdp::Handle h;
@@ -49,10 +50,15 @@ T* dalloc(Handle& h, size_t count) {
 }
 
 template <class T>
-T* upload(Handle& h, const std::vector<T>& v) {
-  T* p = dalloc<T>(h, v.size());
-  if (!v.empty()) HIPCHECK(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+T* upload(Handle& h, const T* v, size_t count) {
+  T* p = dalloc<T>(h, count);
+  if (count) HIPCHECK(hipMemcpy(p, v, count * sizeof(T), hipMemcpyHostToDevice));
   return p;
+}
+
+template <class T>
+T* upload(Handle& h, const std::vector<T>& v) {
+  return upload(h, v.data(), v.size());
 }
 
 std::vector<double2> pack_c(const std::vector<cd>& v) {
@@ -204,10 +210,11 @@ static void coarse_solve_dense_tiles(Handle& h, const double2* g, double2* w, in
 
 // Nested-dissection factor: assembled on the host (coarse_nd.cpp), uploaded
 // with its per-depth front-assembly entries and row tasks.
-static void build_coarse_nd(Handle& h, const std::vector<int64_t>& kidx, const std::vector<double2>& kval) {
+static void build_coarse_nd(Handle& h, const std::vector<int64_t>& kidx, const std::vector<double2>& kval,
+                            Team& team) {
   auto& d = h.d;
   NDHost f;
-  nd_factor(h, kidx, kval, f);
+  nd_factor(h, kidx, kval, f, &team);
   d.nd_off = upload(h, h.nd_off);
   d.nd_boff = upload(h, h.nd_boff);
   d.nd_bnd = upload(h, h.nd_bnd);
@@ -223,7 +230,7 @@ static void build_coarse_nd(Handle& h, const std::vector<int64_t>& kidx, const s
     d.nd_g1[bwd] = upload(h, p.gptr);
     h.nd_l1[bwd] = p.launches;
   }
-  d.nd_fac = upload(h, f.fac);
+  d.nd_fac = upload(h, static_cast<const double2*>(f.fac.data()), f.fac.size());
   const size_t Rp = size_t(pow2ceil(h.max_rhs));
   {
     // task lists and partial tiles sized for every split the autotuner may try
@@ -469,7 +476,7 @@ static double coarse_residual(Handle& h, const std::vector<int64_t>& kidx, const
   return std::sqrt(rn / bn);
 }
 
-void build_device(Handle& h) {
+void build_device(Handle& h, Team& team) {
   auto& d = h.d;
   int E = h.E;
   d.elem_cls = upload(h, h.cls);
@@ -701,7 +708,7 @@ void build_device(Handle& h) {
   d.Kc = upload(h, Kc);
   std::vector<int64_t> kidx;
   std::vector<double2> kval;
-  coarse_coo(h, kidx, kval);
+  coarse_coo(h, kidx, kval, &team);
   size_t nK = size_t(h.nK);
   h.coarse_band_bytes = coarse_band_bytes(h.nK, kidx);
   rocblas_handle rb;
@@ -710,7 +717,7 @@ void build_device(Handle& h) {
   h.rocblas = rb;   // rocSOLVER's factorisation of the dense coarse inverse at set-up
   // the coarse factor chosen at set-up: dense inverse (0) or nested dissection (2)
   const auto tk = std::chrono::steady_clock::now();
-  if (h.coarse_mode == 2) build_coarse_nd(h, kidx, kval);
+  if (h.coarse_mode == 2) build_coarse_nd(h, kidx, kval, team);
   else build_coarse_dense(h, kidx, kval);
   h.setup_coarse_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - tk).count();
   // work buffers sized for the largest RHS batch (padded to a power of two)
@@ -1451,12 +1458,13 @@ hdp_status hdp_setup(const hdp_mesh* mesh, const hdp_problem* prob, const hdp_op
     HIPCHECK(hipEventCreateWithFlags(&h.order_ev, hipEventDisableTiming));
     HIPCHECK(hipEventRecord(h.order_ev, h.user_stream));
     HIPCHECK(hipStreamWaitEvent(h.stream, h.order_ev, 0));
+    Team team;
     {
       const auto th = std::chrono::steady_clock::now();
-      build_host(h, mesh, prob);
+      build_host(h, mesh, prob, &team);
       h.setup_host_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - th).count();
     }
-    build_device(h);
+    build_device(h, team);
     if (opt->flags & HDP_FLAG_AUTOTUNE) autotune(h, opt->tile_fdm == 0, opt->tile_slot == 0);
   } catch (...) {
     if (h.stream) (void)hipStreamSynchronize(h.stream);

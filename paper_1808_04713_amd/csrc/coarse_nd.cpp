@@ -16,12 +16,14 @@
 // Pivoting is partial inside each F_II (Gauss-Jordan); the blocks are taken in
 // tree order, as the strip factor takes its strips in order.
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <mutex>
-#include <thread>
+#if !defined(__HIP_DEVICE_COMPILE__) && defined(__x86_64__)
+#include <immintrin.h>
+#endif
 
 #include "internal.hpp"
+#include "team.hpp"
 
 namespace hdp {
 
@@ -31,41 +33,95 @@ struct Z {
   double re, im;
 };
 
-// C (m x n) += alpha A (m x k) B (k x n), row-major, alpha real.  Four rows of C
-// share each row of B.
-void zgemm_acc(int m, int n, int k, double alpha, const Z* A, int64_t lda, const Z* B, int64_t ldb, Z* C,
-               int64_t ldc) {
-  int i = 0;
-  for (; i + 4 <= m; i += 4) {
-    Z* c0 = C + i * ldc;
-    Z* c1 = c0 + ldc;
-    Z* c2 = c1 + ldc;
-    Z* c3 = c2 + ldc;
-    for (int q = 0; q < k; ++q) {
-      const Z a0 = A[i * lda + q], a1 = A[(i + 1) * lda + q], a2 = A[(i + 2) * lda + q], a3 = A[(i + 3) * lda + q];
-      const double r0 = alpha * a0.re, j0 = alpha * a0.im, r1 = alpha * a1.re, j1 = alpha * a1.im;
-      const double r2 = alpha * a2.re, j2 = alpha * a2.im, r3 = alpha * a3.re, j3 = alpha * a3.im;
-      const Z* b = B + q * ldb;
-      for (int j = 0; j < n; ++j) {
-        const double br = b[j].re, bi = b[j].im;
-        c0[j].re += r0 * br - j0 * bi; c0[j].im += r0 * bi + j0 * br;
-        c1[j].re += r1 * br - j1 * bi; c1[j].im += r1 * bi + j1 * br;
-        c2[j].re += r2 * br - j2 * bi; c2[j].im += r2 * bi + j2 * br;
-        c3[j].re += r3 * br - j3 * bi; c3[j].im += r3 * bi + j3 * br;
-      }
+// Rows of complex numbers, two to a vector: each product's real part is re re - im im
+// and its imaginary part re im + im re, rounded as the scalar form rounds them (no
+// fused operations), so both forms give the same factor.
+#if !defined(__HIP_DEVICE_COMPILE__) && defined(__x86_64__)
+#define HDP_HOST_AVX 1
+__attribute__((target("avx"))) inline __m256d cmul_avx(__m256d re, __m256d im, __m256d b) {
+  return _mm256_addsub_pd(_mm256_mul_pd(re, b), _mm256_mul_pd(im, _mm256_permute_pd(b, 5)));
+}
+
+// y -= f x over n entries
+__attribute__((target("avx"))) void row_minus_avx(int n, Z f, const Z* x, Z* y) {
+  const __m256d re = _mm256_set1_pd(f.re), im = _mm256_set1_pd(f.im);
+  int j = 0;
+  for (; j + 2 <= n; j += 2) {
+    double* yp = &y[j].re;
+    _mm256_storeu_pd(yp, _mm256_sub_pd(_mm256_loadu_pd(yp), cmul_avx(re, im, _mm256_loadu_pd(&x[j].re))));
+  }
+  for (; j < n; ++j) {
+    y[j].re -= f.re * x[j].re - f.im * x[j].im;
+    y[j].im -= f.re * x[j].im + f.im * x[j].re;
+  }
+}
+
+// C (4 x 4, ldc) += alpha A (4 x k, lda) P, P a packed k x 4 panel: the sums of a tile
+// stay in registers
+__attribute__((target("avx"))) void tile_avx(int k, double alpha, const Z* A, int64_t lda, const Z* P, Z* C,
+                                             int64_t ldc) {
+  __m256d c[4][2];
+  for (int r = 0; r < 4; ++r)
+    for (int h = 0; h < 2; ++h) c[r][h] = _mm256_loadu_pd(&C[r * ldc + 2 * h].re);
+  for (int q = 0; q < k; ++q) {
+    const __m256d b0 = _mm256_loadu_pd(&P[4 * q].re), b1 = _mm256_loadu_pd(&P[4 * q + 2].re);
+    for (int r = 0; r < 4; ++r) {
+      const Z a = A[r * lda + q];
+      const __m256d re = _mm256_set1_pd(alpha * a.re), im = _mm256_set1_pd(alpha * a.im);
+      c[r][0] = _mm256_add_pd(c[r][0], cmul_avx(re, im, b0));
+      c[r][1] = _mm256_add_pd(c[r][1], cmul_avx(re, im, b1));
     }
   }
-  for (; i < m; ++i) {
-    Z* c = C + i * ldc;
-    for (int q = 0; q < k; ++q) {
-      const Z a = A[i * lda + q];
-      const double ar = alpha * a.re, ai = alpha * a.im;
-      const Z* b = B + q * ldb;
-      for (int j = 0; j < n; ++j) {
-        c[j].re += ar * b[j].re - ai * b[j].im;
-        c[j].im += ar * b[j].im + ai * b[j].re;
+  for (int r = 0; r < 4; ++r)
+    for (int h = 0; h < 2; ++h) _mm256_storeu_pd(&C[r * ldc + 2 * h].re, c[r][h]);
+}
+#endif
+
+bool host_avx() {
+#ifdef HDP_HOST_AVX
+  static const bool yes = __builtin_cpu_supports("avx");
+  return yes;
+#else
+  return false;
+#endif
+}
+
+void row_minus(int n, Z f, const Z* x, Z* y) {
+#ifdef HDP_HOST_AVX
+  if (host_avx()) return row_minus_avx(n, f, x, y);
+#endif
+  for (int j = 0; j < n; ++j) {
+    y[j].re -= f.re * x[j].re - f.im * x[j].im;
+    y[j].im -= f.re * x[j].im + f.im * x[j].re;
+  }
+}
+
+// C (m x n) += alpha A (m x k) B (k x n), row-major, alpha real: panels of four columns
+// of B, packed, against four rows of A at a time; the sums run over k in order.
+void zgemm_acc(int m, int n, int k, double alpha, const Z* A, int64_t lda, const Z* B, int64_t ldb, Z* C,
+               int64_t ldc) {
+  std::vector<Z> P(size_t(k) * 4);
+  for (int j = 0; j < n; j += 4) {
+    const int nj = std::min(4, n - j);
+    if (nj == 4)
+      for (int q = 0; q < k; ++q)
+        for (int c = 0; c < 4; ++c) P[4 * size_t(q) + c] = B[q * ldb + j + c];
+    int i = 0;
+#ifdef HDP_HOST_AVX
+    if (nj == 4 && host_avx())
+      for (; i + 4 <= m; i += 4) tile_avx(k, alpha, A + i * lda, lda, P.data(), C + i * ldc + j, ldc);
+#endif
+    for (; i < m; ++i)
+      for (int c = 0; c < nj; ++c) {
+        Z s = C[i * ldc + j + c];
+        for (int q = 0; q < k; ++q) {
+          const double ar = alpha * A[i * lda + q].re, ai = alpha * A[i * lda + q].im;
+          const Z b = B[q * ldb + j + c];
+          s.re += ar * b.re - ai * b.im;
+          s.im += ar * b.im + ai * b.re;
+        }
+        C[i * ldc + j + c] = s;
       }
-    }
   }
 }
 
@@ -100,10 +156,7 @@ bool zinverse(int n, Z* A) {
       const Z f = ri[k];
       if (f.re == 0 && f.im == 0) continue;
       ri[k] = Z{0, 0};
-      for (int j = 0; j < n; ++j) {
-        ri[j].re -= f.re * rk[j].re - f.im * rk[j].im;
-        ri[j].im -= f.re * rk[j].im + f.im * rk[j].re;
-      }
+      row_minus(n, f, rk, ri);
     }
   }
   for (int k = n - 1; k >= 0; --k)
@@ -114,7 +167,10 @@ bool zinverse(int n, Z* A) {
 
 }  // namespace
 
-void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vector<double2>& kval, NDHost& f) {
+void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vector<double2>& kval, NDHost& f,
+               Team* shared) {
+  TeamOr threads(shared);
+  Team& team = threads.team;
   const int nn = int(h.nd_off.size()) - 1;
   const int64_t nK = h.nK;
   int maxd = 0;
@@ -124,8 +180,10 @@ void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vec
     for (int i = h.nd_off[t]; i < h.nd_off[t + 1]; ++i) node_of[i] = t;
   // original entries, each in the front of the node that owns its earlier index
   std::vector<std::vector<int64_t>> bucket(nn);
+  int64_t j = 0;   // keys row + nK column, sorted
   for (size_t q = 0; q < kidx.size(); ++q) {
-    const int64_t i = kidx[q] % nK, j = kidx[q] / nK;
+    while (kidx[q] >= (j + 1) * nK) ++j;
+    const int64_t i = kidx[q] - j * nK;
     bucket[node_of[std::min(i, j)]].push_back(int64_t(q));
   }
   auto nI_of = [&](int t) { return h.nd_off[t + 1] - h.nd_off[t]; };
@@ -143,14 +201,15 @@ void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vec
     f.flops_per_col += 8.0 * double(nI * nI + 2 * nB * nI);
   }
   f.urows = urows;
-  f.fac.assign(size_t(tot), make_double2(0, 0));
+  f.fac.resize(size_t(tot));   // its pages are first written by the threads below
   Z* fac = reinterpret_cast<Z*>(f.fac.data());
   std::vector<std::vector<Z>> schur(nn);   // S of a node until its parent has used it
   std::vector<std::vector<int>> by_depth(maxd + 1);
   for (int t = 0; t < nn; ++t) by_depth[h.nd_depth[t]].push_back(t);
   std::mutex err_mu;
   std::string err;
-  auto factor_node = [&](int t) {
+  std::vector<std::vector<Z>> front(nn);
+  auto assemble = [&](int t) {
     const int off = h.nd_off[t], nI = nI_of(t), nB = nB_of(t), nf = nI + nB;
     const int* B = h.nd_bnd.data() + h.nd_boff[t];
     auto pos = [&](int64_t g) -> int {
@@ -159,9 +218,11 @@ void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vec
       if (it == B + nB || *it != g) return -1;
       return nI + int(it - B);
     };
-    std::vector<Z> F(size_t(nf) * nf, Z{0, 0});
+    std::vector<Z>& F = front[t];
+    F.assign(size_t(nf) * nf, Z{0, 0});
     for (int64_t q : bucket[t]) {
-      const int a = pos(kidx[q] % nK), b = pos(kidx[q] / nK);
+      const int64_t col = kidx[q] / nK;
+      const int a = pos(kidx[q] - col * nK), b = pos(col);
       if (a < 0 || b < 0) {
         std::lock_guard<std::mutex> g(err_mu);
         err = "coarse entry outside its nested-dissection front";
@@ -201,31 +262,35 @@ void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vec
       err = "singular diagonal block in the nested-dissection coarse factor";
       return;
     }
-    if (nB == 0) return;
-    Z* L = fac + f.mL[t];
-    zgemm_acc(nB, nI, nI, 1.0, F.data() + size_t(nI) * nf, nf, D, nI, L, nI);
-    Z* Lt = fac + f.mLt[t];
-    for (int b = 0; b < nB; ++b)
-      for (int i = 0; i < nI; ++i) Lt[size_t(i) * nB + b] = L[size_t(b) * nI + i];
-    std::vector<Z> S(size_t(nB) * nB);
-    for (int a = 0; a < nB; ++a)
-      for (int b = 0; b < nB; ++b) S[size_t(a) * nB + b] = F[size_t(nI + a) * nf + nI + b];
-    zgemm_acc(nB, nB, nI, -1.0, L, nI, F.data() + nI, nf, S.data(), nB);
-    schur[t].swap(S);
+    schur[t].resize(size_t(nB) * nB);
   };
-  const int nthreads = int(std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
+  // rows b0 .. b1 - 1 of L and of S = F_BB - L F_IB
+  auto eliminate = [&](int t, int b0, int b1) {
+    const int nI = nI_of(t), nB = nB_of(t), nf = nI + nB, nb = b1 - b0;
+    const Z* F = front[t].data();
+    Z* L = fac + f.mL[t] + size_t(b0) * nI;
+    std::fill(L, L + size_t(nb) * nI, Z{0, 0});
+    zgemm_acc(nb, nI, nI, 1.0, F + size_t(nI + b0) * nf, nf, fac + f.mD[t], nI, L, nI);
+    Z* Lt = fac + f.mLt[t] + b0;
+    for (int i = 0; i < nI; ++i)
+      for (int b = 0; b < nb; ++b) Lt[size_t(i) * nB + b] = L[size_t(b) * nI + i];
+    Z* S = schur[t].data() + size_t(b0) * nB;
+    for (int b = 0; b < nb; ++b) std::copy_n(F + size_t(nI + b0 + b) * nf + nI, nB, S + size_t(b) * nB);
+    zgemm_acc(nb, nB, nI, -1.0, L, nI, F + nI, nf, S, nB);
+  };
+  // depth by depth: a thread per node, then a thread per 16 rows below a node's block,
+  // so that the few large fronts near the root keep the team busy
+  constexpr int ND_ROWS = 16;
+  struct Rows { int t, b0, b1; };
   for (int dpt = maxd; dpt >= 0; --dpt) {
     const std::vector<int>& lv = by_depth[dpt];
-    std::atomic<int> next(0);
-    auto worker = [&]() {
-      for (int q = next++; q < int(lv.size()); q = next++) factor_node(lv[q]);
-    };
-    const int nt = std::min<int>(nthreads, int(lv.size()));
-    std::vector<std::thread> pool;
-    for (int k = 1; k < nt; ++k) pool.emplace_back(worker);
-    worker();
-    for (auto& th : pool) th.join();
+    team.run(int(lv.size()), [&](int q) { assemble(lv[q]); });
     if (!err.empty()) fail(HDP_E_COARSE, err);
+    std::vector<Rows> rows;
+    for (int t : lv)
+      for (int b = 0; b < nB_of(t); b += ND_ROWS) rows.push_back(Rows{t, b, std::min(b + ND_ROWS, nB_of(t))});
+    team.run(int(rows.size()), [&](int q) { eliminate(rows[q].t, rows[q].b0, rows[q].b1); });
+    for (int t : lv) std::vector<Z>().swap(front[t]);
   }
   // where each update row goes in the parent's front: slot k of the parent's rows
   // for child k (interior rows first, then update rows from nK on)

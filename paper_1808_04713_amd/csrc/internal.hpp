@@ -4,6 +4,8 @@
 
 #include <cstdint>
 #include <map>
+#include <memory>
+#include <new>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -37,7 +39,6 @@ struct ElemClass {
   std::vector<int> Gam;        // dual-touched type-1 edge modes, slot order
   MatC Ex, Ey;                 // generalised eigenvectors, E^T M~ E = I
   std::vector<cd> Dg;          // (hy/2) lx_i + (hx/2) ly_j, index i + n j
-  MatC G;                      // A~^-1 E_R           (n^2 x nr)
   MatC Kc;                     // (E_R^T A~^-1 E_R)^-1 (nr x nr)
   MatC Op1;                    // [D_c ; Phi_c^T]      ((m+nr) x m)
   MatC Phi;                    // Phi_c = -A_11^-1 A_1R = G_Gam Kc on the slots (m x nr)
@@ -433,9 +434,11 @@ void scratch_init(int device);
 void* scratch_ptr(int device);
 
 // setup.cpp
-void build_host(Handle& h, const hdp_mesh* mesh, const hdp_problem* prob);
+// (host set-up; without a team each call makes its own)
+class Team;
+void build_host(Handle& h, const hdp_mesh* mesh, const hdp_problem* prob, Team* team = nullptr);
 // Coarse matrix K = sum_e T_e^T Kc_e T_e as sorted COO (key = row + nK * col).
-void coarse_coo(const Handle& h, std::vector<int64_t>& kidx, std::vector<double2>& kval);
+void coarse_coo(const Handle& h, std::vector<int64_t>& kidx, std::vector<double2>& kval, Team* team = nullptr);
 double coarse_band_bytes(int nK, const std::vector<int64_t>& kidx);
 
 // coarse_nd.cpp: the nested-dissection factor assembled on the host.  Per node
@@ -444,7 +447,20 @@ double coarse_band_bytes(int nK, const std::vector<int64_t>& kidx);
 // push2 names each row's slot in the parent's front.  Per tree depth: the tasks of
 // the device sweeps.
 struct NDHost {
-  std::vector<double2> fac;
+  // the factor's entries: left unset (a vector would write 94 MB of zeros, a page
+  // fault every 4 KB, ahead of the threads that fill them)
+  struct Entries {
+    struct Free { void operator()(double2* q) const { ::operator delete(q); } };
+    std::unique_ptr<double2, Free> p;
+    size_t n = 0;
+    void resize(size_t count) {
+      p.reset(static_cast<double2*>(::operator new(count * sizeof(double2))));
+      n = count;
+    }
+    double2* data() { return p.get(); }
+    const double2* data() const { return p.get(); }
+    size_t size() const { return n; }
+  } fac;
   std::vector<int64_t> uoff, mD, mL, mLt;
   int64_t urows = 0;
   std::vector<int> push2;     // slot row of each update row
@@ -453,7 +469,8 @@ struct NDHost {
   int64_t part_tasks = 0;     // largest split level (tiles x splits)
   double flops_per_col = 0;   // 8 (nI^2 + 2 nB nI) summed over the nodes
 };
-void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vector<double2>& kval, NDHost& f);
+void nd_factor(const Handle& h, const std::vector<int64_t>& kidx, const std::vector<double2>& kval, NDHost& f,
+               Team* team = nullptr);
 // every device block of the handle back through its allocator (or hipFree)
 void release_allocations(Handle& h);
 // the tile tasks alone (levels, tRf/tRb, part_tasks) for a split target;

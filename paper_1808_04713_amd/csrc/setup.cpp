@@ -4,19 +4,16 @@
 // Sec. 2.3.2 (Algorithm 1), Sec. 2.3.3 (block structure and preconditioner).
 #include <algorithm>
 #include <array>
-#include <atomic>
 #include <chrono>
 #include <cmath>
-#include <exception>
 #include <functional>
 #include <map>
-#include <mutex>
 #include <set>
-#include <thread>
 #include <tuple>
 
 #include "basis.hpp"
 #include "internal.hpp"
+#include "team.hpp"
 
 namespace hdp {
 
@@ -108,7 +105,43 @@ void gen_eig(const MatC& A, const MatD& M, MatC& E, std::vector<cd>& lam) {
     fail(HDP_E_RESONANCE, "separable eigenbasis is ill-conditioned (defective 1-D pencil)");
 }
 
-void build_class(ElemClass& C, double k) {
+// S_b: Schur complement of the Laplace-only element matrix A~_L onto the side modes
+// (interior eliminated).  It depends on degree, size and layers alone, so classes that
+// differ in eps_r, boundary or coarse order share it: the interior solve, (p - 1)^2
+// unknowns, was three quarters of a class.
+MatC laplace_sides(const ElemClass& C, double k) {
+  const int n = C.n, n2 = n * n;
+  const MatD Mt = mass_vertex(n), Kt = stiffness_vertex(n);
+  const cd sx(1.0, C.sigx / k), sy(1.0, C.sigy / k);
+  const cd axx = sy / sx, ayy = sx / sy;
+  std::vector<int> bmodes, imodes;
+  for (int md = 0; md < n2; ++md) {
+    int ix = md % n, iy = md / n;
+    if (ix >= 2 && iy >= 2) imodes.push_back(md);
+    else bmodes.push_back(md);
+  }
+  auto AL = [&](int a, int b) {
+    int i1 = a % n, i2 = a / n, j1 = b % n, j2 = b / n;
+    return axx * (C.hy / C.hx) * Mt(i2, j2) * Kt(i1, j1) + ayy * (C.hx / C.hy) * Kt(i2, j2) * Mt(i1, j1);
+  };
+  int nb = int(bmodes.size()), ni = int(imodes.size());
+  MatC Abb(nb, nb), Abi(nb, ni), Aii(ni, ni);
+  for (int b = 0; b < nb; ++b)
+    for (int a = 0; a < nb; ++a) Abb(a, b) = AL(bmodes[a], bmodes[b]);
+  for (int b = 0; b < ni; ++b)
+    for (int a = 0; a < nb; ++a) Abi(a, b) = AL(bmodes[a], imodes[b]);
+  for (int b = 0; b < ni; ++b)
+    for (int a = 0; a < ni; ++a) Aii(a, b) = AL(imodes[a], imodes[b]);
+  MatC Sb = Abb;
+  if (ni > 0) {
+    MatC X = solve(Aii, transpose(Abi));
+    MatC AX = matmul(Abi, X);
+    for (size_t i = 0; i < Sb.a.size(); ++i) Sb.a[i] -= AX.a[i];
+  }
+  return Sb;
+}
+
+void build_class(ElemClass& C, double k, const MatC& Sb) {
   int n = C.n, p = C.p;
   MatD Mt = mass_vertex(n), Kt = stiffness_vertex(n);
   cd gamma(0.0, -k);
@@ -166,14 +199,14 @@ void build_class(ElemClass& C, double k) {
     Y.a[mode] = 1.0;
     return fdm_host(C, Y);
   };
-  C.G = MatC(n2, nr);
+  MatC G(n2, nr);   // A~^-1 E_R
   for (int r = 0; r < nr; ++r) {
     MatC X = unit_solve(C.R[r]);
-    for (int i = 0; i < n2; ++i) C.G(i, r) = X.a[i];
+    for (int i = 0; i < n2; ++i) G(i, r) = X.a[i];
   }
   MatC Ccap(nr, nr);
   for (int b = 0; b < nr; ++b)
-    for (int a = 0; a < nr; ++a) Ccap(a, b) = C.G(C.R[a], b);
+    for (int a = 0; a < nr; ++a) Ccap(a, b) = G(C.R[a], b);
   // C_cap is the coarse block of A~^-1; its inverse is the element coarse matrix
   try {
     C.Kc = inverse(Ccap);
@@ -184,7 +217,7 @@ void build_class(ElemClass& C, double k) {
   for (int g = 0; g < m; ++g) {
     MatC X = unit_solve(C.Gam[g]);
     for (int a = 0; a < m; ++a) H(a, g) = X.a[C.Gam[a]];
-    for (int r = 0; r < nr; ++r) GG(g, r) = C.G(C.Gam[g], r);
+    for (int r = 0; r < nr; ++r) GG(g, r) = G(C.Gam[g], r);
   }
   // Phi = -A_11^-1 A_1R on the dual slots; by the block inverse of A~ this is
   // G_Gam Kc (the type-1 block of A~^-1 E_R times the coarse Schur complement)
@@ -197,34 +230,13 @@ void build_class(ElemClass& C, double k) {
     for (int a = 0; a < m; ++a) C.Op1(a, b) = Dc(a, b);
     for (int r = 0; r < nr; ++r) C.Op1(m + r, b) = C.Phi(b, r);
   }
-  // Laplace-only blocks of the preconditioner (Sec. 2.3.3).  S_b: Schur
-  // complement of A~_L onto the side modes (interior eliminated); its block on
-  // the dual slots is the Dirichlet block Se, and eliminating the remaining
-  // type-1 side modes from it leaves the element's Laplace coarse matrix KL.
-  std::vector<int> bmodes, imodes;
-  for (int md = 0; md < n2; ++md) {
-    int ix = md % n, iy = md / n;
-    if (ix >= 2 && iy >= 2) imodes.push_back(md);
-    else bmodes.push_back(md);
-  }
-  auto AL = [&](int a, int b) {
-    int i1 = a % n, i2 = a / n, j1 = b % n, j2 = b / n;
-    return axx * (C.hy / C.hx) * Mt(i2, j2) * Kt(i1, j1) + ayy * (C.hx / C.hy) * Kt(i2, j2) * Mt(i1, j1);
-  };
-  int nb = int(bmodes.size()), ni = int(imodes.size());
-  MatC Abb(nb, nb), Abi(nb, ni), Aii(ni, ni);
-  for (int b = 0; b < nb; ++b)
-    for (int a = 0; a < nb; ++a) Abb(a, b) = AL(bmodes[a], bmodes[b]);
-  for (int b = 0; b < ni; ++b)
-    for (int a = 0; a < nb; ++a) Abi(a, b) = AL(bmodes[a], imodes[b]);
-  for (int b = 0; b < ni; ++b)
-    for (int a = 0; a < ni; ++a) Aii(a, b) = AL(imodes[a], imodes[b]);
-  MatC Sb = Abb;
-  if (ni > 0) {
-    MatC X = solve(Aii, transpose(Abi));
-    MatC AX = matmul(Abi, X);
-    for (size_t i = 0; i < Sb.a.size(); ++i) Sb.a[i] -= AX.a[i];
-  }
+  // Laplace-only blocks of the preconditioner (Sec. 2.3.3): the block of S_b on the
+  // dual slots is the Dirichlet block Se, and eliminating the remaining type-1 side
+  // modes from it leaves the element's Laplace coarse matrix KL.
+  std::vector<int> bmodes;
+  for (int md = 0; md < n2; ++md)
+    if (md % n < 2 || md / n < 2) bmodes.push_back(md);
+  const int nb = int(bmodes.size());
   std::vector<int> bpos(n2, -1), inR(n2, 0);
   for (int a = 0; a < nb; ++a) bpos[bmodes[a]] = a;
   for (int r : C.R) inR[r] = 1;
@@ -338,24 +350,27 @@ void order_coarse_levels(Handle& h) {
 }
 
 // Coarse unknowns that share an element (the sparsity of K), as sorted lists.
-static std::vector<std::vector<int>> coarse_adjacency(const Handle& h) {
-  std::vector<std::vector<int>> elem_dofs(h.E);
+static std::vector<std::vector<int>> coarse_adjacency(const Handle& h, Team& team) {
+  std::vector<std::vector<int>> elem_dofs(h.E), elems(h.nK);
   for (int e = 0; e < h.E; ++e) {
     auto& v = elem_dofs[e];
     for (int i = h.cm_off[e]; i < h.cm_off[e + 1]; ++i)
       for (int t = h.t_ptr[i]; t < h.t_ptr[i + 1]; ++t) v.push_back(h.t_dof[t]);
     std::sort(v.begin(), v.end());
     v.erase(std::unique(v.begin(), v.end()), v.end());
+    for (int a : v) elems[a].push_back(e);
   }
   std::vector<std::vector<int>> adj(h.nK);
-  for (int e = 0; e < h.E; ++e)
-    for (int a : elem_dofs[e])
-      for (int b : elem_dofs[e])
-        if (a != b) adj[a].push_back(b);
-  for (auto& v : adj) {
-    std::sort(v.begin(), v.end());
-    v.erase(std::unique(v.begin(), v.end()), v.end());
-  }
+  team.ranges(h.nK, 256, [&](int64_t a0, int64_t a1) {
+    for (int64_t a = a0; a < a1; ++a) {
+      auto& v = adj[a];
+      for (int e : elems[a])
+        for (int b : elem_dofs[e])
+          if (b != a) v.push_back(b);
+      std::sort(v.begin(), v.end());
+      v.erase(std::unique(v.begin(), v.end()), v.end());
+    }
+  });
   return adj;
 }
 
@@ -368,12 +383,13 @@ static std::vector<std::vector<int>> coarse_adjacency(const Handle& h) {
 // Nodes are numbered in postorder (children before parents); the unknowns a
 // node owns are consecutive in the new numbering, and its boundary lists the
 // later (ancestor) unknowns its subtree is coupled to after elimination.
-void order_coarse_nd(Handle& h, size_t leaf) {
+void order_coarse_nd(Handle& h, size_t leaf, Team& team) {
   const int nK = h.nK;
-  const auto adj = coarse_adjacency(h);
+  const auto adj = coarse_adjacency(h, team);
   struct Node { std::vector<int> own; int child[2] = {-1, -1}; int depth = 0; };
   std::vector<Node> nodes;
-  std::vector<int> side(nK, -1);
+  std::vector<char> in(nK, 0);        // the set being cut
+  std::vector<double> nearest(nK);    // smallest coordinate among an unknown's neighbours in it
   std::function<int(std::vector<int>&, int)> build = [&](std::vector<int>& S, int depth) -> int {
     const int id = int(nodes.size());
     nodes.emplace_back();
@@ -403,18 +419,23 @@ void order_coarse_nd(Handle& h, size_t leaf) {
       // the vertex lines nearest to the median of the set, a few on each side
       const double med = cs[cs.size() / 2];
       const size_t at = size_t(std::lower_bound(lines.begin(), lines.end(), med) - lines.begin());
+      for (int u : S) in[u] = 1;
+      team.ranges(int64_t(S.size()), 512, [&](int64_t q0, int64_t q1) {
+        for (int64_t q = q0; q < q1; ++q) {
+          double m = 1e300;
+          for (int v : adj[S[q]])
+            if (in[v]) m = std::min(m, c[v]);
+          nearest[S[q]] = m;
+        }
+      });
+      for (int u : S) in[u] = 0;
       for (size_t q = at >= 3 ? at - 3 : 0; q < std::min(lines.size(), at + 4); ++q) {
         const double m = lines[q];
-        for (int u : S) side[u] = c[u] < m ? 0 : 1;
         std::vector<int> sep, a, b;
         for (int u : S) {
-          if (side[u] == 0) { a.push_back(u); continue; }
-          bool touch = false;
-          for (int v : adj[u])
-            if (side[v] == 0) { touch = true; break; }
-          (touch ? sep : b).push_back(u);
+          if (c[u] < m) a.push_back(u);
+          else (nearest[u] < m ? sep : b).push_back(u);   // the far side's unknowns next to the near side
         }
-        for (int u : S) side[u] = -1;
         if (a.empty() || b.empty()) continue;
         const double imb = std::abs(double(a.size()) - double(b.size())) / double(S.size());
         const double score = double(sep.size()) * (1.0 + 2.0 * imb);
@@ -606,28 +627,60 @@ void build_hanging_blocks(Handle& h) {
 
 }  // namespace
 
-void coarse_coo(const Handle& h, std::vector<int64_t>& kidx, std::vector<double2>& kval) {
-  std::vector<std::pair<int64_t, cd>> coo;
-  for (int e = 0; e < h.E; ++e) {
-    const ElemClass& C = h.classes[h.cls[e]];
-    const int co = h.cm_off[e];
-    for (int b = 0; b < C.nr; ++b)
-      for (int a = 0; a < C.nr; ++a) {
-        cd kab = C.Kc(a, b);
-        for (int t = h.t_ptr[co + a]; t < h.t_ptr[co + a + 1]; ++t)
-          for (int u = h.t_ptr[co + b]; u < h.t_ptr[co + b + 1]; ++u)
-            coo.push_back({h.t_dof[t] + int64_t(h.nK) * h.t_dof[u], h.t_coef[t] * kab * h.t_coef[u]});
+void coarse_coo(const Handle& h, std::vector<int64_t>& kidx, std::vector<double2>& kval, Team* shared) {
+  TeamOr threads(shared);
+  Team& team = threads.team;
+  // column by column, each from the coarse modes that expand into it (elements in
+  // order): no list of all element entries, three times as long, to sort
+  struct Use { int e, b; double coef; };
+  std::vector<int> ptr(size_t(h.nK) + 1, 0);
+  for (int d : h.t_dof) ptr[d + 1]++;
+  for (int d = 0; d < h.nK; ++d) ptr[d + 1] += ptr[d];
+  std::vector<Use> use(h.t_dof.size());
+  std::vector<int> at(ptr.begin(), ptr.end() - 1);
+  for (int e = 0; e < h.E; ++e)
+    for (int i = h.cm_off[e]; i < h.cm_off[e + 1]; ++i)
+      for (int t = h.t_ptr[i]; t < h.t_ptr[i + 1]; ++t)
+        use[at[h.t_dof[t]]++] = Use{e, i - h.cm_off[e], h.t_coef[t]};
+  const int64_t grain = 256, parts = (h.nK + grain - 1) / grain;
+  std::vector<std::vector<int64_t>> idx(parts);
+  std::vector<std::vector<double2>> val(parts);
+  team.run(int(parts), [&](int q) {
+    std::vector<int> slot(h.nK, -1), rows;
+    std::vector<cd> sum;
+    for (int c = int(q * grain); c < std::min<int64_t>(h.nK, (q + 1) * grain); ++c) {
+      rows.clear();
+      sum.clear();
+      for (int u = ptr[c]; u < ptr[c + 1]; ++u) {
+        const ElemClass& C = h.classes[h.cls[use[u].e]];
+        const int co = h.cm_off[use[u].e];
+        for (int a = 0; a < C.nr; ++a) {
+          const cd kab = C.Kc(a, use[u].b);
+          for (int t = h.t_ptr[co + a]; t < h.t_ptr[co + a + 1]; ++t) {
+            const int r = h.t_dof[t];
+            if (slot[r] < 0) {
+              slot[r] = int(rows.size());
+              rows.push_back(r);
+              sum.push_back(0.0);
+            }
+            sum[slot[r]] += h.t_coef[t] * kab * use[u].coef;
+          }
+        }
       }
-  }
-  std::sort(coo.begin(), coo.end(), [](auto& x, auto& y) { return x.first < y.first; });
+      std::sort(rows.begin(), rows.end());
+      for (int r : rows) {
+        const cd s = sum[slot[r]];
+        idx[q].push_back(r + int64_t(h.nK) * c);
+        val[q].push_back(make_double2(s.real(), s.imag()));
+        slot[r] = -1;
+      }
+    }
+  });
   kidx.clear();
   kval.clear();
-  for (size_t t = 0; t < coo.size();) {
-    int64_t key = coo[t].first;
-    cd s = 0;
-    while (t < coo.size() && coo[t].first == key) s += coo[t++].second;
-    kidx.push_back(key);
-    kval.push_back(make_double2(s.real(), s.imag()));
+  for (int64_t q = 0; q < parts; ++q) {
+    kidx.insert(kidx.end(), idx[q].begin(), idx[q].end());
+    kval.insert(kval.end(), val[q].begin(), val[q].end());
   }
 }
 
@@ -637,8 +690,10 @@ void coarse_coo(const Handle& h, std::vector<int64_t>& kidx, std::vector<double2
 double coarse_band_bytes(int nK, const std::vector<int64_t>& kidx) {
   std::vector<int> first(static_cast<size_t>(nK));
   for (int i = 0; i < nK; ++i) first[size_t(i)] = i;
+  int64_t c = 0;
   for (int64_t key : kidx) {
-    const int64_t r = key % nK, c = key / nK;
+    while (key >= (c + 1) * nK) ++c;
+    const int64_t r = key - c * nK;
     first[size_t(r)] = std::min(first[size_t(r)], int(c));
   }
   double env = 0;
@@ -646,7 +701,9 @@ double coarse_band_bytes(int nK, const std::vector<int64_t>& kidx) {
   return 16.0 * (2.0 * env - double(nK));
 }
 
-void build_host(Handle& h, const hdp_mesh* mesh, const hdp_problem* prob) {
+void build_host(Handle& h, const hdp_mesh* mesh, const hdp_problem* prob, Team* shared) {
+  TeamOr threads(shared);
+  Team& team = threads.team;
   if (!mesh || !prob || !mesh->leaf || !mesh->degree) fail(HDP_E_ARG, "null mesh or problem");
   int E = mesh->n_leaves;
   if (E <= 0 || mesh->base_nx <= 0 || mesh->base_ny <= 0) fail(HDP_E_ARG, "empty mesh");
@@ -881,29 +938,20 @@ void build_host(Handle& h, const hdp_mesh* mesh, const hdp_problem* prob) {
     h.cls[e] = it->second;
     h.classes[it->second].elems.push_back(e);
   }
-  // classes are independent: build them on host threads (an error in any
-  // class is rethrown after all threads have joined)
+  // classes are independent: built on the team's threads
   {
     const auto tc = std::chrono::steady_clock::now();
-    const int nthreads = int(std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
-    std::atomic<int> next{0};
-    std::exception_ptr err;
-    std::mutex err_mu;
-    auto work = [&] {
-      for (int c = next++; c < int(h.classes.size()); c = next++) {
-        try {
-          build_class(h.classes[c], h.k);
-        } catch (...) {
-          std::lock_guard<std::mutex> lock(err_mu);
-          if (!err) err = std::current_exception();
-        }
-      }
-    };
-    std::vector<std::thread> pool;
-    for (int t = 1; t < std::min<int>(nthreads, int(h.classes.size())); ++t) pool.emplace_back(work);
-    work();
-    for (auto& t : pool) t.join();
-    if (err) std::rethrow_exception(err);
+    std::map<std::tuple<int, double, double, double, double>, int> sides;   // Laplace blocks, by what they depend on
+    std::vector<int> side_of, first;
+    for (int c = 0; c < int(h.classes.size()); ++c) {
+      const ElemClass& C = h.classes[c];
+      const auto it = sides.emplace(std::make_tuple(C.n, C.hx, C.hy, C.sigx, C.sigy), int(first.size()));
+      if (it.second) first.push_back(c);
+      side_of.push_back(it.first->second);
+    }
+    std::vector<MatC> Sb(first.size());
+    team.run(int(first.size()), [&](int q) { Sb[q] = laplace_sides(h.classes[first[q]], h.k); });
+    team.run(int(h.classes.size()), [&](int c) { build_class(h.classes[c], h.k, Sb[side_of[c]]); });
     h.setup_classes_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - tc).count();
   }
   h.min_margin = 1;
@@ -1143,7 +1191,7 @@ void build_host(Handle& h, const hdp_mesh* mesh, const hdp_problem* prob) {
   // 162 us per coarse solve of the 80x80 layered scatterer)
   const bool requested = h.coarse_mode >= 0;
   if (h.coarse_mode < 0) h.coarse_mode = h.nK > 6000 ? 2 : 0;
-  if (h.coarse_mode == 2) order_coarse_nd(h, requested ? 32 : (h.max_rhs >= 9 ? 192 : 96));
+  if (h.coarse_mode == 2) order_coarse_nd(h, requested ? 32 : (h.max_rhs >= 9 ? 192 : 96), team);
   else order_coarse_levels(h);
   // algorithmic work counts
   for (auto& C : h.classes) {
