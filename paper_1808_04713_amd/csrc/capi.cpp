@@ -515,6 +515,9 @@ void build_device(Handle& h, Team& team) {
     std::vector<int> blk(h.nh);
     for (size_t b = 0; b + 1 < h.hb_off.size(); ++b)
       for (int i = h.hb_off[b]; i < h.hb_off[b + 1]; ++i) blk[i] = int(b);
+    std::vector<int> of(h.nlam, -1);   // dual row -> its number among the blocks' rows
+    for (int i = 0; i < h.nh; ++i) of[h.hb_rows[i]] = i;
+    d.hb_of = upload(h, of);
     d.hb_off = upload(h, h.hb_off);
     d.hb_rows = upload(h, h.hb_rows);
     d.hb_blk = upload(h, blk);
@@ -973,8 +976,7 @@ void apply_P_ws(Handle& h, const double2* v, double2* u, int R, int prec, const 
     // P^-1 = X^-1 Y X^-1: X is diagonal except for dense blocks on the hanging
     // rows, whose scale factor is 1 in row_xinv; first s = X^-1 v there
     Timed t(h, KF_HBLOCK, hb_bytes + 2 * nh * c + nl * 2 * c, 2.0 * h.hb_xinv.size() * 2 * R);
-    launch_axpby(v, v, w.pv, int64_t(h.nlam) * R, 1.0, 0.0, s);   // a copy by kernel (capturable)
-    launch_hblock(h, false, v, true, nullptr, w.pv, true, R, s);
+    launch_hcopy(h, v, w.pv, R, s);
     v = w.pv;
   }
   if (prec != HDP_FP64) {
@@ -986,13 +988,19 @@ void apply_P_ws(Handle& h, const double2* v, double2* u, int R, int prec, const 
     if (prec == HDP_FP64) launch_slot_apply<double2>(h, 1, v, w.slot, nullptr, R, s);
     else launch_slot_apply<float2>(h, 1, w.vf, w.slot_f, nullptr, R, s);
   }
+  if (h.nh > 0) {
+    // hanging rows: u = X^-1 (C_1 S C_1^T s + Y_2 s)
+    Timed t(h, KF_HBLOCK, nsl * cw + nl * c + 2 * hb_bytes + 2 * nh * c, 2.0 * 2 * h.hb_xinv.size() * 2 * R);
+    if (prec == HDP_FP64 ? launch_hgather<double2>(h, w.slot, w.pv, u, R, s)
+                         : launch_hgather<float2>(h, w.slot_f, w.pv, u, R, s))
+      return;
+  }
   {
     Timed t(h, KF_ROWGATHER, nsl * cw + nl * c, 0);
     if (prec == HDP_FP64) launch_rowgather<double2>(h, w.slot, false, true, nullptr, u, R, s);
     else launch_rowgather<float2>(h, w.slot_f, false, true, nullptr, u, R, s);
   }
   if (h.nh > 0) {
-    // hanging rows: u = X^-1 (C_1 S C_1^T s + Y_2 s)
     Timed t(h, KF_HBLOCK, 2 * hb_bytes + 6 * nh * c, 2.0 * 2 * h.hb_xinv.size() * 2 * R);
     launch_hblock(h, true, w.pv, true, u, w.hb_tmp, false, R, s);
     launch_hblock(h, false, w.hb_tmp, false, nullptr, u, true, R, s);

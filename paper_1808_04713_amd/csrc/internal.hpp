@@ -278,7 +278,7 @@ struct Handle {
     double* id_coef = nullptr;
     int *c2_ptr = nullptr, *c2_dof = nullptr, *c2t_ptr = nullptr, *c2t_row = nullptr;
     double *c2_coef = nullptr, *c2t_coef = nullptr;
-    int *hb_off = nullptr, *hb_rows = nullptr, *hb_blk = nullptr;
+    int *hb_off = nullptr, *hb_rows = nullptr, *hb_blk = nullptr, *hb_of = nullptr;
     int64_t* hb_moff = nullptr;
     double *hb_xinv = nullptr, *hb_y2 = nullptr;
     double2 *hb_tmp = nullptr, *fv = nullptr, *pv = nullptr;

@@ -580,16 +580,14 @@ __global__ void __launch_bounds__(NT) k_slot_coarse_sym(const SlotBlock* __restr
   }
 }
 
-// u[row] = scale_row * (sum coef * src[pos(slot)] + sum_{C_2} coef * w[dof])
+// scale_row * (sum coef * src[pos(slot)] + sum_{C_2} coef * w[dof])
 template <class T2>
-__global__ void k_rowgather(int nlam, const int* __restrict__ row_slot, const double* __restrict__ row_coef,
-                            const double* __restrict__ row_xinv, const int64_t* __restrict__ slot_pos,
-                            const T2* __restrict__ src, const int* __restrict__ c2_ptr,
-                            const int* __restrict__ c2_dof, const double* __restrict__ c2_coef,
-                            const double2* __restrict__ w, double2* __restrict__ u, int R) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)nlam * R) return;
-  int row = int(idx / R), r = int(idx - (int64_t)row * R);
+__device__ __forceinline__ double2 row_value(int row, int r, int R, const int* __restrict__ row_slot,
+                                             const double* __restrict__ row_coef,
+                                             const double* __restrict__ row_xinv, const int64_t* __restrict__ slot_pos,
+                                             const T2* __restrict__ src, const int* __restrict__ c2_ptr,
+                                             const int* __restrict__ c2_dof, const double* __restrict__ c2_coef,
+                                             const double2* __restrict__ w) {
   double ax = 0, ay = 0;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
@@ -611,7 +609,19 @@ __global__ void k_rowgather(int nlam, const int* __restrict__ row_slot, const do
     ax *= row_xinv[row];
     ay *= row_xinv[row];
   }
-  u[idx] = make_double2(ax, ay);
+  return make_double2(ax, ay);
+}
+
+template <class T2>
+__global__ void k_rowgather(int nlam, const int* __restrict__ row_slot, const double* __restrict__ row_coef,
+                            const double* __restrict__ row_xinv, const int64_t* __restrict__ slot_pos,
+                            const T2* __restrict__ src, const int* __restrict__ c2_ptr,
+                            const int* __restrict__ c2_dof, const double* __restrict__ c2_coef,
+                            const double2* __restrict__ w, double2* __restrict__ u, int R) {
+  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (int64_t)nlam * R) return;
+  int row = int(idx / R), r = int(idx - (int64_t)row * R);
+  u[idx] = row_value<T2>(row, r, R, row_slot, row_coef, row_xinv, slot_pos, src, c2_ptr, c2_dof, c2_coef, w);
 }
 
 // The same at one right-hand side with one wave per coarse unknown, for meshes
@@ -693,8 +703,98 @@ __global__ void k_assemble(int nK, const int* __restrict__ ptr, const int* __res
   g[idx] = make_double2(ax, ay);
 }
 
-// Dense blocks over the dual rows that C_2 couples (hanging edges): one
-// wavefront per block row i, RHS in chunks of 8.
+// Dense blocks over the dual rows that C_2 couples (hanging edges).  They hold a few
+// rows of the many (4 of 9,698 on the refined disk), so a launch of theirs is the
+// chain of its loads: X^-1 v shares the launch that copies the other rows, and
+// X^-1 (u + Y_2 s) the one that gathers them, in workgroups of their own.
+// X^-1 Y X^-1 of the disk at 12 columns: 73 us a call with six launches, of it 3 + 8 +
+// 4 + 9 + 6 for these steps.
+
+// sum_j M[il, j] in(j) for one block row, on a wave: 64 / RB lanes per column split the
+// sum (RB columns, a power of two); valid in the first RB lanes
+template <class F>
+__device__ __forceinline__ double2 hblock_row(const double* __restrict__ Mb, int nb, int il, int RB, F&& in) {
+  const int lane = threadIdx.x & 63, rl = lane & (RB - 1);
+  double sx = 0, sy = 0;
+#pragma unroll 2
+  for (int j = lane / RB; j < nb; j += 64 / RB) {
+    const double m = Mb[il + (int64_t)nb * j];
+    const double2 v = in(j, rl);
+    sx += m * v.x;
+    sy += m * v.y;
+  }
+  for (int off = 32; off >= RB; off >>= 1) {
+    sx += __shfl_xor(sx, off, 64);
+    sy += __shfl_xor(sy, off, 64);
+  }
+  return make_double2(sx, sy);
+}
+
+// y = v, X^-1 v on the blocks' rows (hb_of: the row's number among them, or -1):
+// workgroups of entries, then, from block `copies` on, a wave per block row and HB_R columns
+constexpr int HB_R = 16;
+
+__global__ void __launch_bounds__(NT) k_hcopy(int64_t count, int copies, const int* __restrict__ hb_of, int nh,
+                                              const int* __restrict__ blk, const int* __restrict__ off,
+                                              const int* __restrict__ rows, const int64_t* __restrict__ moff,
+                                              const double* __restrict__ M, const double2* __restrict__ v,
+                                              double2* __restrict__ y, int R, int RB) {
+  if ((int)blockIdx.x < copies) {
+    const int64_t idx = (int64_t)blockIdx.x * NT + threadIdx.x;
+    if (idx < count && hb_of[idx / R] < 0) y[idx] = v[idx];
+    return;
+  }
+  const int nch = (R + RB - 1) / RB;
+  const int t = ((int)blockIdx.x - copies) * (NT / 64) + (threadIdx.x >> 6), i = t / nch, r0 = (t - i * nch) * RB;
+  if (i >= nh) return;
+  const int b = blk[i], o = off[b], nb = off[b + 1] - o;
+  const double2 s = hblock_row(M + moff[b], nb, i - o, RB, [&](int j, int rl) {
+    return r0 + rl < R ? v[(int64_t)rows[o + j] * R + r0 + rl] : make_double2(0, 0);
+  });
+  const int lane = threadIdx.x & 63;
+  if (lane < RB && r0 + lane < R) y[(int64_t)rows[i] * R + r0 + lane] = s;
+}
+
+// u = the row gather of src; on the blocks' rows X^-1 (that + Y_2 s): workgroups of
+// entries, then one per block and RB columns (the inner sums in shared memory)
+template <class T2>
+__global__ void __launch_bounds__(NT) k_hgather(int64_t count, int copies, const int* __restrict__ hb_of,
+                                                const int* __restrict__ row_slot, const double* __restrict__ row_coef,
+                                                const double* __restrict__ row_xinv, const T2* __restrict__ src,
+                                                const int* __restrict__ off, const int* __restrict__ rows,
+                                                const int64_t* __restrict__ moff, const double* __restrict__ Xi,
+                                                const double* __restrict__ Y2, const double2* __restrict__ sv,
+                                                double2* __restrict__ u, int R, int RB) {
+  extern __shared__ double2 hbt[];   // [nb][RB]
+  auto gather = [&](int row, int r) {
+    return row_value<T2>(row, r, R, row_slot, row_coef, row_xinv, nullptr, src, nullptr, nullptr, nullptr, nullptr);
+  };
+  if ((int)blockIdx.x < copies) {
+    const int64_t idx = (int64_t)blockIdx.x * NT + threadIdx.x;
+    if (idx >= count) return;
+    const int row = int(idx / R);
+    if (hb_of[row] < 0) u[idx] = gather(row, int(idx - (int64_t)row * R));
+    return;
+  }
+  const int nch = (R + RB - 1) / RB, q = (int)blockIdx.x - copies;
+  const int b = q / nch, r0 = (q - b * nch) * RB, o = off[b], nb = off[b + 1] - o;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, r = r0 + lane;
+  const bool mine = lane < RB && r < R;
+  for (int i = wv; i < nb; i += NT / 64) {
+    const double2 a = mine ? gather(rows[o + i], r) : make_double2(0, 0);
+    const double2 s = hblock_row(Y2 + moff[b], nb, i, RB, [&](int j, int rl) {
+      return r0 + rl < R ? sv[(int64_t)rows[o + j] * R + r0 + rl] : make_double2(0, 0);
+    });
+    if (lane < RB) hbt[i * RB + lane] = make_double2(s.x + a.x, s.y + a.y);
+  }
+  __syncthreads();
+  for (int i = wv; i < nb; i += NT / 64) {
+    const double2 s = hblock_row(Xi + moff[b], nb, i, RB, [&](int j, int rl) { return hbt[j * RB + rl]; });
+    if (mine) u[(int64_t)rows[o + i] * R + r] = s;
+  }
+}
+
+// Blocks too large for that: a wave per block row i and RB columns,
 //   out_i = (add ? add[row_i] : 0) + sum_j M_b[i, j] in_j
 // in_j is x[row_j] (gather) or x[off_b + j] (compact); out_i goes to
 // y[row_i] (scatter) or y[off_b + i] (compact).
@@ -702,41 +802,23 @@ __global__ void __launch_bounds__(NT) k_hblock(int nh, const int* __restrict__ b
                                                const int* __restrict__ rows, const int64_t* __restrict__ moff,
                                                const double* __restrict__ M, const double2* __restrict__ x,
                                                int in_gather, const double2* __restrict__ add,
-                                               double2* __restrict__ y, int out_scatter, int R) {
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * (NT / 64) + (threadIdx.x >> 6);
+                                               double2* __restrict__ y, int out_scatter, int R, int RB) {
+  const int nch = (R + RB - 1) / RB;
+  const int t = blockIdx.x * (NT / 64) + (threadIdx.x >> 6), i = t / nch, r0 = (t - i * nch) * RB;
   if (i >= nh) return;
-  const int b = blk[i], o = off[b], nb = off[b + 1] - o, il = i - o;
-  const double* Mb = M + moff[b];
-  for (int r0 = 0; r0 < R; r0 += 8) {
-    int rc = min(8, R - r0);
-    double ax[8] = {0}, ay[8] = {0};
-    for (int j = lane; j < nb; j += 64) {
-      double m = Mb[il + (int64_t)nb * j];
-      int64_t src = in_gather ? (int64_t)rows[o + j] : (int64_t)(o + j);
-      for (int r = 0; r < rc; ++r) {
-        double2 v = x[src * R + r0 + r];
-        ax[r] += m * v.x;
-        ay[r] += m * v.y;
-      }
-    }
-    for (int r = 0; r < rc; ++r) {
-      double sx = ax[r], sy = ay[r];
-      for (int sh = 32; sh > 0; sh >>= 1) {
-        sx += __shfl_down(sx, sh, 64);
-        sy += __shfl_down(sy, sh, 64);
-      }
-      if (lane == 0) {
-        if (add) {
-          double2 a = add[(int64_t)rows[i] * R + r0 + r];
-          sx += a.x;
-          sy += a.y;
-        }
-        int64_t dst = out_scatter ? (int64_t)rows[i] : (int64_t)i;
-        y[dst * R + r0 + r] = make_double2(sx, sy);
-      }
-    }
+  const int b = blk[i], o = off[b], nb = off[b + 1] - o;
+  double2 s = hblock_row(M + moff[b], nb, i - o, RB, [&](int j, int rl) {
+    const int64_t src = in_gather ? (int64_t)rows[o + j] : (int64_t)(o + j);
+    return r0 + rl < R ? x[src * R + r0 + rl] : make_double2(0, 0);
+  });
+  const int lane = threadIdx.x & 63;
+  if (lane >= RB || r0 + lane >= R) return;
+  if (add) {
+    const double2 a = add[(int64_t)rows[i] * R + r0 + lane];
+    s.x += a.x;
+    s.y += a.y;
   }
+  y[(out_scatter ? (int64_t)rows[i] : (int64_t)i) * R + r0 + lane] = s;
 }
 
 // The top depths of the tree as one dense block (several columns): the
@@ -2378,15 +2460,52 @@ void launch_assemble(const Handle& h, const T2* GL, const double2* Bfull, const 
   HIPCHECK(hipGetLastError());
 }
 
-void launch_hblock(const Handle& h, bool y2, const double2* x, bool in_gather, const double2* add, double2* y,
-                   bool out_scatter, int R, hipStream_t s) {
+static int hb_cols(int R) {   // columns a wave takes: a power of two, at most HB_R
+  int rb = 1;
+  while (rb < R && rb < HB_R) rb <<= 1;
+  return rb;
+}
+
+void launch_hcopy(const Handle& h, const double2* v, double2* y, int R, hipStream_t s) {
   const auto& d = h.d;
-  if (h.nh == 0) return;
-  hipLaunchKernelGGL(k_hblock, dim3(nblocks(h.nh, NT / 64)), dim3(NT), 0, s, h.nh, d.hb_blk, d.hb_off, d.hb_rows,
-                     d.hb_moff, y2 ? d.hb_y2 : d.hb_xinv, x, int(in_gather), add, y, int(out_scatter), R);
+  const int RB = hb_cols(R), nch = (R + RB - 1) / RB;
+  const int64_t count = int64_t(h.nlam) * R;
+  const int copies = int(nblocks(count));
+  hipLaunchKernelGGL(k_hcopy, dim3(copies + nblocks(int64_t(h.nh) * nch, NT / 64)), dim3(NT), 0, s, count, copies,
+                     d.hb_of, h.nh, d.hb_blk, d.hb_off, d.hb_rows, d.hb_moff, d.hb_xinv, v, y, R, RB);
   HIPCHECK(hipGetLastError());
 }
 
+// a workgroup per block up to 128 rows
+// whose inner sums take at most 16 KiB (64 rows at 16 columns, two products of 64 x 64 x 16)
+template <class T2>
+bool launch_hgather(const Handle& h, const T2* src, const double2* sv, double2* u, int R, hipStream_t s) {
+  const auto& d = h.d;
+  const int nblk = int(h.hb_off.size()) - 1, RB = hb_cols(R), nch = (R + RB - 1) / RB;
+  int most = 0;
+  for (int b = 0; b < nblk; ++b) most = std::max(most, h.hb_off[b + 1] - h.hb_off[b]);
+  const size_t lds = size_t(most) * RB * sizeof(double2);
+  if (most > 128 || lds > 16 * 1024) return false;
+  const int64_t count = int64_t(h.nlam) * R;
+  const int copies = int(nblocks(count));
+  hipLaunchKernelGGL((k_hgather<T2>), dim3(copies + nblk * nch), dim3(NT), lds, s, count, copies, d.hb_of, d.row_slot,
+                     d.row_coef, d.row_xinv, src, d.hb_off, d.hb_rows, d.hb_moff, d.hb_xinv, d.hb_y2, sv, u, R, RB);
+  HIPCHECK(hipGetLastError());
+  return true;
+}
+
+void launch_hblock(const Handle& h, bool y2, const double2* x, bool in_gather, const double2* add, double2* y,
+                   bool out_scatter, int R, hipStream_t s) {
+  const auto& d = h.d;
+  const int RB = hb_cols(R), nch = (R + RB - 1) / RB;
+  hipLaunchKernelGGL(k_hblock, dim3(nblocks(int64_t(h.nh) * nch, NT / 64)), dim3(NT), 0, s, h.nh, d.hb_blk, d.hb_off,
+                     d.hb_rows, d.hb_moff, y2 ? d.hb_y2 : d.hb_xinv, x, int(in_gather), add, y, int(out_scatter), R,
+                     RB);
+  HIPCHECK(hipGetLastError());
+}
+
+template bool launch_hgather<double2>(const Handle&, const double2*, const double2*, double2*, int, hipStream_t);
+template bool launch_hgather<float2>(const Handle&, const float2*, const double2*, double2*, int, hipStream_t);
 template void launch_slot_apply<double2>(const Handle&, int, const double2*, double2*, double2*, int, hipStream_t);
 template void launch_slot_apply<float2>(const Handle&, int, const float2*, float2*, float2*, int, hipStream_t);
 template void launch_slot_coarse<double2>(const Handle&, const double2*, const double2*, double2*, int, hipStream_t);

@@ -56,6 +56,27 @@ def test_interface_operator_and_preconditioner(name, literal):
     s.close()
 
 
+@pytest.mark.parametrize("R", [3, 8, 12, 16, 17, 33])
+@pytest.mark.parametrize("mesh", ["small_blocks", "large_blocks"])
+def test_preconditioner_at_every_block_width(mesh, R):
+    """P^-1 v on hanging edges, whose blocks take up to 16 columns a wave, against one
+    column at a time; four sides of degree 18 on one coarse side make a block of 68
+    rows, at 16 columns beyond the gather's shared memory."""
+    lv = W.refine_where(W.morton_leaves(2, 2), 0, 1, 0, 1, 2, 2, lambda x, y: (x < 0.5) & (y < 0.5), 2)
+    p = 18 if mesh == "large_blocks" else 5
+    w = dict(domain=(0.0, 1.0, 0.0, 1.0), base=(2, 2), leaves=lv, degree=np.full(len(lv), p), k=6.0, l=1,
+             bc="impedance", eps_r=np.ones(len(lv)), discard_tol=0.0)
+    s = hdp().Solver(w, max_rhs=64, max_iter=10)
+    rng = np.random.default_rng(R)
+    v = torch.from_numpy(rng.standard_normal((s.n_lambda, R)) + 1j * rng.standard_normal((s.n_lambda, R))).cuda()
+    for precision, tol in (("fp64", 1e-12), ("mixed", 1e-5)):
+        got = s.apply_precond(v, precision).cpu().numpy()
+        for r in range(R):
+            one = s.apply_precond(v[:, r:r + 1].contiguous()).cpu().numpy()
+            assert rel(got[:, r], one[:, 0]) < tol, (precision, r)
+    s.close()
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_interface_rhs(name, literal):
     disc, D = literal[name]
