@@ -1833,7 +1833,33 @@ __device__ __forceinline__ void cdot_acc(double2 a, double2 b, double& x, double
   y += a.x * b.y - a.y * b.x;
 }
 
-// few right-hand sides: one wave per (row chunk, basis vector or the extra item)
+// Sums of N values (a power of two) over the lanes of equal lane % R: at each step a
+// lane passes on the half of its values that its partner keeps, so four values take seven
+// exchanges and not 24.  Lane l then
+// holds value `which`, in v[0].
+template <int N>
+__device__ __forceinline__ int lane_sums(double (&v)[N], int R) {
+  const int lane = threadIdx.x & 63;
+  int which = 0, off = 32;
+#pragma unroll
+  for (int half = N / 2; half >= 1; half >>= 1, off >>= 1) {
+    const bool up = lane & off;
+#pragma unroll
+    for (int q = 0; q < half; ++q) {
+      const double keep = up ? v[half + q] : v[q], send = up ? v[q] : v[half + q];
+      v[q] = keep + __shfl_xor(send, off, 64);
+    }
+    which += up ? half : 0;
+  }
+  for (; off >= R; off >>= 1) v[0] += __shfl_xor(v[0], off, 64);
+  return which;
+}
+
+// few right-hand sides (R <= 4): one wave per (row chunk, basis vector or the extra
+// item).  Point source, 27,776 unknowns, one column, 96 vectors on average: 11.6 us
+// a launch for 43 MB of basis (12.6 with a butterfly over all six sums); groups of 2
+// and 4 vectors, which share the reads of u and z, took 14.5 and 21.6, with too few
+// loads in flight.
 __global__ void __launch_bounds__(NT) k_dmdot_wave(const double2* __restrict__ V, int64_t vs,
                                                    const int* __restrict__ jptr, const double2* __restrict__ z, int n,
                                                    int R, int chunk, int nchunks, int dstride,
@@ -1847,41 +1873,32 @@ __global__ void __launch_bounds__(NT) k_dmdot_wave(const double2* __restrict__ V
   for (int item = wave; item < nitems; item += nwaves) {
     const int c = item % nchunks, i = item / nchunks;
     const int64_t lo = (int64_t)c * chunk * R, hi = min((int64_t)n, (int64_t)(c + 1) * chunk) * R;
-    double x0 = 0, y0 = 0, x1 = 0, y1 = 0, x2 = 0, y2 = 0;
+    double2* pc = part + (int64_t)c * dstride * R + lane % R;
+    double v[4] = {0, 0, 0, 0};
     if (i < j) {
-      const double2* q = V + (int64_t)i * vs;
+      const double2* q = V + (int64_t)i * vs;   // q^H u, q^H z
 #pragma unroll 4
       for (int64_t e = lo + lane; e < hi; e += 64) {
         const double2 a = q[e];
-        cdot_acc(a, u[e], x0, y0);
-        cdot_acc(a, z[e], x1, y1);
+        cdot_acc(a, u[e], v[0], v[1]);
+        cdot_acc(a, z[e], v[2], v[3]);
       }
     } else {
 #pragma unroll 4
-      for (int64_t e = lo + lane; e < hi; e += 64) {
+      for (int64_t e = lo + lane; e < hi; e += 64) {   // u^H z, |u|^2, |z|^2
         const double2 a = u[e], b = z[e];
-        cdot_acc(a, b, x0, y0);
-        x1 += a.x * a.x + a.y * a.y;
-        x2 += b.x * b.x + b.y * b.y;
+        cdot_acc(a, b, v[0], v[1]);
+        v[2] += a.x * a.x + a.y * a.y;
+        v[3] += b.x * b.x + b.y * b.y;
       }
     }
-    for (int off = 32; off >= R; off >>= 1) {
-      x0 += __shfl_xor(x0, off, 64);
-      y0 += __shfl_xor(y0, off, 64);
-      x1 += __shfl_xor(x1, off, 64);
-      y1 += __shfl_xor(y1, off, 64);
-      x2 += __shfl_xor(x2, off, 64);
-    }
-    if (lane < R) {
-      double2* pc = part + (int64_t)c * dstride * R + lane;
-      if (i < j) {
-        pc[(int64_t)i * R] = make_double2(x0, y0);
-        pc[(int64_t)(j + i) * R] = make_double2(x1, y1);
-      } else {
-        pc[(int64_t)(2 * j) * R] = make_double2(x0, y0);
-        pc[(int64_t)(2 * j + 1) * R] = make_double2(x1, 0);
-        pc[(int64_t)(2 * j + 2) * R] = make_double2(x2, 0);
-      }
+    const int k = lane_sums(v, R);   // (lanes that hold the same value write it alike)
+    if (i < j) {
+      reinterpret_cast<double*>(pc + (int64_t)(k < 2 ? i : j + i) * R)[k & 1] = v[0];
+    } else {
+      double* o = reinterpret_cast<double*>(pc + (int64_t)(2 * j + max(0, k - 1)) * R);
+      o[k == 1] = v[0];
+      if (k >= 2) o[1] = 0;
     }
   }
 }
@@ -2085,8 +2102,8 @@ __global__ void __launch_bounds__(NT) k_dcgs_scalar(int* __restrict__ jptr, cons
 // three blocks, 168 unknowns, took 8 of the 13 us of that update).
 __device__ void first_pass_rows(int j, int R, int maxvec, const double2* __restrict__ Hraw,
                                 const double2* __restrict__ uc, double2* __restrict__ hprev) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int item = (gridDim.x - 1 - blockIdx.x) * (NT / 64) + wv; item < (j + 1) * R; item += gridDim.x * (NT / 64)) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  for (int item = (gridDim.x - 1 - blockIdx.x) * nw + wv; item < (j + 1) * R; item += gridDim.x * nw) {
     const int i = item / R, r = item - i * R;
     double x = 0, y = 0;
     for (int k = max(0, i - 1) + lane; k < j; k += 64) {
@@ -2108,14 +2125,17 @@ __device__ void first_pass_rows(int j, int R, int maxvec, const double2* __restr
 
 // The update of iteration j (read as *jptr - 1, after the scalar step):
 // V_j = q_j = (u - Q s) / nu and V_{j+1} = out2 = (z - Q t - q_j tau) / sigma.
-// Short vectors: a workgroup owns 64 entries and its four waves take every
-// fourth basis vector.
-__global__ void __launch_bounds__(NT) k_dupdate_split(double2* __restrict__ V, int64_t vs,
+// Short vectors: a workgroup owns 64 entries and its UW waves take every UW-th basis
+// vector (a wave's loads, four in flight, are a chain: with four waves the update of
+// the point source, 27,776 unknowns and 96 vectors on average, took 12.2 us).
+constexpr int UW = 8;
+
+__global__ void __launch_bounds__(64 * UW) k_dupdate_split(double2* __restrict__ V, int64_t vs,
                                                       const int* __restrict__ jptr, const double2* __restrict__ uc,
                                                       double2* __restrict__ z, int n, int R,
                                                       double2* __restrict__ out2, const double2* __restrict__ Hraw,
                                                       double2* __restrict__ hprev, int maxvec) {
-  __shared__ double2 red[2][NT / 64][64];
+  __shared__ double2 red[2][UW][64];
   const int j = *jptr - 1;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t idx = (int64_t)blockIdx.x * 64 + lane;
@@ -2124,7 +2144,7 @@ __global__ void __launch_bounds__(NT) k_dupdate_split(double2* __restrict__ V, i
   double sx = 0, sy = 0, tx = 0, ty = 0;
   if (live) {
 #pragma unroll 4
-    for (int i = wv; i < j; i += NT / 64) {
+    for (int i = wv; i < j; i += UW) {
       const double2 a = V[(int64_t)i * vs + idx], b = uc[(int64_t)i * R + r], c = uc[(int64_t)(j + i) * R + r];
       sx += a.x * b.x - a.y * b.y;
       sy += a.x * b.y + a.y * b.x;
@@ -2137,7 +2157,7 @@ __global__ void __launch_bounds__(NT) k_dupdate_split(double2* __restrict__ V, i
   __syncthreads();
   if (wv == 0 && live) {
     double ax = 0, ay = 0, bx = 0, by = 0;
-    for (int q = 0; q < NT / 64; ++q) {
+    for (int q = 0; q < UW; ++q) {
       ax += red[0][q][lane].x;
       ay += red[0][q][lane].y;
       bx += red[1][q][lane].x;
@@ -2559,14 +2579,13 @@ GmresDims gmres_dims(int n, int R, int maxvec) {
   GmresDims g;
   g.step = NT / R;
   g.wave = R < 8;
-  g.ngroups = maxvec;   // one basis vector per multi-dot item
   if (g.wave) {
     // one wave per (chunk, basis vector): 256 entries per chunk (four per lane),
     // more when the partial buffer's 512 chunks would not cover the rows; a
     // grid of up to 4,096 workgroups (16,384 waves) strides over the items
     g.chunk = int(std::max<int64_t>(256 / R, (int64_t(n) + 511) / 512));
     g.nchunks = int((int64_t(n) + g.chunk - 1) / g.chunk);
-    g.grid = int(std::max<int64_t>(1, std::min<int64_t>(4096, (int64_t(g.nchunks) * g.ngroups + 3) / 4)));
+    g.grid = int(std::max<int64_t>(1, std::min<int64_t>(4096, (int64_t(g.nchunks) * maxvec + 3) / 4)));
   } else {
     // up to 512 row chunks (the partial buffer holds 512) keep the chip busy with
     // many right-hand sides while only a few Arnoldi vectors exist
@@ -2637,7 +2656,7 @@ void launch_dupdate(double2* V, int64_t vs, const int* jptr, const double2* uc, 
                     double2* out2, const double2* Hraw, double2* hprev, int maxvec, hipStream_t s) {
   if (int64_t(n) * R <= UPD_SPLIT_MAX)
     // (blocks past the entries take first-pass rows alone)
-    hipLaunchKernelGGL(k_dupdate_split, dim3(std::max(nblocks(int64_t(n) * R, 64), 32u)), dim3(NT), 0, s, V, vs, jptr, uc, z, n, R,
+    hipLaunchKernelGGL(k_dupdate_split, dim3(std::max(nblocks(int64_t(n) * R, 64), 32u)), dim3(64 * UW), 0, s, V, vs, jptr, uc, z, n, R,
                        out2, Hraw, hprev, maxvec);
   else
     hipLaunchKernelGGL(k_dupdate, dim3(nblocks(int64_t(n) * R)), dim3(NT), 0, s, V, vs, jptr, uc, z, n, R, out2, Hraw,

@@ -139,7 +139,7 @@ int dots_blocks(int n, int R);
 
 // Device-resident GMRES (R divides 64; j read from device memory when jptr != nullptr)
 struct GmresDims {
-  int nchunks = 1, chunk = 1, ngroups = 1, nnorm = 1, step = 1, grid = 1;
+  int nchunks = 1, chunk = 1, nnorm = 1, step = 1, grid = 1;
   bool wave = false;   // wave-per-item multi-dot (few right-hand sides)
 };
 // symmetric tiled coarse apply (one right-hand side): tile edge, packing of
