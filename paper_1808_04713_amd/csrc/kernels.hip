@@ -112,6 +112,91 @@ __global__ void __launch_bounds__(NT) k_slot_apply(const SlotBlock* __restrict__
   }
 }
 
+// One column: a thread per row of the element's matrix, its sum in order.  The chain of
+// such a block is its cost (record, slot records, gathered rows, 60 matrix columns), so
+// the matrix is read SLOT_AHEAD columns ahead of the sum, the first ones before the
+// operand is gathered, and a block has no more waves than rows.  F and P^-1 of the
+// point source (32x32 elements, 60 slots each) 7.2 -> 6.2 and 8.1 -> 7.0 us, of the
+// refined disk 7.8 -> 6.5 and 7.6 -> 6.0.  (Phi read ahead in the same way in
+// k_slot_coarse, whose other waves gather, took it from 12 to 23 us at 64x64 elements:
+// its 155 registers leave three waves a SIMD.)
+constexpr int SLOT_AHEAD = 16;
+
+template <class T2>
+struct ColumnSum {
+  T2 a[SLOT_AHEAD];
+  const T2* A;
+  int ld, K;
+  // columns of row i from k0 on (past the last one: the last, against zeros)
+  __device__ __forceinline__ void load(int i, int k0) {
+#pragma unroll
+    for (int q = 0; q < SLOT_AHEAD; ++q) a[q] = A[i + (int64_t)ld * min(k0 + q, K - 1)];
+  }
+  // acc + sum_k A[i, k] y[k ys]; y is zero up to the next multiple of SLOT_AHEAD past K
+  __device__ __forceinline__ T2 sum(int i, const T2* y, int ys, T2 acc) {
+    for (int k0 = 0; k0 < K; k0 += SLOT_AHEAD) {
+      T2 b[SLOT_AHEAD];
+#pragma unroll
+      for (int q = 0; q < SLOT_AHEAD; ++q) b[q] = a[q];
+      if (k0 + SLOT_AHEAD < K) load(i, k0 + SLOT_AHEAD);
+#pragma unroll
+      for (int q = 0; q < SLOT_AHEAD; ++q) acc = cfma(b[q], y[(k0 + q) * ys], acc);
+    }
+    return acc;
+  }
+};
+
+enum SlotKind { SLOT_F, SLOT_P, SLOT_JUMPS, SLOT_ROWS };
+
+// SLOT_F: op1 on the gathered dual rows (X and the coarse modes' GL); SLOT_P: S_e on
+// them (X); SLOT_JUMPS: S_e on the jumps of the slots (X); SLOT_ROWS: the same, added
+// into the dual rows `out` as k_slot_apply_rows does
+template <class T2, int KIND>
+__global__ void __launch_bounds__(NT) k_slot_one(const SlotBlock* __restrict__ blk, const SlotIn* __restrict__ sin,
+                                                 const SlotOut* __restrict__ sout, const T2* __restrict__ mat,
+                                                 const T2* __restrict__ v, T2* __restrict__ X, T2* __restrict__ GL,
+                                                 double2* __restrict__ out) {
+  using S = typename Scal<T2>::T;
+  __shared__ T2 y[MMAX + SLOT_AHEAD];
+  const SlotBlock B = blk[blockIdx.x];
+  const int m = B.m, so = B.so, i = threadIdx.x;
+  const int nrow = KIND == SLOT_F ? m + B.nr : m;
+  ColumnSum<T2> c{{}, mat + (KIND == SLOT_F ? B.op1 : B.se), nrow, m};
+  const int row = min(i, nrow - 1);
+  if (m > 0) c.load(row, 0);
+  for (int s = i; s < m + SLOT_AHEAD; s += blockDim.x) {
+    S ax = 0, ay = 0;
+    if (s < m) {
+      const SlotIn g = sin[so + s];
+      if (g.s0 >= 0) {
+        const T2 z = v[g.s0];
+        ax += S(g.a0) * z.x;
+        ay += S(g.a0) * z.y;
+      }
+      if (KIND >= SLOT_JUMPS && g.s1 >= 0) {
+        const T2 z = v[g.s1];
+        ax += S(g.a1) * z.x;
+        ay += S(g.a1) * z.y;
+      }
+    }
+    y[s] = mk<T2>(ax, ay);
+  }
+  SlotOut o{};
+  if (KIND == SLOT_ROWS && i < m) o = sout[so + i];
+  __syncthreads();
+  const T2 acc = c.sum(row, y, 1, mk<T2>(0, 0));
+  if (i >= nrow) return;
+  if (KIND == SLOT_ROWS) {
+    double2* p = out + o.row;
+    unsafeAtomicAdd(&p->x, o.coef * double(acc.x));
+    unsafeAtomicAdd(&p->y, o.coef * double(acc.y));
+  } else if (i < m) {
+    X[so + i] = acc;
+  } else {
+    GL[B.cmo + i - m] = acc;
+  }
+}
+
 // The preconditioner on dual slots (S_e on the jumps C_1 z of each element's
 // slots) with the row gather fused: every output slot adds its value times its
 // row coefficient into the dual row.  A row has at most two slots and out is
@@ -2337,12 +2422,23 @@ static size_t slot_mfma_lds(const Handle& h, int R, int mode) {
   return lds;
 }
 
+// threads of the one-column slot kernels: the waves that hold the longest class's rows
+static int slot_one_threads(const Handle& h, bool f) {
+  int rows = 1;
+  for (auto& C : h.classes) rows = std::max(rows, f ? C.m + C.nr : C.m);
+  return (rows + 63) / 64 * 64;
+}
+
 bool slot_rows_fused(const Handle& h, int R) { return !h.nonconforming && R < 16; }
 
 void launch_slot_apply_rows(const Handle& h, const double2* v, double2* out, int R, hipStream_t s) {
   const auto& d = h.d;
-  hipLaunchKernelGGL(k_slot_apply_rows, dim3(h.E, (R + RC - 1) / RC), dim3(NT), 0, s, d.slot_blk, d.slot_in[2],
-                     d.slot_out, d.se, v, out, R);
+  if (R == 1)
+    hipLaunchKernelGGL((k_slot_one<double2, SLOT_ROWS>), dim3(h.E), dim3(slot_one_threads(h, false)), 0, s, d.slot_blk,
+                       d.slot_in[2], d.slot_out, d.se, v, nullptr, nullptr, out);
+  else
+    hipLaunchKernelGGL(k_slot_apply_rows, dim3(h.E, (R + RC - 1) / RC), dim3(NT), 0, s, d.slot_blk, d.slot_in[2],
+                       d.slot_out, d.se, v, out, R);
   HIPCHECK(hipGetLastError());
 }
 
@@ -2380,6 +2476,18 @@ void launch_slot_apply(const Handle& h, int mode, const T2* v, T2* X, T2* GL, in
   const T2* se;
   if constexpr (std::is_same<T2, double2>::value) { op1 = d.op1; se = d.se; }
   else { op1 = d.op1_f; se = d.se_f; }
+  if (R == 1) {
+    const dim3 t(slot_one_threads(h, mode == 0));
+#define HDP_SLOT_ONE(KIND, MAT) \
+  hipLaunchKernelGGL((k_slot_one<T2, KIND>), dim3(h.E), t, 0, s, d.slot_blk, d.slot_in[mode], nullptr, MAT, v, X, GL, \
+                     nullptr)
+    if (mode == 0) HDP_SLOT_ONE(SLOT_F, op1);
+    else if (mode == 1) HDP_SLOT_ONE(SLOT_P, se);
+    else HDP_SLOT_ONE(SLOT_JUMPS, se);
+#undef HDP_SLOT_ONE
+    HIPCHECK(hipGetLastError());
+    return;
+  }
 #define HDP_SLOT_ARGS d.slot_blk, d.slot_in[mode], op1, se, v, X, GL, R
   if (mode == 0)
     hipLaunchKernelGGL((k_slot_apply<T2, 0>), grid, dim3(NT), 0, s, HDP_SLOT_ARGS);
