@@ -801,7 +801,7 @@ template <class F>
 __device__ __forceinline__ double2 hblock_row(const double* __restrict__ Mb, int nb, int il, int RB, F&& in) {
   const int lane = threadIdx.x & 63, rl = lane & (RB - 1);
   double sx = 0, sy = 0;
-#pragma unroll 2
+#pragma unroll 4
   for (int j = lane / RB; j < nb; j += 64 / RB) {
     const double m = Mb[il + (int64_t)nb * j];
     const double2 v = in(j, rl);
@@ -817,7 +817,7 @@ __device__ __forceinline__ double2 hblock_row(const double* __restrict__ Mb, int
 
 // y = v, X^-1 v on the blocks' rows (hb_of: the row's number among them, or -1):
 // workgroups of entries, then, from block `copies` on, a wave per block row and HB_R columns
-constexpr int HB_R = 16;
+constexpr int HB_R = 4;   // 16 lanes a column: sums of 16 rows in one step, of 64 in four loads in flight
 
 __global__ void __launch_bounds__(NT) k_hcopy(int64_t count, int copies, const int* __restrict__ hb_of, int nh,
                                               const int* __restrict__ blk, const int* __restrict__ off,
@@ -2612,8 +2612,8 @@ void launch_hcopy(const Handle& h, const double2* v, double2* y, int R, hipStrea
   HIPCHECK(hipGetLastError());
 }
 
-// a workgroup per block up to 128 rows
-// whose inner sums take at most 16 KiB (64 rows at 16 columns, two products of 64 x 64 x 16)
+// a workgroup per block of up to 16 rows, two products of four rows a wave; longer
+// blocks keep their waves per row, in two launches
 template <class T2>
 bool launch_hgather(const Handle& h, const T2* src, const double2* sv, double2* u, int R, hipStream_t s) {
   const auto& d = h.d;
@@ -2621,7 +2621,7 @@ bool launch_hgather(const Handle& h, const T2* src, const double2* sv, double2* 
   int most = 0;
   for (int b = 0; b < nblk; ++b) most = std::max(most, h.hb_off[b + 1] - h.hb_off[b]);
   const size_t lds = size_t(most) * RB * sizeof(double2);
-  if (most > 128 || lds > 16 * 1024) return false;
+  if (most > 16) return false;
   const int64_t count = int64_t(h.nlam) * R;
   const int copies = int(nblocks(count));
   hipLaunchKernelGGL((k_hgather<T2>), dim3(copies + nblk * nch), dim3(NT), lds, s, count, copies, d.hb_of, d.row_slot,
@@ -2655,7 +2655,7 @@ template void launch_assemble<double2>(const Handle&, const double2*, const doub
 template void launch_assemble<float2>(const Handle&, const float2*, const double2*, const double2*, double, double2*,
                                       int, hipStream_t);
 
-// Strip sweeps of the block-tridiagonal coarse factor at one column.
+// The tiled symmetric inverse at one column: partial products, then their row sums.
 void launch_coarse_symv_tiles(const Handle& h, const double2* g, hipStream_t s) {
   hipLaunchKernelGGL(k_coarse_symv_tiles, dim3(h.sym_ntiles), dim3(SYM_WAVES * 64), 0, s, h.nK, h.sym_nt,
                      h.d.sym_tij, h.d.Ksym, g, h.d.sym_part);

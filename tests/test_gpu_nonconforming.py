@@ -59,9 +59,9 @@ def test_interface_operator_and_preconditioner(name, literal):
 @pytest.mark.parametrize("R", [3, 8, 12, 16, 17, 33])
 @pytest.mark.parametrize("mesh", ["small_blocks", "large_blocks"])
 def test_preconditioner_at_every_block_width(mesh, R):
-    """P^-1 v on hanging edges, whose blocks take up to 16 columns a wave, against one
+    """P^-1 v on hanging edges, whose blocks take up to four columns a wave, against one
     column at a time; four sides of degree 18 on one coarse side make a block of 68
-    rows, at 16 columns beyond the gather's shared memory."""
+    rows, too long for the gather's workgroup."""
     lv = W.refine_where(W.morton_leaves(2, 2), 0, 1, 0, 1, 2, 2, lambda x, y: (x < 0.5) & (y < 0.5), 2)
     p = 18 if mesh == "large_blocks" else 5
     w = dict(domain=(0.0, 1.0, 0.0, 1.0), base=(2, 2), leaves=lv, degree=np.full(len(lv), p), k=6.0, l=1,
