@@ -793,7 +793,7 @@ __global__ void k_assemble(int nK, const int* __restrict__ ptr, const int* __res
 // chain of its loads: X^-1 v shares the launch that copies the other rows, and
 // X^-1 (u + Y_2 s) the one that gathers them, in workgroups of their own.
 // X^-1 Y X^-1 of the disk at 12 columns: 73 us a call with six launches, of it 3 + 8 +
-// 4 + 9 + 6 for these steps.
+// 4 + 9 + 6 for these steps, which take 3.6 + 4.3 now; 49 us.
 
 // sum_j M[il, j] in(j) for one block row, on a wave: 64 / RB lanes per column split the
 // sum (RB columns, a power of two); valid in the first RB lanes
@@ -1352,7 +1352,7 @@ __global__ void __launch_bounds__(NT) k_far_trace(const int* __restrict__ elem, 
 // of FAR_Q nodes are formed once (a sine and a cosine each) and shared by its columns,
 // and a node's U and DU are read once for its angles.  360 angles and 64 columns on
 // the boundary of a 64x64-element box: 316 us with a workgroup per angle and the
-// phases formed by every column's thread.
+// phases formed by every column's thread, 77 now.
 constexpr int FAR_A = 4, FAR_R = 16, FAR_Q = 64;
 
 __global__ void __launch_bounds__(NT) k_far_sum(int nq, const double* __restrict__ px, const double* __restrict__ py,
@@ -1466,7 +1466,7 @@ __global__ void __launch_bounds__(NT) k_far_adjoint(int nsides, const int* __res
 // once per column (2 q or 4 q of them, in shared memory), then every basis function's
 // integral, then the element's block in runs of RB columns.  With a workgroup per
 // column and the phases formed again for every basis function, 256 elements of degree
-// 15 and 64 angles took 330 us, nearly all of it sines and cosines.
+// 12 and 64 angles took 330 us, nearly all of it sines and cosines; now 38.
 constexpr int PW_R = 8;
 
 __global__ void __launch_bounds__(NT) k_plane_wave_loads(
