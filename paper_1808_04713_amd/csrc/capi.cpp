@@ -1352,7 +1352,7 @@ static void autotune(Handle& h, bool fdm, bool slot) {
       double tbest = 1e300;
       const size_t first = h.tune.size();
       for (int rc : {1, 2, 4, 8, 16}) {
-        if (rc > std::min(16, R)) break;
+        if (rc > std::min(16, R) || !sep_width_fits(h, rc)) break;
         launch_fill_zero(d.cmX, int64_t(h.ncm) * R, s);
         const double ms = time3([&] {
           launch_sep_coarse(h, d.full0, R, s, nullptr, nullptr, rc);

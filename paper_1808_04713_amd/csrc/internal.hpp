@@ -12,6 +12,7 @@
 
 #include "../../include/hdp.h"
 #include "dense.hpp"
+#include "sep_cut.hpp"
 
 namespace hdp {
 
@@ -123,17 +124,9 @@ struct SlotBlock {
   int64_t op1, se, phi;
   int e, c, so, cmo, m, nr, pad0, pad1;
 };
-// The separable element solves (separable.hip): per element, in class order, its
-// first coefficient, coarse mode and dual slot; per class its sizes and the offsets of
+// The separable element solves (separable.hip): per class its sizes and the offsets of
 // its eigenbases, 1/D, K_e, GLL sampling matrix, coarse-mode and dual-slot lists.
-// Classes are bucketed by kernel (sep_len); a bucket's items are runs of
-// at most eg elements of one class in class order, for each eg up to SEP_EG_MAX.
-constexpr int SEP_EG_MAX = 8;
 enum { SEP_SOLVE = 0, SEP_COARSE = 1, SEP_FULL = 2, SEP_GLL = 3 };
-struct SepElem {
-  int64_t base;
-  int cmo, s0;
-};
 struct SepClass {
   int64_t ex, ey, doff, kc, voff;
   int n, nr, ns, roff, goff, rx, ry, pad;   // rx, ry: 1 where the eigenbasis is real
@@ -141,10 +134,6 @@ struct SepClass {
 struct SepItem {
   SepClass cls;
   int pos, count;
-};
-struct SepBucket {
-  int N = 0, n = 0, nr = 0;   // kernel (sep_len), largest n and nr
-  int first[SEP_EG_MAX] = {0}, count[SEP_EG_MAX] = {0};   // items for 1, 2, .. elements per workgroup
 };
 // Per-slot input gather of the slot kernels: value = a0 v[s0] + a1 v[s1] (an
 // index < 0 contributes nothing), the row scalings already multiplied in.

@@ -62,6 +62,8 @@ void launch_coarse_solve(const Handle& h, const double2* g, double2* w, int R, h
 // x_R - T_e w, or -T_e w where kx gives K_e x_R ([ncm][R]).  rc: right-hand sides
 // per workgroup (0: the handle's choice).
 int sep_len(int n);
+// whether rc right-hand sides of every element fit a workgroup
+bool sep_width_fits(const Handle& h, int rc);
 void launch_sep_solve(const Handle& h, const double2* in, double2* out, int R, hipStream_t s);
 void launch_sep_coarse(const Handle& h, const double2* in, int R, hipStream_t s, const double2* nu,
                        double2* xslot = nullptr, int rc = 0);

@@ -374,61 +374,6 @@ __global__ void __launch_bounds__(256) k_sep(SepArgs g, const double* __restrict
   }
 }
 
-// Cut of a bucket's columns: rc columns of one element per workgroup, or all R
-// columns of eg elements of a class where R alone leaves lanes idle.
-struct SepCut {
-  int rc, eg, nchunk, threads;
-  size_t lds;
-};
-
-// shared memory: the stage and the coarse values
-size_t sep_lds(int n, int nr, int ncol, bool padded) {
-  return (size_t(n) * n * (padded ? ncol | 1 : ncol) + size_t(nr) * ncol) * sizeof(double2);
-}
-
-// The widest classes of a bucket decide (n, nr its largest).  Of the widths whose
-// stage stays within 40 KiB (four workgroups per compute unit, so that the loads
-// of some cover the products of others), the one with the least chunks x (tiles of
-// 16 lines + 3) is taken: a workgroup's load, store and barriers cost about three
-// tiles, and narrow chunks read pieces of cache lines (at 16 modes, where one column
-// fills a tile exactly, single columns took twice the time of eight).  Where so few
-// elements leave less than two workgroups per compute unit, a workgroup's own chain
-// counts and single columns are the faster (100 elements of 22 modes, 3 columns: 51
-// us a call in one chunk, 42 in three).  want > 0 fixes the width (options,
-// autotuner).
-SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
-  const int n = b.n, nr = b.nr;
-  auto tiles = [&](int ncol) { return (n * ncol + 15) / 16; };
-  SepCut c{1, 1, R, 0, 0};
-  if (want > 0) {
-    c.rc = std::min(want, R);
-    while (c.rc > 1 && sep_lds(n, nr, c.rc, padded) > 160 * 1024) c.rc /= 2;
-  } else {
-    int64_t best = INT64_MAX;
-    for (int rc = 1; rc <= std::min(R, 64); ++rc) {
-      const int nchunk = (R + rc - 1) / rc;
-      if (rc > 1 && (sep_lds(n, nr, rc, padded) > 40 * 1024 || int64_t(b.count[0]) * nchunk < 512)) break;
-      const int64_t cost = int64_t(nchunk) * (tiles(rc) + 3);
-      if (cost < best) { best = cost; c.rc = rc; }
-    }
-    if (c.rc == R) {
-      // several elements of a class share a workgroup, as long as some 512
-      // workgroups (two per compute unit) remain
-      double per = tiles(R);
-      for (int eg = 2; eg <= SEP_EG_MAX; ++eg) {
-        if (sep_lds(n, nr, R * eg, true) > 40 * 1024 || b.count[eg - 1] < 512) break;
-        const double p = double(tiles(R * eg)) / eg;
-        if (p < per) { per = p; c.eg = eg; }
-      }
-    }
-  }
-  c.nchunk = (R + c.rc - 1) / c.rc;
-  const int nt = tiles(c.rc * c.eg), rounds = (nt + 3) / 4;
-  c.threads = 64 * ((nt + rounds - 1) / rounds);   // at most four waves, no more than the tiles keep busy
-  c.lds = sep_lds(n, nr, c.rc * c.eg, padded || c.eg > 1);
-  return c;
-}
-
 template <int KS, int MT, int XR>
 void launch_n(int mode, const SepArgs& a, dim3 grid, int threads, size_t lds, const Handle& h, hipStream_t s) {
   const auto& d = h.d;
@@ -471,6 +416,12 @@ void launch_sep(const Handle& h, int mode, SepArgs a, int want, hipStream_t s) {
 }
 
 }  // namespace
+
+bool sep_width_fits(const Handle& h, int rc) {
+  for (const SepBucket& b : h.sep_buckets)
+    if (!sep_fits(b, rc, false)) return false;
+  return true;
+}
 
 // the kernel of a class of n modes per direction, by the largest n it takes
 int sep_len(int n) {

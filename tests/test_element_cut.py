@@ -1,0 +1,50 @@
+"""How the separable element solves are cut into workgroups (csrc/sep_cut.hpp, host
+arithmetic), over the modes, coarse modes, columns and requested widths that a handle
+can have."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LDS = 160 * 1024        # a compute unit's shared memory
+STATIC = 8 * 16         # of it the kernel's own array, a record per element of a workgroup
+COLUMNS = (1, 2, 3, 4, 5, 7, 8, 9, 12, 16, 17, 33, 48, 64)
+
+
+@pytest.fixture(scope="module")
+def cut(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if not cxx:
+        pytest.skip("no host compiler")
+    exe = str(tmp_path_factory.mktemp("cut") / "element_cut")
+    subprocess.run([cxx, "-O1", "-std=c++17", os.path.join(ROOT, "tests", "element_cut.cpp"), "-o", exe], check=True)
+
+    def run(cases):
+        """[(n, nr, elements, R, want, padded)] -> [(rc, eg, nchunk, threads, bytes, fits)]"""
+        text = "\n".join(" ".join(str(int(v)) for v in c) for c in cases) + "\n"
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, check=True)
+        return [tuple(int(v) for v in line.split()) for line in r.stdout.splitlines()]
+    return run
+
+
+def test_every_cut_fits_a_compute_unit(cut):
+    """n modes per direction, nr <= 4 p of them coarse: the dynamic and the kernel's own
+    shared memory together stay within a compute unit's, whatever width is asked for.
+    (24 modes, 64 of them coarse, 16 columns: the dynamic part alone fills it.)"""
+    cases = [(n, nr, ne, R, want, padded) for n in range(2, 42) for nr in sorted({4, 4 * (n - 1) // 2, 64, 4 * (n - 1)})
+             if nr <= 4 * (n - 1) for ne in (4, 1024) for R in COLUMNS for want in (0, 1, 2, 4, 8, 16)
+             for padded in (0, 1)]
+    assert (24, 64, 1024, 16, 16, 0) in cases
+    for c, (rc, eg, nchunk, threads, lds, fits) in zip(cases, cut(cases)):
+        assert lds + STATIC <= LDS, (c, rc, lds)
+        assert 1 <= rc <= c[3] and nchunk * rc >= c[3] > (nchunk - 1) * rc, c
+        assert 64 <= threads <= 256 and threads % 64 == 0, c
+
+
+def test_the_autotuner_is_told_which_widths_fit(cut):
+    widths = (1, 2, 4, 8, 16)
+    for n, nr, most in ((13, 48, 16), (23, 64, 16), (24, 63, 16), (24, 64, 8), (32, 124, 8), (41, 160, 4)):
+        fits = [bool(r[5]) for r in cut([(n, nr, 64, 16, w, 0) for w in widths])]
+        assert fits == [w <= most for w in widths], (n, nr)

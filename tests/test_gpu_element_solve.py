@@ -137,3 +137,24 @@ def test_local_solve_at_the_edges_of_every_kernel(p):
         x = s.local_solve(torch.from_numpy(y).cuda()).cpu().numpy()
         assert rel(x, _dense_ref(w, y)) < 1e-10, R
     s.close()
+
+
+def test_a_width_that_does_not_fit_a_compute_unit():
+    """24 modes, 64 of them coarse: 16 columns of an element and the kernel's own array
+    pass a compute unit's shared memory by that array.  Asked for, the size rule takes
+    over; the autotuner leaves the width out.  cond(E_x) cond(E_y) eps as above."""
+    w = W.small_uniform(2, 23, 9.0, l=16)
+    rng = np.random.default_rng(23)
+    s = hdp().Solver(w, max_rhs=16, tile_fdm=16)
+    y = rng.standard_normal((s.dof, 16)) + 1j * rng.standard_normal((s.dof, 16))
+    x = s.local_solve(torch.from_numpy(y).cuda()).cpu().numpy()
+    assert rel(x, _dense_ref(w, y)) < 1e-10
+    s.close()
+    angles = np.linspace(0.0, 6.0, 16)
+    st = hdp().Solver(w, max_rhs=16, autotune=True)
+    assert {t["cols"] for t in st.autotune_table() if t["kernel"] == "fdm_element_solve"} == {1, 2, 4, 8}
+    su = hdp().Solver(w, max_rhs=16)
+    a, b = st.interface_rhs("plane_wave_total", angles), su.interface_rhs("plane_wave_total", angles)
+    assert rel(a.cpu().numpy(), b.cpu().numpy()) < 1e-10
+    st.close()
+    su.close()
