@@ -47,7 +47,10 @@ inline bool sep_fits(const SepBucket& b, int rc, bool padded) { return sep_lds(b
 // fills a tile exactly, single columns took twice the time of eight).  Where so few
 // elements leave less than two workgroups per compute unit, a workgroup's own chain
 // counts and single columns are the faster (100 elements of 22 modes, 3 columns: 51
-// us a call in one chunk, 42 in three).  want > 0 fixes the width (options,
+// us a call in one chunk, 42 in three), unless all columns make four tiles, a wave
+// each: no longer a chain than one, and one contiguous run to read (the kernel on 256
+// elements, 2 columns: 14.2 us by single columns, 11.1 together at 17 modes, 24.2 and
+// 18.6 at 29).  want > 0 fixes the width (options,
 // autotuner) where it fits a workgroup.
 inline SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
   const int n = b.n, nr = b.nr;
@@ -59,7 +62,8 @@ inline SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
     int64_t best = INT64_MAX;
     for (int rc = 1; rc <= std::min(R, 64); ++rc) {
       const int nchunk = (R + rc - 1) / rc;
-      if (rc > 1 && (sep_lds(n, nr, rc, padded) > 40 * 1024 || int64_t(b.count[0]) * nchunk < 512)) break;
+      if (rc > 1 && sep_lds(n, nr, rc, padded) > 40 * 1024) break;
+      if (rc > 1 && int64_t(b.count[0]) * nchunk < 512 && !(rc == R && tiles(rc) <= 4)) continue;
       const int64_t cost = int64_t(nchunk) * (tiles(rc) + 3);
       if (cost < best) { best = cost; c.rc = rc; }
     }

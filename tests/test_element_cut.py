@@ -48,3 +48,18 @@ def test_the_autotuner_is_told_which_widths_fit(cut):
     for n, nr, most in ((13, 48, 16), (23, 64, 16), (24, 63, 16), (24, 64, 8), (32, 124, 8), (41, 160, 4)):
         fits = [bool(r[5]) for r in cut([(n, nr, 64, 16, w, 0) for w in widths])]
         assert fits == [w <= most for w in widths], (n, nr)
+
+
+
+def test_few_columns_on_few_elements_stay_together(cut):
+    """All columns of an element as one chunk read one contiguous run; four tiles of 16
+    lines, a wave each, take no longer than one, whatever the number of workgroups (256
+    elements of 29 modes, 2 columns: 24 us in two chunks, 18 in one)."""
+    for ne in (4, 16, 100, 256):
+        for n, nr in ((9, 16), (13, 48), (17, 40), (21, 16), (25, 64), (32, 124)):
+            for R in range(2, 8):
+                (rc, eg, nchunk, *_), = cut([(n, nr, ne, R, 0, 0)])
+                if n * R <= 64 and (n * n + nr) * R * 16 <= 40 * 1024:
+                    assert (rc, nchunk) == (R, 1), (n, R, ne)
+                elif ne * nchunk < 512:   # else single columns where workgroups are few
+                    assert rc == 1, (n, R, ne)
