@@ -50,7 +50,9 @@ inline bool sep_fits(const SepBucket& b, int rc, bool padded) { return sep_lds(b
 // us a call in one chunk, 42 in three), unless all columns make four tiles, a wave
 // each: no longer a chain than one, and one contiguous run to read (the kernel on 256
 // elements, 2 columns: 14.2 us by single columns, 11.1 together at 17 modes, 24.2 and
-// 18.6 at 29).  want > 0 fixes the width (options,
+// 18.6 at 29).  Columns in whole cache lines (8) are not cut between one and two lines,
+// where every chunk shares lines with its neighbours on other XCDs (1,024 elements of
+// 14 modes, 64 columns: 180 us in chunks of 11, 156 in chunks of 8).  want > 0 fixes the width (options,
 // autotuner) where it fits a workgroup.
 inline SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
   const int n = b.n, nr = b.nr;
@@ -64,6 +66,7 @@ inline SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
       const int nchunk = (R + rc - 1) / rc;
       if (rc > 1 && sep_lds(n, nr, rc, padded) > 40 * 1024) break;
       if (rc > 1 && int64_t(b.count[0]) * nchunk < 512 && !(rc == R && tiles(rc) <= 4)) continue;
+      if (R % 8 == 0 && rc > 8 && rc < 16 && rc < R) continue;
       const int64_t cost = int64_t(nchunk) * (tiles(rc) + 3);
       if (cost < best) { best = cost; c.rc = rc; }
     }

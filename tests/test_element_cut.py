@@ -63,3 +63,14 @@ def test_few_columns_on_few_elements_stay_together(cut):
                     assert (rc, nchunk) == (R, 1), (n, R, ne)
                 elif ne * nchunk < 512:   # else single columns where workgroups are few
                     assert rc == 1, (n, R, ne)
+
+
+def test_cut_columns_of_whole_lines_stay_in_whole_lines(cut):
+    """Eight columns fill a cache line.  Of columns that come in whole lines, a chunk
+    between one and two lines wide takes one (1,024 elements of 14 modes, 64 columns:
+    180 us in chunks of 11, 156 in chunks of 8)."""
+    for ne in (256, 1024):
+        for n, nr in ((9, 16), (12, 16), (13, 48), (14, 20), (15, 4), (17, 40)):
+            for R in (16, 24, 40, 48, 64):
+                (rc, eg, nchunk, *_), = cut([(n, nr, ne, R, 0, 0)])
+                assert nchunk == 1 or not 8 < rc < 16, (n, R, ne, rc)
