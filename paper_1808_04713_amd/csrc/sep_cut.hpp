@@ -44,27 +44,32 @@ inline bool sep_fits(const SepBucket& b, int rc, bool padded) { return sep_lds(b
 // of some cover the products of others), the one with the least chunks x (tiles of
 // 16 lines + 3) is taken: a workgroup's load, store and barriers cost about three
 // tiles, and narrow chunks read pieces of cache lines (at 16 modes, where one column
-// fills a tile exactly, single columns took twice the time of eight).  Where so few
-// elements leave less than two workgroups per compute unit, a workgroup's own chain
-// counts and single columns are the faster (100 elements of 22 modes, 3 columns: 51
-// us a call in one chunk, 42 in three), unless all columns make four tiles, a wave
-// each: no longer a chain than one, and one contiguous run to read (the kernel on 256
-// elements, 2 columns: 14.2 us by single columns, 11.1 together at 17 modes, 24.2 and
-// 18.6 at 29).  Columns in whole cache lines (8) are not cut between one and two lines,
-// where every chunk shares lines with its neighbours on other XCDs (1,024 elements of
-// 14 modes, 64 columns: 180 us in chunks of 11, 156 in chunks of 8).  want > 0 fixes the width (options,
-// autotuner) where it fits a workgroup.
+// fills a tile exactly, single columns took twice the time of eight).  But
+//  - at 25 to 32 modes the stage of a solve may take 80 KiB: its 150 registers leave
+//    room for two workgroups anyway (29 modes, 8 columns of 256 elements: 64 us in
+//    chunks of 3, 45 in chunks of 4);
+//  - where so few elements leave less than two workgroups per compute unit, a
+//    workgroup's own chain counts and single columns are the faster (100 elements of 22
+//    modes, 3 columns: 51 us a call in one chunk, 42 in three), unless all columns make
+//    four tiles, a wave each: no longer a chain than one, and one contiguous run to read
+//    (the kernel on 256 elements, 2 columns: 14.2 us by single columns, 11.1 together at
+//    17 modes, 24.2 and 18.6 at 29);
+//  - columns in whole cache lines (8) are not cut between one and two lines, where
+//    every chunk shares lines with its neighbours on other XCDs (1,024 elements of 14
+//    modes, 64 columns: 180 us in chunks of 11, 156 in chunks of 8).
+// want > 0 fixes the width (options, autotuner) where it fits a workgroup.
 inline SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
   const int n = b.n, nr = b.nr;
   auto tiles = [&](int ncol) { return (n * ncol + 15) / 16; };
   SepCut c{1, 1, R, 0, 0};
+  const size_t stage = n > 24 && n <= 32 && !padded ? 80 * 1024 - SEP_EG_MAX * sizeof(SepElem) : 40 * 1024;
   if (want > 0 && sep_fits(b, std::min(want, R), padded)) {
     c.rc = std::min(want, R);
   } else {
     int64_t best = INT64_MAX;
     for (int rc = 1; rc <= std::min(R, 64); ++rc) {
       const int nchunk = (R + rc - 1) / rc;
-      if (rc > 1 && sep_lds(n, nr, rc, padded) > 40 * 1024) break;
+      if (rc > 1 && sep_lds(n, nr, rc, padded) > stage) break;
       if (rc > 1 && int64_t(b.count[0]) * nchunk < 512 && !(rc == R && tiles(rc) <= 4)) continue;
       if (R % 8 == 0 && rc > 8 && rc < 16 && rc < R) continue;
       const int64_t cost = int64_t(nchunk) * (tiles(rc) + 3);

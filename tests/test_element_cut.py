@@ -74,3 +74,16 @@ def test_cut_columns_of_whole_lines_stay_in_whole_lines(cut):
             for R in (16, 24, 40, 48, 64):
                 (rc, eg, nchunk, *_), = cut([(n, nr, ne, R, 0, 0)])
                 assert nchunk == 1 or not 8 < rc < 16, (n, R, ne, rc)
+
+
+def test_the_stage_takes_what_registers_leave_idle(cut):
+    """Of the kernels for 25 to 32 modes a compute unit's registers hold two workgroups
+    of four waves, so half of its shared memory is each one's (29 modes, 8 columns of
+    256 elements: 64 us in chunks of 3, 45 in chunks of 4); of the sampling kernel it
+    holds four."""
+    for n in range(25, 33):
+        for ne in (256, 1024):
+            (rc, eg, nchunk, threads, lds, _), = cut([(n, 16, ne, 8, 0, 0)])
+            assert rc >= 4 and 2 * (lds + STATIC) <= LDS, (n, ne)
+            (rc, eg, nchunk, threads, lds, _), = cut([(n, 16, ne, 8, 0, 1)])
+            assert 4 * (lds - STATIC) <= LDS, (n, ne)
