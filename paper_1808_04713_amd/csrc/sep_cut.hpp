@@ -36,6 +36,10 @@ inline size_t sep_lds(int n, int nr, int ncol, bool padded) {
   return (size_t(n) * n * (padded ? ncol | 1 : ncol) + size_t(nr) * ncol) * 2 * sizeof(double);
 }
 
+// whether the waves of a workgroup with one column share its rows too: the kernels of
+// two tiles of rows and none beyond (sep_splits in separable.hip)
+inline bool sep_split_rows(int n) { return n > 20 && n <= 32; }
+
 // whether rc columns of one element of any class of the bucket fit a workgroup
 inline bool sep_fits(const SepBucket& b, int rc, bool padded) { return sep_lds(b.n, b.nr, rc, padded) <= SEP_LDS_MAX; }
 
@@ -89,6 +93,11 @@ inline SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
   c.nchunk = (R + c.rc - 1) / c.rc;
   const int nt = tiles(c.rc * c.eg), rounds = (nt + 3) / 4;
   c.threads = 64 * ((nt + rounds - 1) / rounds);   // at most four waves, no more than the tiles keep busy
+  // one column of 21 to 32 modes is two tiles of lines by two of rows, a wave each: 10.4
+  // us on 256 elements of 21 modes and 12.9 at 29, where two waves of all rows took 13.2
+  // and 16.7.  Past two workgroups per compute unit the two are the faster (1,024
+  // elements of 29 modes: 24.0 us, with four 27.3)
+  if (c.rc * c.eg == 1 && sep_split_rows(n) && int64_t(b.count[0]) * c.nchunk <= 512) c.threads = 256;
   c.lds = sep_lds(n, nr, c.rc * c.eg, padded || c.eg > 1);
   return c;
 }

@@ -56,7 +56,7 @@ struct SepMat {
   double re[MT][KS], im[CPLX ? MT : 1][KS];
   double xre[XR ? XR : 1][KS], xim[CPLX && XR ? XR : 1][KS];
 
-  __device__ __forceinline__ void load(const double* __restrict__ M, int n, int ms, int ks) {
+  __device__ __forceinline__ void load(const double* __restrict__ M, int n, int ms, int ks, int m0 = 0) {
     const int l = threadIdx.x & 63, c16 = l & 15, kq = l >> 4;
     constexpr int W = CPLX ? 2 : 1;
 #pragma unroll
@@ -64,7 +64,7 @@ struct SepMat {
       const int k = 4 * q + kq, kc = min(k, n - 1);
 #pragma unroll
       for (int t = 0; t < MT; ++t) {
-        const int m = 16 * t + c16;
+        const int m = m0 + 16 * t + c16;
         const double* p = M + W * (min(m, n - 1) * ms + kc * ks);
         const bool in = m < n && k < n;
         re[t][q] = in ? p[0] : 0.0;
@@ -84,13 +84,16 @@ struct SepMat {
 
 // out(m) = sum_k M(m, k) line(k) in place on the block's nl lines; line i has its
 // entries st apart from at(i) on, read times scale(i, k) when given.
-template <int KS, int MT, int XR, bool CPLX, class At, class Sc>
+// SPLIT: 17 to 32 lines and four waves, of which wave w forms the 16 rows from
+// 16 (w >> 1) on (M holds these) of the lines of tile w & 1.
+template <bool SPLIT, int KS, int MT, int XR, bool CPLX, class At, class Sc>
 __device__ __forceinline__ void tile_products(const SepMat<KS, MT, XR, CPLX>& M, int n, int nl, double2* A, int st,
                                               At at, Sc scale, bool scaled) {
   const int l = threadIdx.x & 63, c16 = l & 15, kq = l >> 4;
-  const int nw = blockDim.x >> 6;
+  const int w = threadIdx.x >> 6, nw = SPLIT ? 2 : blockDim.x >> 6;
+  const int m0 = SPLIT ? 16 * (w >> 1) : 0;
 #pragma unroll 1
-  for (int t0 = threadIdx.x >> 6; 16 * t0 < nl; t0 += nw) {
+  for (int t0 = SPLIT ? w & 1 : w; 16 * t0 < nl; t0 += nw) {
     const int i = min(16 * t0 + c16, nl - 1);   // lanes past the last line repeat it
     double2* line = A + at(i);
     double2 s[KS];
@@ -138,12 +141,14 @@ __device__ __forceinline__ void tile_products(const SepMat<KS, MT, XR, CPLX>& M,
       ay += __shfl_xor(ay, 32, 64);
       xo[x] = make_double2(ax, ay);
     }
-    // lane l holds rows (l >> 4) + 4 v of line c16; every read of the tile is done
+    // lane l holds rows (l >> 4) + 4 v of line c16; every read of the tile is done,
+    // another wave's too where it forms the lines' other rows
+    if (SPLIT) __syncthreads();
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int m = 16 * t + kq + 4 * v;
+        const int m = m0 + 16 * t + kq + 4 * v;
         if (m < n) line[m * st] = make_double2(cr[t][v], ci[t][v]);
       }
 #pragma unroll
@@ -152,20 +157,32 @@ __device__ __forceinline__ void tile_products(const SepMat<KS, MT, XR, CPLX>& M,
   }
 }
 
+// The kernels whose one column a workgroup's four waves share by lines and rows: two
+// tiles of each (21 to 32 modes).
+constexpr bool sep_splits(int KS, int MT, int XR) { return MT == 2 && XR == 0 && KS <= 8; }
+
 // One product on the stage A (entry (ix + n iy) ld + column): along x (the lines of
 // (iy, column)) or y; M(m, k) at mat[m ms + k ks].  With dinv (along x) the entries
 // are read times 1 / D (entry (k, j) of D at k + n j).
 template <int KS, int MT, int XR, bool CPLX>
 __device__ __forceinline__ void sep_product(const double* __restrict__ mat, int ms, int ks, bool along_x, int n,
                                             int ncol, int ld, double2* A, const double2* __restrict__ dinv = nullptr) {
+  const int step = along_x ? n * ld : ld, st = along_x ? ld : n * ld;
+  if constexpr (sep_splits(KS, MT, XR)) {
+    if (ncol == 1 && blockDim.x == 256) {
+      SepMat<KS, 1, 0, CPLX> M;
+      M.load(mat, n, ms, ks, 16 * (threadIdx.x >> 7));
+      tile_products<true>(M, n, n, A, st, [&](int i) { return i * step; },
+                          [&](int i, int k) { return dinv[k + n * i]; }, dinv != nullptr);
+      return;
+    }
+  }
   SepMat<KS, MT, XR, CPLX> M;
   M.load(mat, n, ms, ks);
-  const int step = along_x ? n * ld : ld;
   const float inv = 1.0f / float(ncol);
   auto over = [&](int i) { return int((float(i) + 0.5f) * inv); };   // i / ncol (i below 2^15)
-  tile_products(M, n, n * ncol, A, along_x ? ld : n * ld,
-                [&](int i) { const int q = over(i); return q * step + (i - q * ncol); },
-                [&](int i, int k) { return dinv[k + n * over(i)]; }, dinv != nullptr);
+  tile_products<false>(M, n, n * ncol, A, st, [&](int i) { const int q = over(i); return q * step + (i - q * ncol); },
+                       [&](int i, int k) { return dinv[k + n * over(i)]; }, dinv != nullptr);
 }
 
 template <int KS, int MT, int XR>

@@ -87,3 +87,12 @@ def test_the_stage_takes_what_registers_leave_idle(cut):
             assert rc >= 4 and 2 * (lds + STATIC) <= LDS, (n, ne)
             (rc, eg, nchunk, threads, lds, _), = cut([(n, 16, ne, 8, 0, 1)])
             assert 4 * (lds - STATIC) <= LDS, (n, ne)
+
+
+def test_one_column_of_two_row_tiles_keeps_four_waves_busy(cut):
+    for n in range(17, 42):
+        for ne in (4, 256, 512, 513, 1024):
+            (rc, eg, nchunk, threads, *_), = cut([(n, 16, ne, 1, 0, 0)])
+            if eg == 1:
+                lines = (n + 15) // 16
+                assert threads == (256 if 20 < n <= 32 and ne <= 512 else 64 * lines), (n, ne)

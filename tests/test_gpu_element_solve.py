@@ -158,3 +158,22 @@ def test_a_width_that_does_not_fit_a_compute_unit():
     assert rel(a.cpu().numpy(), b.cpu().numpy()) < 1e-10
     st.close()
     su.close()
+
+
+@pytest.mark.parametrize("p", [20, 22, 23, 24, 26, 27, 28, 30, 31])
+def test_one_column_and_single_last_columns_of_two_row_tiles(p):
+    """21 to 32 modes: four waves share a workgroup's only column by lines and rows, the
+    only column of a last, narrower chunk with as many waves as the others' columns have
+    tiles.  Columns of one call against the same columns one at a time (every sum in
+    the same order: equal to the last bit) and against dense solves."""
+    w = W.small_uniform(3, p, 2.0 * p ** 0.5, l=1)
+    rng = np.random.default_rng(p)
+    for cols in (0, 2, 4):
+        s = hdp().Solver(w, tile_fdm=cols)
+        y = rng.standard_normal((s.dof, 5)) + 1j * rng.standard_normal((s.dof, 5))
+        yd = torch.from_numpy(y).cuda()
+        x = s.local_solve(yd)
+        ones = torch.cat([s.local_solve(yd[:, r:r + 1].contiguous()) for r in range(5)], dim=1)
+        assert torch.equal(x, ones), cols
+        assert rel(x.cpu().numpy(), _dense_ref(w, y)) < 1e-10, cols
+        s.close()
