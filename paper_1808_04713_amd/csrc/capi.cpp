@@ -564,7 +564,7 @@ void build_device(Handle& h, Team& team) {
       }
     }
     sc[c] = SepClass{at[0], at[1], int64_t(Dinv.size()), int64_t(Kc.size()), int64_t(V.size()), C.n, C.nr,
-                     C.m, int(rmod.size()), int(gam.size()), real[0], real[1], 0};
+                     C.m, int(rmod.size()), int(gam.size()), real[0], real[1], sep_len(C.n)};
     for (auto& v : C.Dg) { cd iv = 1.0 / v; Dinv.push_back(make_double2(iv.real(), iv.imag())); }
     for (auto& v : C.Kc.a) Kc.push_back(make_double2(v.real(), v.imag()));
     std::vector<double> t = gll_nodes(C.n), row(C.n);
@@ -643,6 +643,21 @@ void build_device(Handle& h, Team& team) {
         bk.count[eg - 1] = int(items.size()) - bk.first[eg - 1];
       }
       h.sep_buckets.push_back(bk);
+    }
+    // the same of every kernel of up to SEP_MIX_N modes together, longest first
+    h.sep_mix = SepBucket{};
+    int kernels = 0;
+    for (auto& kv : runs) kernels += kv.first <= SEP_MIX_N;
+    if (kernels > 1) {
+      SepBucket& bk = h.sep_mix;
+      bk.first[0] = int(items.size());
+      for (auto b = h.sep_buckets.rbegin(); b != h.sep_buckets.rend(); ++b) {
+        if (b->N > SEP_MIX_N) continue;
+        bk.n = std::max(bk.n, b->n);
+        bk.nr = std::max(bk.nr, b->nr);
+        for (int q = 0; q < b->count[0]; ++q) items.push_back(SepItem(items[b->first[0] + q]));
+        bk.count[0] += b->count[0];
+      }
     }
     d.sep_elem = upload(h, el);
     d.sep_items = upload(h, items);

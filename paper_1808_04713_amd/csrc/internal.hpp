@@ -129,7 +129,7 @@ struct SlotBlock {
 enum { SEP_SOLVE = 0, SEP_COARSE = 1, SEP_FULL = 2, SEP_GLL = 3 };
 struct SepClass {
   int64_t ex, ey, doff, kc, voff;
-  int n, nr, ns, roff, goff, rx, ry, pad;   // rx, ry: 1 where the eigenbasis is real
+  int n, nr, ns, roff, goff, rx, ry, N;   // rx, ry: 1 where the eigenbasis is real; N: kernel
 };
 struct SepItem {
   SepClass cls;
@@ -376,6 +376,7 @@ struct Handle {
   bool use_graphs = false;
   int fdm_rc = 0;    // right-hand sides per workgroup of the separable element solve (0: by size)
   std::vector<SepBucket> sep_buckets;
+  SepBucket sep_mix;   // the classes of all kernels of up to SEP_MIX_N modes (empty if only one)
   int slot_rb = 32;  // right-hand sides per block of the matrix-core slot operators (16, 32, 64)
   struct Tune {
     std::string kernel;

@@ -16,7 +16,7 @@ struct SepElem {
   int cmo, s0;
 };
 struct SepBucket {
-  int N = 0, n = 0, nr = 0;   // kernel (sep_len), largest n and nr
+  int N = 0, n = 0, nr = 0;   // kernel (sep_len; 0: each class's own), largest n and nr
   int first[SEP_EG_MAX] = {0}, count[SEP_EG_MAX] = {0};   // items for 1, 2, .. elements per workgroup
 };
 
@@ -100,6 +100,19 @@ inline SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
   if (c.rc * c.eg == 1 && sep_split_rows(n) && int64_t(b.count[0]) * c.nchunk <= 512) c.threads = 256;
   c.lds = sep_lds(n, nr, c.rc * c.eg, padded || c.eg > 1);
   return c;
+}
+
+// Whether the classes of several kernels of up to SEP_MIX_N modes (bucket m, cut c) run in
+// one launch.  A launch of few workgroups takes one workgroup's chain, 5 to 15 us, so a
+// kernel after the other adds up their chains; together they cost the longest, at the
+// registers of the widest kernel.  The solves of a disk's elements, separate and
+// together: 64 of degree 8 to 20, one column 42.5 and 13.4 us (one padded kernel of all
+// degrees 12.2), 372 of them at 16 columns 94 and 47; 1,644 of degree 4 to 16 at 7
+// columns (1,644 workgroups) 59 and 37, at 12 (3,288) 73 and 71, at 16 80 and 97; 712 of
+// degree 6 to 12 at 24 columns (2,136) 47.5 and 47.1, at 33 (3,560) 60 and 62.
+constexpr int SEP_MIX_N = 32, SEP_MIX_BLOCKS = 2048;
+inline bool sep_mixes(const SepBucket& m, const SepCut& c) {
+  return int64_t(m.count[0]) * c.nchunk <= SEP_MIX_BLOCKS;
 }
 
 }  // namespace hdp

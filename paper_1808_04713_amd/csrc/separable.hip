@@ -169,7 +169,7 @@ __device__ __forceinline__ void sep_product(const double* __restrict__ mat, int 
                                             int ncol, int ld, double2* A, const double2* __restrict__ dinv = nullptr) {
   const int step = along_x ? n * ld : ld, st = along_x ? ld : n * ld;
   if constexpr (sep_splits(KS, MT, XR)) {
-    if (ncol == 1 && blockDim.x == 256) {
+    if (ncol == 1 && blockDim.x == 256) {   // (n is past 16: two tiles of lines)
       SepMat<KS, 1, 0, CPLX> M;
       M.load(mat, n, ms, ks, 16 * (threadIdx.x >> 7));
       tile_products<true>(M, n, n, A, st, [&](int i) { return i * step; },
@@ -254,10 +254,9 @@ struct SepArgs {
 //   K_e T_e w - kx; out = A~^-1 (y - E_R mu) = A~^-1 y - G mu.
 // SEP_GLL: field = V X V^T at the GLL nodes, one contiguous field per column.
 template <int KS, int MT, int XR, int MODE>
-__global__ void __launch_bounds__(256) k_sep(SepArgs g, const double* __restrict__ mats, const double2* __restrict__ Dinv,
-                                             const double2* __restrict__ Kc, const double* __restrict__ gll) {
-  extern __shared__ double2 sm[];
-  __shared__ SepElem se[SEP_EG];
+__device__ __forceinline__ void sep_block(const SepArgs& g, const double* __restrict__ mats,
+                                          const double2* __restrict__ Dinv, const double2* __restrict__ Kc,
+                                          const double* __restrict__ gll, double2* sm, SepElem* se) {
   const SepItem I = g.items[blockIdx.x / g.nchunk];
   const int r0 = int(blockIdx.x % g.nchunk) * g.RC;
   const int R = g.R, rc = min(g.RC, g.cols - r0);
@@ -391,45 +390,72 @@ __global__ void __launch_bounds__(256) k_sep(SepArgs g, const double* __restrict
   }
 }
 
-template <int KS, int MT, int XR>
-void launch_n(int mode, const SepArgs& a, dim3 grid, int threads, size_t lds, const Handle& h, hipStream_t s) {
-  const auto& d = h.d;
-#define HDP_SEP(M) \
-  hipLaunchKernelGGL((k_sep<KS, MT, XR, M>), grid, dim3(threads), lds, s, a, d.sep_mat, d.Dinv, d.Kc, d.sep_gll)
-  if (mode == SEP_SOLVE) HDP_SEP(SEP_SOLVE);
-  else if (mode == SEP_COARSE) HDP_SEP(SEP_COARSE);
-  else if (mode == SEP_FULL) HDP_SEP(SEP_FULL);
-  else HDP_SEP(SEP_GLL);
-#undef HDP_SEP
+template <int KS, int MT, int XR, int MODE>
+__global__ void __launch_bounds__(256) k_sep(SepArgs g, const double* __restrict__ mats, const double2* __restrict__ Dinv,
+                                             const double2* __restrict__ Kc, const double* __restrict__ gll) {
+  extern __shared__ double2 sm[];
+  __shared__ SepElem se[SEP_EG];
+  sep_block<KS, MT, XR, MODE>(g, mats, Dinv, Kc, gll, sm, se);
 }
 
-void launch_sep(const Handle& h, int mode, SepArgs a, int want, hipStream_t s) {
+// The kernels: the largest n of each, its steps of 4 summation indices, tiles of 16 rows
+// and rows beyond them.
+#define HDP_SEP_TO_32(CASE) \
+  CASE(4, 1, 1, 0) CASE(8, 2, 1, 0) CASE(12, 3, 1, 0) CASE(16, 4, 1, 0) CASE(18, 5, 1, 2) CASE(20, 5, 1, 4) \
+  CASE(24, 6, 2, 0) CASE(28, 7, 2, 0) CASE(32, 8, 2, 0)
+#define HDP_SEP_ABOVE_32(CASE) CASE(34, 9, 2, 2) CASE(36, 9, 2, 4) CASE(40, 10, 3, 0) CASE(44, 11, 3, 0)
+
+// Elements of uneven degree, each by the kernel of its class: a launch per kernel leaves
+// most of the chip idle where each has few workgroups (sep_mixes).
+template <int MODE>
+__global__ void __launch_bounds__(256) k_sep_mix(SepArgs g, const double* __restrict__ mats,
+                                                 const double2* __restrict__ Dinv, const double2* __restrict__ Kc,
+                                                 const double* __restrict__ gll) {
+  extern __shared__ double2 sm[];
+  __shared__ SepElem se[SEP_EG];
+  switch (g.items[blockIdx.x / g.nchunk].cls.N) {
+#define HDP_SEP_CASE(V, KS, MT, XR) \
+  case V: sep_block<KS, MT, XR, MODE>(g, mats, Dinv, Kc, gll, sm, se); break;
+    HDP_SEP_TO_32(HDP_SEP_CASE)
+#undef HDP_SEP_CASE
+  }
+}
+
+template <int MODE>
+void launch_bucket(const SepBucket& b, SepArgs a, const SepCut& c, const Handle& h, hipStream_t s) {
+  const auto& d = h.d;
+  a.items = d.sep_items + b.first[c.eg - 1];
+  a.nchunk = c.nchunk;
+  a.RC = c.rc;
+  const int64_t blocks = int64_t(b.count[c.eg - 1]) * c.nchunk;
+  if (blocks > 0x7fffffff) fail(HDP_E_ARG, "element solve: too many columns");
+  const dim3 grid{unsigned(blocks)}, block{unsigned(c.threads)};
+  switch (b.N) {
+#define HDP_SEP_CASE(V, KS, MT, XR)                                                                             \
+  case V:                                                                                                       \
+    hipLaunchKernelGGL((k_sep<KS, MT, XR, MODE>), grid, block, c.lds, s, a, d.sep_mat, d.Dinv, d.Kc, d.sep_gll); \
+    break;
+    HDP_SEP_TO_32(HDP_SEP_CASE) HDP_SEP_ABOVE_32(HDP_SEP_CASE)
+#undef HDP_SEP_CASE
+    default: hipLaunchKernelGGL(k_sep_mix<MODE>, grid, block, c.lds, s, a, d.sep_mat, d.Dinv, d.Kc, d.sep_gll);
+  }
+  HIPCHECK(hipGetLastError());
+}
+
+template <int MODE>
+void launch_sep(const Handle& h, SepArgs a, int want, hipStream_t s) {
   const auto& d = h.d;
   a.elem = d.sep_elem;
   a.r_modes = d.r_modes;
   a.gam_modes = d.gam_modes;
-  for (const SepBucket& b : h.sep_buckets) {
-    const SepCut c = sep_cut(b, a.cols, want, mode == SEP_GLL);
-    a.items = d.sep_items + b.first[c.eg - 1];
-    a.nchunk = c.nchunk;
-    a.RC = c.rc;
-    const int64_t blocks = int64_t(b.count[c.eg - 1]) * c.nchunk;
-    if (blocks > 0x7fffffff) fail(HDP_E_ARG, "element solve: too many columns");
-    const dim3 grid{unsigned(blocks)};
-    // N: the largest n of a kernel's steps of 4 summation indices, tiles of 16 rows
-    // and rows beyond them
-    switch (b.N) {
-#define HDP_SEP_CASE(V, KS, MT, XR) \
-  case V: launch_n<KS, MT, XR>(mode, a, grid, c.threads, c.lds, h, s); break;
-      HDP_SEP_CASE(4, 1, 1, 0) HDP_SEP_CASE(8, 2, 1, 0) HDP_SEP_CASE(12, 3, 1, 0) HDP_SEP_CASE(16, 4, 1, 0)
-      HDP_SEP_CASE(18, 5, 1, 2) HDP_SEP_CASE(20, 5, 1, 4) HDP_SEP_CASE(24, 6, 2, 0)
-      HDP_SEP_CASE(28, 7, 2, 0) HDP_SEP_CASE(32, 8, 2, 0) HDP_SEP_CASE(34, 9, 2, 2) HDP_SEP_CASE(36, 9, 2, 4)
-      HDP_SEP_CASE(40, 10, 3, 0) HDP_SEP_CASE(44, 11, 3, 0)
-#undef HDP_SEP_CASE
-      default: fail(HDP_E_UNSUPPORTED, "element solve: degree out of range");
-    }
-    HIPCHECK(hipGetLastError());
+  bool mixed = false;
+  if (h.sep_mix.count[0] > 0) {
+    const SepCut c = sep_cut(h.sep_mix, a.cols, want, MODE == SEP_GLL);
+    mixed = sep_mixes(h.sep_mix, c);
+    if (mixed) launch_bucket<MODE>(h.sep_mix, a, c, h, s);
   }
+  for (const SepBucket& b : h.sep_buckets)
+    if (!mixed || b.N > SEP_MIX_N) launch_bucket<MODE>(b, a, sep_cut(b, a.cols, want, MODE == SEP_GLL), h, s);
 }
 
 }  // namespace
@@ -452,7 +478,7 @@ void launch_sep_solve(const Handle& h, const double2* in, double2* out, int R, h
   a.in = in;
   a.out = out;
   a.R = a.cols = R;
-  launch_sep(h, SEP_SOLVE, a, h.fdm_rc, s);
+  launch_sep<SEP_SOLVE>(h, a, h.fdm_rc, s);
 }
 
 void launch_sep_coarse(const Handle& h, const double2* in, int R, hipStream_t s, const double2* nu, double2* xslot,
@@ -466,7 +492,7 @@ void launch_sep_coarse(const Handle& h, const double2* in, int R, hipStream_t s,
   a.Xr = h.d.cmX;
   a.GL = h.d.cmA;
   a.xslot = xslot;
-  launch_sep(h, SEP_COARSE, a, rc > 0 ? rc : h.fdm_rc, s);
+  launch_sep<SEP_COARSE>(h, a, rc > 0 ? rc : h.fdm_rc, s);
 }
 
 void launch_sep_full(const Handle& h, const double2* in, double2* out, int R, hipStream_t s, const double2* nu,
@@ -480,7 +506,7 @@ void launch_sep_full(const Handle& h, const double2* in, double2* out, int R, hi
   a.slot_coef = h.d.slot_coef;
   a.Xr = h.d.cmX;
   a.kx = kx;
-  launch_sep(h, SEP_FULL, a, rc > 0 ? rc : h.fdm_rc, s);
+  launch_sep<SEP_FULL>(h, a, rc > 0 ? rc : h.fdm_rc, s);
 }
 
 void launch_gll(const Handle& h, const double2* X, double2* field, int R, int64_t rhs_stride, int nrhs_out,
@@ -491,7 +517,7 @@ void launch_gll(const Handle& h, const double2* X, double2* field, int R, int64_
   a.R = R;
   a.cols = nrhs_out;
   a.rhs_stride = rhs_stride;
-  launch_sep(h, SEP_GLL, a, 0, s);
+  launch_sep<SEP_GLL>(h, a, 0, s);
 }
 
 }  // namespace hdp

@@ -2,7 +2,8 @@
 // run by tests/test_element_cut.py.
 //
 // Input, a line each: n nr elements R want padded, for a bucket of one class; output:
-// rc eg nchunk threads dynamic_bytes fits, the last for want columns of one element.
+// rc eg nchunk threads dynamic_bytes fits mixes: fits for want columns of one element,
+// mixes for a bucket of several kernels' classes.
 #include <cstdio>
 
 #include "../paper_1808_04713_amd/csrc/sep_cut.hpp"
@@ -15,7 +16,8 @@ int main() {
     b.nr = nr;
     for (int eg = 1; eg <= hdp::SEP_EG_MAX; ++eg) b.count[eg - 1] = (ne + eg - 1) / eg;
     const hdp::SepCut c = hdp::sep_cut(b, R, want, padded != 0);
-    std::printf("%d %d %d %d %zu %d\n", c.rc, c.eg, c.nchunk, c.threads, c.lds, int(hdp::sep_fits(b, want, padded != 0)));
+    std::printf("%d %d %d %d %zu %d %d\n", c.rc, c.eg, c.nchunk, c.threads, c.lds,
+                int(hdp::sep_fits(b, want, padded != 0)), int(hdp::sep_mixes(b, c)));
   }
   return 0;
 }

@@ -22,7 +22,7 @@ def cut(tmp_path_factory):
     subprocess.run([cxx, "-O1", "-std=c++17", os.path.join(ROOT, "tests", "element_cut.cpp"), "-o", exe], check=True)
 
     def run(cases):
-        """[(n, nr, elements, R, want, padded)] -> [(rc, eg, nchunk, threads, bytes, fits)]"""
+        """[(n, nr, elements, R, want, padded)] -> [(rc, eg, nchunk, threads, bytes, fits, mixes)]"""
         text = "\n".join(" ".join(str(int(v)) for v in c) for c in cases) + "\n"
         r = subprocess.run([exe], input=text, capture_output=True, text=True, check=True)
         return [tuple(int(v) for v in line.split()) for line in r.stdout.splitlines()]
@@ -37,7 +37,7 @@ def test_every_cut_fits_a_compute_unit(cut):
              if nr <= 4 * (n - 1) for ne in (4, 1024) for R in COLUMNS for want in (0, 1, 2, 4, 8, 16)
              for padded in (0, 1)]
     assert (24, 64, 1024, 16, 16, 0) in cases
-    for c, (rc, eg, nchunk, threads, lds, fits) in zip(cases, cut(cases)):
+    for c, (rc, eg, nchunk, threads, lds, fits, mixes) in zip(cases, cut(cases)):
         assert lds + STATIC <= LDS, (c, rc, lds)
         assert 1 <= rc <= c[3] and nchunk * rc >= c[3] > (nchunk - 1) * rc, c
         assert 64 <= threads <= 256 and threads % 64 == 0, c
@@ -83,9 +83,9 @@ def test_the_stage_takes_what_registers_leave_idle(cut):
     holds four."""
     for n in range(25, 33):
         for ne in (256, 1024):
-            (rc, eg, nchunk, threads, lds, _), = cut([(n, 16, ne, 8, 0, 0)])
+            (rc, eg, nchunk, threads, lds, *_), = cut([(n, 16, ne, 8, 0, 0)])
             assert rc >= 4 and 2 * (lds + STATIC) <= LDS, (n, ne)
-            (rc, eg, nchunk, threads, lds, _), = cut([(n, 16, ne, 8, 0, 1)])
+            (rc, eg, nchunk, threads, lds, *_), = cut([(n, 16, ne, 8, 0, 1)])
             assert 4 * (lds - STATIC) <= LDS, (n, ne)
 
 
@@ -96,3 +96,11 @@ def test_one_column_of_two_row_tiles_keeps_four_waves_busy(cut):
             if eg == 1:
                 lines = (n + 15) // 16
                 assert threads == (256 if 20 < n <= 32 and ne <= 512 else 64 * lines), (n, ne)
+
+
+def test_few_workgroups_of_several_kernels_share_a_launch(cut):
+    """13 elements of 1 to 32 modes per direction in one launch up to 2,048 workgroups,
+    kernel by kernel beyond."""
+    mixes = {R: cut([(32, 16, 13, R, 0, 0)])[0][6] for R in (1, 64, 300, 720)}
+    assert mixes == {1: 1, 64: 1, 300: 1, 720: 0}
+    assert [cut([(17, 16, ne, 1, 0, 0)])[0][6] for ne in (2048, 2049)] == [1, 0]

@@ -177,3 +177,27 @@ def test_one_column_and_single_last_columns_of_two_row_tiles(p):
         assert torch.equal(x, ones), cols
         assert rel(x.cpu().numpy(), _dense_ref(w, y)) < 1e-10, cols
         s.close()
+
+
+def _every_kernel():
+    """16 elements of 16 kernels or more: the smaller ones' few workgroups run in one
+    launch, those of more than 32 modes in their own."""
+    w = W.small_uniform(4, 6, 9.0, l=1)
+    w["degree"] = np.array([1, 3, 5, 9, 12, 15, 16, 18, 20, 22, 26, 28, 31, 33, 35, 37])
+    return w
+
+
+@pytest.mark.parametrize("R", [1, 2, 5, 64, 720])
+def test_local_solve_of_every_kernel_in_one_mesh(R):
+    """Columns from one to so many that the small kernels run one after the other (2,048
+    workgroups); the tolerance is cond(E_x) cond(E_y) eps."""
+    w = _every_kernel()
+    s = hdp().Solver(w)
+    rng = np.random.default_rng(R)
+    y = rng.standard_normal((s.dof, R)) + 1j * rng.standard_normal((s.dof, R))
+    x = s.local_solve(torch.from_numpy(y).cuda()).cpu().numpy()
+    ref = _dense_ref(w, y)
+    off = np.concatenate([[0], np.cumsum((np.asarray(w["degree"]) + 1) ** 2)])
+    for a, b in zip(off[:-1], off[1:]):
+        assert rel(x[a:b], ref[a:b]) < 1e-10
+    s.close()
