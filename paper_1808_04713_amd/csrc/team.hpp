@@ -9,7 +9,6 @@
 #include <functional>
 #include <memory>
 #include <mutex>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -19,9 +18,10 @@ class Team {
  public:
   Team() {
     const int n = int(std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
+    threads_.reserve(n);
     try {
       for (int t = 1; t < n; ++t) threads_.emplace_back([this] { loop(); });
-    } catch (const std::system_error&) {   // fewer threads, down to the caller alone
+    } catch (const std::exception&) {   // no thread or no memory for it: fewer, down to the caller alone
     }
   }
   ~Team() {
