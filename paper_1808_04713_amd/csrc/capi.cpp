@@ -1003,12 +1003,12 @@ void apply_P_ws(Handle& h, const double2* v, double2* u, int R, int prec, const 
     if (prec == HDP_FP64) launch_slot_apply<double2>(h, 1, v, w.slot, nullptr, R, s);
     else launch_slot_apply<float2>(h, 1, w.vf, w.slot_f, nullptr, R, s);
   }
-  if (h.nh > 0) {
+  if (h.nh > 0 && h.hb_largest <= HB_GATHER) {
     // hanging rows: u = X^-1 (C_1 S C_1^T s + Y_2 s)
     Timed t(h, KF_HBLOCK, nsl * cw + nl * c + 2 * hb_bytes + 2 * nh * c, 2.0 * 2 * h.hb_xinv.size() * 2 * R);
-    if (prec == HDP_FP64 ? launch_hgather<double2>(h, w.slot, w.pv, u, R, s)
-                         : launch_hgather<float2>(h, w.slot_f, w.pv, u, R, s))
-      return;
+    if (prec == HDP_FP64) launch_hgather<double2>(h, w.slot, w.pv, u, R, s);
+    else launch_hgather<float2>(h, w.slot_f, w.pv, u, R, s);
+    return;
   }
   {
     Timed t(h, KF_ROWGATHER, nsl * cw + nl * c, 0);

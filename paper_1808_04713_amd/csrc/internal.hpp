@@ -117,6 +117,11 @@ constexpr int STATUS_SLOTS = 4;
 // (2,048 unknowns at one column)
 constexpr int DOTS_FOLD = 8;
 
+// rows of the largest hanging-edge block up to which X^-1 (u + Y_2 s) runs with the row
+// gather, a workgroup per block (two products of four rows a wave); longer blocks keep a
+// wave per row, in two launches after the gather
+constexpr int HB_GATHER = 16;
+
 // Per-block record of the slot kernels (blocks follow the class-grouped element
 // order): the element, its class, slot and coarse-mode offsets and counts, and
 // the class's operator offsets, so that a block starts with one load.
@@ -233,7 +238,7 @@ struct Handle {
   std::vector<int> hb_off, hb_rows;
   std::vector<int64_t> hb_moff;
   std::vector<double> hb_xinv, hb_y2;
-  int nh = 0;
+  int nh = 0, hb_largest = 0;   // their rows in all, and of the largest block
   // class-sorted element order and launch tables
   std::vector<int> order;         // elements grouped by class
   // per degree n: Gauss-Legendre rule with n+40 nodes and the vertex basis there

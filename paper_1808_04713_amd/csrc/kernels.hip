@@ -2625,22 +2625,16 @@ void launch_hcopy(const Handle& h, const double2* v, double2* y, int R, hipStrea
   HIPCHECK(hipGetLastError());
 }
 
-// a workgroup per block of up to 16 rows, two products of four rows a wave; longer
-// blocks keep their waves per row, in two launches
 template <class T2>
-bool launch_hgather(const Handle& h, const T2* src, const double2* sv, double2* u, int R, hipStream_t s) {
+void launch_hgather(const Handle& h, const T2* src, const double2* sv, double2* u, int R, hipStream_t s) {
   const auto& d = h.d;
   const int nblk = int(h.hb_off.size()) - 1, RB = hb_cols(R), nch = (R + RB - 1) / RB;
-  int most = 0;
-  for (int b = 0; b < nblk; ++b) most = std::max(most, h.hb_off[b + 1] - h.hb_off[b]);
-  const size_t lds = size_t(most) * RB * sizeof(double2);
-  if (most > 16) return false;
+  const size_t lds = size_t(h.hb_largest) * RB * sizeof(double2);
   const int64_t count = int64_t(h.nlam) * R;
   const int copies = int(nblocks(count));
   hipLaunchKernelGGL((k_hgather<T2>), dim3(copies + nblk * nch), dim3(NT), lds, s, count, copies, d.hb_of, d.row_slot,
                      d.row_coef, d.row_xinv, src, d.hb_off, d.hb_rows, d.hb_moff, d.hb_xinv, d.hb_y2, sv, u, R, RB);
   HIPCHECK(hipGetLastError());
-  return true;
 }
 
 void launch_hblock(const Handle& h, bool y2, const double2* x, bool in_gather, const double2* add, double2* y,
@@ -2653,8 +2647,8 @@ void launch_hblock(const Handle& h, bool y2, const double2* x, bool in_gather, c
   HIPCHECK(hipGetLastError());
 }
 
-template bool launch_hgather<double2>(const Handle&, const double2*, const double2*, double2*, int, hipStream_t);
-template bool launch_hgather<float2>(const Handle&, const float2*, const double2*, double2*, int, hipStream_t);
+template void launch_hgather<double2>(const Handle&, const double2*, const double2*, double2*, int, hipStream_t);
+template void launch_hgather<float2>(const Handle&, const float2*, const double2*, double2*, int, hipStream_t);
 template void launch_slot_apply<double2>(const Handle&, int, const double2*, double2*, double2*, int, hipStream_t);
 template void launch_slot_apply<float2>(const Handle&, int, const float2*, float2*, float2*, int, hipStream_t);
 template void launch_slot_coarse<double2>(const Handle&, const double2*, const double2*, double2*, int, hipStream_t);

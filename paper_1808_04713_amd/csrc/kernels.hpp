@@ -44,9 +44,9 @@ void launch_assemble(const Handle& h, const T2* GL, const double2* Bfull, const 
 // y = X^-1 v (a copy but on the hanging rows' blocks)
 void launch_hcopy(const Handle& h, const double2* v, double2* y, int R, hipStream_t s);
 // u = the preconditioner's row gather of src, on the hanging rows X^-1 (that + Y_2 sv);
-// false: the blocks are too large for one launch
+// blocks of at most HB_GATHER rows
 template <class T2>
-bool launch_hgather(const Handle& h, const T2* src, const double2* sv, double2* u, int R, hipStream_t s);
+void launch_hgather(const Handle& h, const T2* src, const double2* sv, double2* u, int R, hipStream_t s);
 // Dense blocks over the hanging dual rows: y = add + M x with M = X^-1 (y2 false) or Y_2;
 // x gathered from a dual vector (in_gather) or compact [nh][R]; y scattered or compact
 void launch_hblock(const Handle& h, bool y2, const double2* x, bool in_gather, const double2* add, double2* y,

@@ -623,6 +623,8 @@ void build_hanging_blocks(Handle& h) {
     h.hb_moff.push_back(int64_t(h.hb_xinv.size()));
   }
   h.nh = int(h.hb_rows.size());
+  h.hb_largest = 0;
+  for (size_t b = 0; b + 1 < h.hb_off.size(); ++b) h.hb_largest = std::max(h.hb_largest, h.hb_off[b + 1] - h.hb_off[b]);
 }
 
 }  // namespace

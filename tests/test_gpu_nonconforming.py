@@ -246,3 +246,43 @@ def test_true_residual_warning_on_decayed_hanging_rows():
             assert st["true_residual"] > 1e-3
         else:
             assert st["true_residual"] < 1e-6
+
+
+@pytest.mark.parametrize("mesh", ["small_blocks", "large_blocks"])
+def test_profile_counts_the_hanging_blocks_once(mesh):
+    """The blocks' two steps of a preconditioner call are two records of the profile,
+    whichever kernels run them; with large blocks the row gather is a third, of its
+    own family."""
+    lv = W.refine_where(W.morton_leaves(2, 2), 0, 1, 0, 1, 2, 2, lambda x, y: (x < 0.5) & (y < 0.5), 2)
+    p = 18 if mesh == "large_blocks" else 3   # blocks of 136 and of 16 rows
+    w = dict(domain=(0.0, 1.0, 0.0, 1.0), base=(2, 2), leaves=lv, degree=np.full(len(lv), p), k=6.0, l=1,
+             bc="impedance", eps_r=np.ones(len(lv)), discard_tol=0.0)
+    s = hdp().Solver(w, max_rhs=4, max_iter=10)
+    v = torch.ones((s.n_lambda, 3), dtype=torch.complex128, device="cuda")
+    s.profile(True)
+    for _ in range(5):
+        s.apply_precond(v)
+    n = {t["name"]: t["launches"] for t in s.kernel_times()}
+    s.profile(False)
+    assert n["hanging_blocks"] == 10
+    assert n.get("row_gather", 0) == (5 if mesh == "large_blocks" else 0)
+    s.close()
+
+
+@pytest.mark.parametrize("R", [2, 3, 5, 8, 17, 33])
+@pytest.mark.parametrize("base,p,passes", [(2, 3, 2), (3, 4, 1), (2, 3, 1)])
+def test_preconditioner_with_blocks_of_up_to_16_rows(base, p, passes, R):
+    """Blocks of 16, 12 and 8 rows, whose products share the row gather's launch, at column
+    counts beside multiples of the four a wave takes, against one column at a time."""
+    lv = W.refine_where(W.morton_leaves(base, base), 0, 1, 0, 1, base, base, lambda x, y: (x < 0.5) & (y < 0.5), passes)
+    w = dict(domain=(0.0, 1.0, 0.0, 1.0), base=(base, base), leaves=lv, degree=np.full(len(lv), p), k=6.0, l=1,
+             bc="impedance", eps_r=np.ones(len(lv)), discard_tol=0.0)
+    s = hdp().Solver(w, max_rhs=64, max_iter=10)
+    rng = np.random.default_rng(R)
+    v = torch.from_numpy(rng.standard_normal((s.n_lambda, R)) + 1j * rng.standard_normal((s.n_lambda, R))).cuda()
+    for precision, tol in (("fp64", 1e-12), ("mixed", 1e-5)):
+        got = s.apply_precond(v, precision).cpu().numpy()
+        for r in range(R):
+            one = s.apply_precond(v[:, r:r + 1].contiguous()).cpu().numpy()
+            assert rel(got[:, r], one[:, 0]) < tol, (precision, r)
+    s.close()
