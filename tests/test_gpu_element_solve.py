@@ -201,3 +201,36 @@ def test_local_solve_of_every_kernel_in_one_mesh(R):
     for a, b in zip(off[:-1], off[1:]):
         assert rel(x[a:b], ref[a:b]) < 1e-10
     s.close()
+
+
+@pytest.mark.parametrize("p", [27, 31, 33, 35, 36, 39, 40])
+def test_local_solve_at_the_edges_of_the_largest_kernels(p):
+    """The numbers of modes above 24 at which a kernel's last step, tile or row is full or
+    begins, up to the largest degree, on corner, side and interior elements (complex,
+    mixed and real eigenbases), one column and five; cond(E_x) cond(E_y) eps."""
+    w = W.small_uniform(3, p, 2.0 * p ** 0.5, l=1)
+    s = hdp().Solver(w)
+    rng = np.random.default_rng(p)
+    y = rng.standard_normal((s.dof, 5)) + 1j * rng.standard_normal((s.dof, 5))
+    yd = torch.from_numpy(y).cuda()
+    x = torch.cat([s.local_solve(yd), s.local_solve(yd[:, :1].contiguous())], dim=1).cpu().numpy()
+    ref = _dense_ref(w, y)
+    assert rel(x[:, :5], ref) < 1e-10
+    assert rel(x[:, 5], ref[:, 0]) < 1e-10
+    s.close()
+
+
+def test_interface_rhs_and_field_above_36_modes():
+    """Degrees 40, 36, 38 and 9: the coarse pass, the corrected solve and the GLL sampling
+    of the kernels of three row tiles, beside a small one, against the literal oracle."""
+    w = W.small_uniform(2, 9, 5.0, l=2)
+    w["degree"] = np.array([40, 36, 38, 9])
+    disc = pb.Discretisation(w)
+    D = dp.LiteralDP(disc, pb.coarse_order(w, disc.mesh))
+    s = hdp().Solver(w, tol=1e-12, max_iter=300)
+    kind, vals = hdp().rhs_values(w)
+    assert rel(s.interface_rhs(kind, vals).cpu().numpy()[:, 0], D.g) < 1e-11
+    field, st = s.solve(kind, vals)
+    ref = np.concatenate(pb.gll_field(disc.mesh, disc.degrees, D.solve(tol=1e-12, max_iter=300)))
+    assert rel(field.cpu().numpy()[0], ref) < 1e-10
+    s.close()
