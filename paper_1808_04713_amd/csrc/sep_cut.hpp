@@ -43,7 +43,12 @@ inline bool sep_split_rows(int n) { return n > 20 && n <= 32; }
 // whether rc columns of one element of any class of the bucket fit a workgroup
 inline bool sep_fits(const SepBucket& b, int rc, bool padded) { return sep_lds(b.n, b.nr, rc, padded) <= SEP_LDS_MAX; }
 
-// The widest classes of a bucket decide (n, nr its largest).  Of the widths whose
+// workgroups of four waves that a compute unit's registers hold of the solves' kernels
+inline int sep_resident(int n) { return n <= 16 ? 4 : n <= 18 ? 3 : n <= 20 ? 2 : n <= 24 ? 3 : n <= 32 ? 2 : 1; }
+
+// The widest classes of a bucket decide (n, nr its largest).
+//
+// Many workgroups: of the widths whose
 // stage stays within 40 KiB (four workgroups per compute unit, so that the loads
 // of some cover the products of others), the one with the least chunks x (tiles of
 // 16 lines + 3) is taken: a workgroup's load, store and barriers cost about three
@@ -52,42 +57,56 @@ inline bool sep_fits(const SepBucket& b, int rc, bool padded) { return sep_lds(b
 //  - at 25 to 32 modes the stage of a solve may take 80 KiB: its 150 registers leave
 //    room for two workgroups anyway (29 modes, 8 columns of 256 elements: 64 us in
 //    chunks of 3, 45 in chunks of 4);
-//  - where so few elements leave less than two workgroups per compute unit, a
-//    workgroup's own chain counts and single columns are the faster (100 elements of 22
-//    modes, 3 columns: 51 us a call in one chunk, 42 in three), unless all columns make
-//    four tiles, a wave each: no longer a chain than one, and one contiguous run to read
-//    (the kernel on 256 elements, 2 columns: 14.2 us by single columns, 11.1 together at
-//    17 modes, 24.2 and 18.6 at 29);
+//  - two workgroups per compute unit have to remain;
 //  - columns in whole cache lines (8) are not cut between one and two lines, where
 //    every chunk shares lines with its neighbours on other XCDs (1,024 elements of 14
 //    modes, 64 columns: 180 us in chunks of 11, 156 in chunks of 8).
+//
+// Few workgroups, all at work at once: what counts is one's own chain, and four tiles, a
+// wave each, are no longer a chain than one.  So
+//  - all columns together where they make four tiles, one contiguous run to read (256
+//    elements, 2 columns: 14.2 us by single columns, 11.1 together at 17 modes, 24.2
+//    and 18.6 at 29);
+//  - else single columns up to one per compute unit; at 21 to 32 modes, where the four
+//    waves share a column's rows as well, up to two (100 elements of 29 modes, 5 columns:
+//    22.9 us, in twos 26.0), and two columns up to one (16 elements: 13.6 us apart, 16.7
+//    together);
+//  - else the fewest chunks of at most four tiles (100 elements, 8 columns: 11.4 us in
+//    single columns, 9.9 in fours at 14 modes; 27.2 and 21.2 in twos at 22).
 // want > 0 fixes the width (options, autotuner) where it fits a workgroup.
 inline SepCut sep_cut(const SepBucket& b, int R, int want, bool padded) {
   const int n = b.n, nr = b.nr;
   auto tiles = [&](int ncol) { return (n * ncol + 15) / 16; };
   SepCut c{1, 1, R, 0, 0};
+  const int64_t singles = int64_t(b.count[0]) * R;
+  const int one = std::max(1, 64 / n), chunks = (R + one - 1) / one;   // columns in four tiles
   const size_t stage = n > 24 && n <= 32 && !padded ? 80 * 1024 - SEP_EG_MAX * sizeof(SepElem) : 40 * 1024;
-  if (want > 0 && sep_fits(b, std::min(want, R), padded)) {
+  const bool fixed = want > 0 && sep_fits(b, std::min(want, R), padded);
+  if (fixed) {
     c.rc = std::min(want, R);
+  } else if (R > one ? singles <= (sep_split_rows(n) ? 512 : 256) : singles <= 256 && sep_split_rows(n)) {
+    c.rc = 1;
+  } else if (int64_t(b.count[0]) * chunks < 256 * sep_resident(n)) {
+    c.rc = (R + chunks - 1) / chunks;
   } else {
     int64_t best = INT64_MAX;
     for (int rc = 1; rc <= std::min(R, 64); ++rc) {
       const int nchunk = (R + rc - 1) / rc;
       if (rc > 1 && sep_lds(n, nr, rc, padded) > stage) break;
-      if (rc > 1 && int64_t(b.count[0]) * nchunk < 512 && !(rc == R && tiles(rc) <= 4)) continue;
+      if (rc > 1 && int64_t(b.count[0]) * nchunk < 512) continue;
       if (R % 8 == 0 && rc > 8 && rc < 16 && rc < R) continue;
       const int64_t cost = int64_t(nchunk) * (tiles(rc) + 3);
       if (cost < best) { best = cost; c.rc = rc; }
     }
-    if (c.rc == R) {
-      // several elements of a class share a workgroup, as long as some 512
-      // workgroups (two per compute unit) remain
-      double per = tiles(R);
-      for (int eg = 2; eg <= SEP_EG_MAX; ++eg) {
-        if (sep_lds(n, nr, R * eg, true) > 40 * 1024 || b.count[eg - 1] < 512) break;
-        const double p = double(tiles(R * eg)) / eg;
-        if (p < per) { per = p; c.eg = eg; }
-      }
+  }
+  if (c.rc == R && !fixed) {
+    // several elements of a class share a workgroup, as long as some 512
+    // workgroups (two per compute unit) remain
+    double per = tiles(R);
+    for (int eg = 2; eg <= SEP_EG_MAX; ++eg) {
+      if (sep_lds(n, nr, R * eg, true) > 40 * 1024 || b.count[eg - 1] < 512) break;
+      const double p = double(tiles(R * eg)) / eg;
+      if (p < per) { per = p; c.eg = eg; }
     }
   }
   c.nchunk = (R + c.rc - 1) / c.rc;

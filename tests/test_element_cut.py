@@ -51,18 +51,25 @@ def test_the_autotuner_is_told_which_widths_fit(cut):
 
 
 
-def test_few_columns_on_few_elements_stay_together(cut):
-    """All columns of an element as one chunk read one contiguous run; four tiles of 16
-    lines, a wave each, take no longer than one, whatever the number of workgroups (256
-    elements of 29 modes, 2 columns: 24 us in two chunks, 18 in one)."""
+def test_few_workgroups_take_one_round_of_tiles(cut):
+    """Where all workgroups are at work at once, four tiles of 16 lines, a wave each, are
+    no longer a chain than one: columns that make four tiles stay together, more go by
+    single columns up to one per compute unit (of 21 to 32 modes, whose rows four waves
+    share, up to two, and two columns up to one), else in the fewest chunks of four
+    tiles."""
+    resident = {9: 4, 13: 4, 17: 3, 20: 2, 21: 3, 25: 2, 32: 2}
     for ne in (4, 16, 100, 256):
-        for n, nr in ((9, 16), (13, 48), (17, 40), (21, 16), (25, 64), (32, 124)):
-            for R in range(2, 8):
-                (rc, eg, nchunk, *_), = cut([(n, nr, ne, R, 0, 0)])
-                if n * R <= 64 and (n * n + nr) * R * 16 <= 40 * 1024:
-                    assert (rc, nchunk) == (R, 1), (n, R, ne)
-                elif ne * nchunk < 512:   # else single columns where workgroups are few
+        for n, wgs in resident.items():
+            one = 64 // n
+            for R in COLUMNS:
+                (rc, eg, nchunk, *_), = cut([(n, 16, ne, R, 0, 0)])
+                shared = 20 < n <= 32
+                if ne * R <= (512 if shared and R > one else 256) and (R > one or shared):
                     assert rc == 1, (n, R, ne)
+                elif ne * -(-R // one) < 256 * wgs:
+                    assert nchunk == -(-R // one) and n * rc <= 64, (n, R, ne)
+                else:
+                    assert rc == 1 or ne * nchunk >= 512, (n, R, ne)
 
 
 def test_cut_columns_of_whole_lines_stay_in_whole_lines(cut):
