@@ -480,16 +480,12 @@ void build_device(Handle& h, Team& team) {
   auto& d = h.d;
   int E = h.E;
   d.elem_cls = upload(h, h.cls);
-  d.order = upload(h, h.order);
-  d.slot_off = upload(h, h.slot_off);
-  d.cm_off = upload(h, h.cm_off);
   d.dof_off = upload(h, h.dof_off);
   d.row_slot = upload(h, h.row_slot);
   d.row_coef = upload(h, h.row_coef);
   d.row_xinv = upload(h, h.row_xinv);
   d.slot_row = upload(h, h.slot_row);
   d.slot_coef = upload(h, h.slot_coef);
-  d.slot_mode = upload(h, h.slot_mode);
   d.t_ptr = upload(h, h.t_ptr);
   d.t_dof = upload(h, h.t_dof);
   d.t_coef = upload(h, h.t_coef);
@@ -504,7 +500,6 @@ void build_device(Handle& h, Team& team) {
   d.cdof_ptr = upload(h, h.cdof_ptr);
   d.cdof_list = upload(h, h.cdof_list);
   d.cdof_coef = upload(h, h.cdof_coef);
-  d.cm_mode = upload(h, h.cm_mode);
   d.c2_ptr = upload(h, h.c2_ptr);
   d.c2_dof = upload(h, h.c2_dof);
   d.c2_coef = upload(h, h.c2_coef);
@@ -534,7 +529,7 @@ void build_device(Handle& h, Team& team) {
   d.cm_pos = upload(h, cm_pos);
   // class tables and operators
   int NC = int(h.classes.size());
-  std::vector<int> cn(NC), cm(NC), cnr(NC);
+  std::vector<int> cn(NC);
   std::vector<int64_t> o_op1(NC), o_phi(NC), o_se(NC);
   std::vector<double2> op1, phi, Dinv, Kc;
   std::vector<double2> se;
@@ -543,7 +538,7 @@ void build_device(Handle& h, Team& team) {
   std::vector<SepClass> sc(NC);
   for (int c = 0; c < NC; ++c) {
     const ElemClass& C = h.classes[c];
-    cn[c] = C.n; cm[c] = C.m; cnr[c] = C.nr;
+    cn[c] = C.n;
     o_op1[c] = op1.size(); o_phi[c] = phi.size(); o_se[c] = se.size();
     for (auto& v : C.Op1.a) op1.push_back(make_double2(v.real(), v.imag()));
     for (auto& v : C.Phi.a) phi.push_back(make_double2(v.real(), v.imag()));
@@ -575,14 +570,13 @@ void build_device(Handle& h, Team& team) {
     gam.insert(gam.end(), C.Gam.begin(), C.Gam.end());
     rmod.insert(rmod.end(), C.R.begin(), C.R.end());
   }
-  d.cls_n = upload(h, cn); d.cls_m = upload(h, cm); d.cls_nr = upload(h, cnr);
-  d.cls_op1 = upload(h, o_op1); d.cls_phi = upload(h, o_phi); d.cls_se = upload(h, o_se);
+  d.cls_n = upload(h, cn);
   {
     // flattened per-block and per-slot tables of the slot kernels
     std::vector<SlotBlock> blk(E);
     for (int b = 0; b < E; ++b) {
       const int e = h.order[b], c = h.cls[e];
-      blk[b] = SlotBlock{o_op1[c], o_se[c], o_phi[c], e, c, h.slot_off[e], h.cm_off[e], cm[c], cnr[c], 0, 0};
+      blk[b] = SlotBlock{o_op1[c], o_se[c], o_phi[c], e, c, h.slot_off[e], h.cm_off[e], h.classes[c].m, h.classes[c].nr, 0, 0};
     }
     d.slot_blk = upload(h, blk);
     const size_t ns = h.slot_row.size();

@@ -255,15 +255,15 @@ struct Handle {
   // device buffers --------------------------------------------------------
   struct Dev {
     // maps
-    int *elem_cls = nullptr, *order = nullptr, *slot_off = nullptr, *cm_off = nullptr;
+    int* elem_cls = nullptr;
     SlotBlock* slot_blk = nullptr;
     SlotIn* slot_in[3] = {nullptr, nullptr, nullptr};   // modes 0 (F), 1 (P, rows), 2 (P, slots)
     SlotOut* slot_out = nullptr;
     int64_t* dof_off = nullptr;
-    int *row_slot = nullptr, *slot_row = nullptr, *slot_mode = nullptr;
+    int *row_slot = nullptr, *slot_row = nullptr;
     int64_t *slot_pos = nullptr, *cm_pos = nullptr;   // positions in full-element arrays
     double *row_coef = nullptr, *row_xinv = nullptr, *slot_coef = nullptr;
-    int *t_ptr = nullptr, *t_dof = nullptr, *cdof_ptr = nullptr, *cdof_list = nullptr, *cm_mode = nullptr;
+    int *t_ptr = nullptr, *t_dof = nullptr, *cdof_ptr = nullptr, *cdof_list = nullptr;
     double *t_coef = nullptr, *cdof_coef = nullptr;
     // the identity expansion with coefficient -1 (coarse mode i -> entry i of a
     // [ncm][R] array): the slot coarse correction then applies -Phi to
@@ -310,11 +310,10 @@ struct Handle {
     int4* nd_top_tasks = nullptr;
     int64_t nd_ld = 0;
     // per-class tables
-    int *cls_n = nullptr, *cls_m = nullptr, *cls_nr = nullptr;
+    int* cls_n = nullptr;
     SepElem* sep_elem = nullptr;
     SepItem* sep_items = nullptr;
     double *sep_mat = nullptr, *sep_gll = nullptr;   // eigenbases, GLL sampling matrices
-    int64_t *cls_op1 = nullptr, *cls_phi = nullptr, *cls_se = nullptr;   // offsets
     int *gam_modes = nullptr, *r_modes = nullptr;   // dual-slot and coarse modes of every class
     // operators
     double2 *op1 = nullptr, *phi = nullptr;   // FP64
@@ -483,7 +482,6 @@ void nd_units(const Handle& h, NDHost& f, bool bwd, ND1Plan& p);
 constexpr int ND_SPLITS[] = {256, 512, 1024, 2048};
 // most unknowns of the dense top block of the nested-dissection sweeps
 constexpr int64_t ND_TOP_MAX = 3072;
-void build_device(Handle& h);
 // Element loads of the elements with a non-zero load: elems lists them and
 // vals holds their blocks back to back, each [n_e^2][R].
 void compute_loads(const Handle& h, const hdp_rhs* rhs, int R, std::vector<int>& elems, std::vector<cd>& vals);

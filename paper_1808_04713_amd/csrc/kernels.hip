@@ -1194,107 +1194,7 @@ __global__ void __launch_bounds__(NT) k_coarse_minus_tw(int ncm, int R, const in
 }
 
 // ---------------------------------------------------------------------------
-// Krylov kernels.  R divides NT; thread t owns RHS column t % R.
-__global__ void __launch_bounds__(NT) k_dots(const double2* __restrict__ V, int64_t vstride, int nvec,
-                                             const double2* __restrict__ w, int n, int R,
-                                             double2* __restrict__ part) {
-  __shared__ double2 red[NT];
-  const int r = threadIdx.x % R;
-  const int rl = threadIdx.x / R;
-  const int step = NT / R;
-  const int64_t chunk = ((int64_t)n + gridDim.x - 1) / gridDim.x;
-  const int64_t lo = (int64_t)blockIdx.x * chunk;
-  const int64_t hi = min((int64_t)n, lo + chunk);
-  for (int i = 0; i < nvec; ++i) {
-    const double2* Vi = V + (int64_t)i * vstride;
-    double ax = 0, ay = 0;
-    for (int64_t row = lo + rl; row < hi; row += step) {
-      double2 a = Vi[row * R + r], b = w[row * R + r];
-      ax += a.x * b.x + a.y * b.y;
-      ay += a.x * b.y - a.y * b.x;
-    }
-    red[threadIdx.x] = make_double2(ax, ay);
-    __syncthreads();
-    for (int s = NT / 2; s >= R; s >>= 1) {
-      if (threadIdx.x < s) {
-        red[threadIdx.x].x += red[threadIdx.x + s].x;
-        red[threadIdx.x].y += red[threadIdx.x + s].y;
-      }
-      __syncthreads();
-    }
-    if (threadIdx.x < R) part[((int64_t)blockIdx.x * nvec + i) * R + threadIdx.x] = red[threadIdx.x];
-    __syncthreads();
-  }
-}
-
-__global__ void k_dots_final(const double2* __restrict__ part, int nblk, int nvec, int R,
-                             double2* __restrict__ h, double2* __restrict__ hsum) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nvec * R) return;
-  double ax = 0, ay = 0;
-  for (int b = 0; b < nblk; ++b) {
-    double2 a = part[(int64_t)b * nvec * R + idx];
-    ax += a.x;
-    ay += a.y;
-  }
-  h[idx] = make_double2(ax, ay);
-  if (hsum) {
-    hsum[idx].x += ax;
-    hsum[idx].y += ay;
-  }
-}
-
-__global__ void k_update(const double2* __restrict__ V, int64_t vstride, int nvec,
-                         const double2* __restrict__ hc, double2* __restrict__ w, int n, int R, double sign) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)n * R) return;
-  int r = int(idx % R);
-  double2 acc = w[idx];
-  for (int i = 0; i < nvec; ++i) {
-    double2 p = cmul(V[(int64_t)i * vstride + idx], hc[i * R + r]);
-    acc.x += sign * p.x;
-    acc.y += sign * p.y;
-  }
-  w[idx] = acc;
-}
-
-__global__ void __launch_bounds__(NT) k_norm_part(const double2* __restrict__ w, int n, int R,
-                                                  double* __restrict__ part) {
-  __shared__ double red[NT];
-  const int r = threadIdx.x % R;
-  const int rl = threadIdx.x / R;
-  const int rows_per_pass = NT / R;
-  double acc = 0;
-  for (int64_t row = (int64_t)blockIdx.x * rows_per_pass + rl; row < n; row += (int64_t)gridDim.x * rows_per_pass) {
-    double2 a = w[row * R + r];
-    acc += a.x * a.x + a.y * a.y;
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = NT / 2; s >= R; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x < R) part[blockIdx.x * R + threadIdx.x] = red[threadIdx.x];
-}
-
-__global__ void k_norm_final(const double* __restrict__ part, int nblk, int R, double* __restrict__ nrm) {
-  int r = threadIdx.x;
-  if (r >= R) return;
-  double s = 0;
-  for (int b = 0; b < nblk; ++b) s += part[b * R + r];
-  nrm[r] = sqrt(s);
-}
-
-__global__ void k_scale(const double2* __restrict__ w, const double* __restrict__ nrm, double2* __restrict__ out,
-                        int n, int R) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)n * R) return;
-  double d = nrm[idx % R];
-  double s = d > 0 ? 1.0 / d : 0.0;
-  out[idx] = make_double2(w[idx].x * s, w[idx].y * s);
-}
-
+// Vector kernels.
 __global__ void k_axpby(const double2* __restrict__ x, const double2* __restrict__ y, double2* __restrict__ z,
                         int64_t count, double a, double b) {
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1306,10 +1206,6 @@ __global__ void k_axpby(const double2* __restrict__ x, const double2* __restrict
 __global__ void k_cast_f(const double2* __restrict__ x, float2* __restrict__ y, int64_t count) {
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < count) y[idx] = make_float2(float(x[idx].x), float(x[idx].y));
-}
-__global__ void k_cast_d(const float2* __restrict__ x, double2* __restrict__ y, int64_t count) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < count) y[idx] = make_double2(double(x[idx].x), double(x[idx].y));
 }
 
 // Far field, step 1: trace u and normal derivative d_n' u at the Gauss nodes of
@@ -2422,7 +2318,7 @@ inline int pow2_at_least(int x) {
 
 // ---------------------------------------------------------------------------
 // shared memory of the matrix-core slot kernels at R columns, or 0 when they do
-// not apply (R not 16, 32 or 64, or an element's operand or output rows do not
+// not apply (R not a multiple of 16, or an element's operand or output rows do not
 // fit: at most 64 KB and 16 output tiles per element)
 
 // columns per block of the matrix-core slot operators: the handle's choice
@@ -2801,39 +2697,6 @@ void launch_gmres_init(const double* nrm, double* beta, double2* g, int* done, i
   HIPCHECK(hipGetLastError());
 }
 
-int dots_blocks(int n, int R) {
-  int64_t want = (int64_t(n) * R + NT - 1) / NT;
-  return int(std::max<int64_t>(1, std::min<int64_t>(512, want)));
-}
-
-void launch_dots(const double2* V, int64_t vstride, int nvec, const double2* w, int n, int R, double2* part, int nblk,
-                 hipStream_t s) {
-  hipLaunchKernelGGL(k_dots, dim3(nblk), dim3(NT), 0, s, V, vstride, nvec, w, n, R, part);
-  HIPCHECK(hipGetLastError());
-}
-
-void launch_dots_final(const double2* part, int nblk, int nvec, int R, double2* hh, double2* hsum, hipStream_t s) {
-  hipLaunchKernelGGL(k_dots_final, dim3(nblocks(int64_t(nvec) * R)), dim3(NT), 0, s, part, nblk, nvec, R, hh, hsum);
-  HIPCHECK(hipGetLastError());
-}
-
-void launch_update(const double2* V, int64_t vstride, int nvec, const double2* hc, double2* w, int n, int R,
-                   double sign, hipStream_t s) {
-  hipLaunchKernelGGL(k_update, dim3(nblocks(int64_t(n) * R)), dim3(NT), 0, s, V, vstride, nvec, hc, w, n, R, sign);
-  HIPCHECK(hipGetLastError());
-}
-
-void launch_norm(const double2* w, int n, int R, double* part, int nblk, double* nrm, hipStream_t s) {
-  hipLaunchKernelGGL(k_norm_part, dim3(nblk), dim3(NT), 0, s, w, n, R, part);
-  hipLaunchKernelGGL(k_norm_final, dim3(1), dim3(NT), 0, s, part, nblk, R, nrm);
-  HIPCHECK(hipGetLastError());
-}
-
-void launch_scale(const double2* w, const double* nrm, double2* out, int n, int R, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale, dim3(nblocks(int64_t(n) * R)), dim3(NT), 0, s, w, nrm, out, n, R);
-  HIPCHECK(hipGetLastError());
-}
-
 void launch_axpby(const double2* x, const double2* y, double2* z, int64_t count, double a, double b, hipStream_t s) {
   hipLaunchKernelGGL(k_axpby, dim3(nblocks(count)), dim3(NT), 0, s, x, y, z, count, a, b);
   HIPCHECK(hipGetLastError());
@@ -2841,11 +2704,6 @@ void launch_axpby(const double2* x, const double2* y, double2* z, int64_t count,
 
 void launch_cast_f(const double2* x, float2* y, int64_t count, hipStream_t s) {
   hipLaunchKernelGGL(k_cast_f, dim3(nblocks(count)), dim3(NT), 0, s, x, y, count);
-  HIPCHECK(hipGetLastError());
-}
-
-void launch_cast_d(const float2* x, double2* y, int64_t count, hipStream_t s) {
-  hipLaunchKernelGGL(k_cast_d, dim3(nblocks(count)), dim3(NT), 0, s, x, y, count);
   HIPCHECK(hipGetLastError());
 }
 

@@ -72,19 +72,10 @@ void launch_sep_full(const Handle& h, const double2* in, double2* out, int R, hi
 void launch_gll(const Handle& h, const double2* X, double2* field, int R, int64_t rhs_stride,
                 int nrhs_out, hipStream_t s);
 
-// Krylov vector kernels (R must divide 256)
-void launch_dots(const double2* V, int64_t vstride, int nvec, const double2* w, int n, int R,
-                 double2* part, int nblk, hipStream_t s);
-void launch_dots_final(const double2* part, int nblk, int nvec, int R, double2* h, double2* hsum,
-                       hipStream_t s);
-void launch_update(const double2* V, int64_t vstride, int nvec, const double2* hcoef, double2* w,
-                   int n, int R, double sign, hipStream_t s);
-void launch_norm(const double2* w, int n, int R, double* part, int nblk, double* nrm, hipStream_t s);
-void launch_scale(const double2* w, const double* nrm, double2* out, int n, int R, hipStream_t s);
+// Vector kernels
 void launch_axpby(const double2* x, const double2* y, double2* z, int64_t count, double a, double b,
                   hipStream_t s);
 void launch_cast_f(const double2* x, float2* y, int64_t count, hipStream_t s);
-void launch_cast_d(const float2* x, double2* y, int64_t count, hipStream_t s);
 // Nested-dissection coarse solve (device views of the node tables and the factor).
 struct NDView {
   const int* off = nullptr;
@@ -137,7 +128,6 @@ void launch_plane_wave_loads(const Handle& h, int kind, const int* elems, int ne
 // far field of the recovered fields X ([dof][R]) into E ([nrhs_out][nfar]) using h.far
 void launch_far_adjoint(const Handle& h, double2* G, hipStream_t s);
 void launch_far_field(const Handle& h, const double2* X, int R, int nrhs_out, double2* E, hipStream_t s);
-int dots_blocks(int n, int R);
 
 // Device-resident GMRES (R divides 64; j read from device memory when jptr != nullptr)
 struct GmresDims {
