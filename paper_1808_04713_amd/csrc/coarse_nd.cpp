@@ -14,7 +14,7 @@
 //   forward  (leaves first):  Y_I = front_I,  U = front_B - L Y_I
 //   backward (root first):    X_I = Dinv Y_I - L^T X_B.
 // Pivoting is partial inside each F_II (Gauss-Jordan); the blocks are taken in
-// tree order, as the strip factor takes its strips in order.
+// tree order.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -346,7 +346,7 @@ void nd_tasks(const Handle& h, NDHost& f, int target) {
         if (nout > 0) kmax = std::max(kmax, bwd ? nI_of(t) + nB_of(t) : nI_of(t));
       }
       int S = 1;
-      if (ntiles > 0) S = std::max(1, std::min((target + ntiles - 1) / ntiles, (kmax + 63) / 64));   // at least 16 rows for each of a tile's four waves
+      if (ntiles > 0) S = std::max(1, std::min((target + ntiles - 1) / ntiles, (kmax + 63) / 64));   // ranges of the longest sums keep more than 32 rows
       std::vector<int4>& T = bwd ? f.tRb : f.tRf;
       const int first = int(T.size());
       // nodes with the longest sums first: a depth whose tiles overflow one round
@@ -381,7 +381,11 @@ void nd_tasks(const Handle& h, NDHost& f, int target) {
 // and consecutive ones become the stages of one launch, a workgroup per subtree rooted
 // at the shallowest of them, while there are ND1_MIN_ROOTS subtrees (half the compute
 // units) and none holds more than ND1_MAX_WORK factor entries (0.6 MB, some 5 us for
-// a compute unit at 0.13 MB per us, about what the merged launches save).
+// a compute unit at 0.13 MB per us, about what the merged launches save).  Backward,
+// where sums are longer by the boundary, only such stages do: a single depth in units
+// took 4.3 us, by rows 3.7 (96x96 elements, l = 1).  They come with the small leaves of
+// a requested factor: 545 us in stages, 582 by rows, for the 15 backward sweeps of a
+// solve on 64x64 elements, l = 2.
 //
 // Backward units read D by columns; so that they use the same inverse as the rows
 // (the computed D is symmetric only up to its own error, which a nearly singular
@@ -447,7 +451,7 @@ void nd_units(const Handle& h, NDHost& f, bool bwd, ND1Plan& p) {
   for (auto& b : batches) {
     ND1Launch L;
     L.stages = b.second - b.first + 1;
-    if (L.stages == 1 && long_sums(b.first)) {
+    if (L.stages == 1 && (bwd || long_sums(b.first))) {
       L.rows = true;
       L.first = int64_t(p.rows.size());
       for (int t : by_depth[b.first])
