@@ -7,8 +7,8 @@
 // has two slots, one per child, so the updates are plain stores and a slot row that
 // no child writes stays zero from set-up.
 //
-// One column.  What bounds it near the root is the chain record -> operands -> sums -> store of a
-// launch, about 4 us for 5 to 30 MB of factor; near the leaves the number of waves,
+// One column.  What bounds it near the root is the chain record -> operands -> sums ->
+// store of a launch, about 4 us for 5 to 30 MB of factor; near the leaves the number of waves,
 // as fronts there own 10 to 60 unknowns.  So two forms:
 //  - k_nd1_row, long sums: a wave per output, its lanes along the row;
 //  - k_nd1, short sums and many outputs: the product as out(j) = sum_k M[k][j] z_k with
@@ -20,8 +20,8 @@
 //    subtree: the stages of a launch are consecutive depths, with a barrier between
 //    instead of a launch.
 // nd_units (coarse_nd.cpp) has the rules.  One coarse solve of the 80x80 layered
-// scatterer (n_K = 71,361): 23 launches and a clearing, 212 us, with a wave per output
-// at every depth; 19 launches, 160 us, of which the subtrees' two take 41.
+// scatterer (n_K = 71,361), within its GMRES: 21 launches and a clearing, 177 us, with a
+// wave per output at every depth and atomic updates; 19 launches, 131 us.
 //
 // Several columns: k_nd_tile, below, also for the dense inverse (a one-node tree).
 #include <hip/hip_runtime.h>
