@@ -154,7 +154,9 @@ typedef struct {
   int32_t flags;              /* HDP_FLAG_* bits, 0 for defaults */
   int32_t tile_fdm;           /* right-hand sides per workgroup of the separable element solve on
                                  the matrix cores (1, 2, 4, 8 or 16; 0: the autotuner's choice
-                                 with HDP_FLAG_AUTOTUNE, else a shared-memory heuristic) */
+                                 with HDP_FLAG_AUTOTUNE, else a rule on modes, elements and
+                                 columns, which also takes the place of a width that does not
+                                 fit a workgroup) */
   int32_t tile_slot;          /* right-hand sides per workgroup of the matrix-core slot operators
                                  at 16 or more columns (16, 32 or 64; 0: autotuned or 32) */
   hdp_allocator allocator;    /* device memory of the handle (zero: hipMalloc / hipFree) */
@@ -172,7 +174,7 @@ typedef struct {
 #define HDP_FLAG_COARSE_BLOCK 2
 #define HDP_FLAG_COARSE_DENSE 4
 #define HDP_FLAG_COARSE_ND 8
-/* time every candidate tile width of the separable element solve and of the
+/* time every candidate tile width that fits, of the separable element solve and of the
    matrix-core slot operators, and (nested-dissection coarse factor, max_rhs > 1)
    every split target of the coarse sweeps, at set-up, on the handle's own mesh
    at max_rhs columns, and keep the fastest (hdp_autotune_table lists the
